@@ -71,9 +71,9 @@ size_t itq3s_scales_bytes(int64_t N, int64_t K);
 /* Bytes of scratch itq3s_matmul needs (Sec. 2.3: H is symmetric and its own inverse, so
  * <H v, x> = <v, H x>; the library rotates X once per call instead of every weight block).  Never 0.
  * M <= 4: 256 (the streaming kernel rotates inside the kernel; the workspace is not touched).
- * Larger M: room for the rotated activations, grows with M*K; for M > 16 and shapes with few output
- * tiles (at most 128 tiles of 128 x 256) also the partial sums of the workgroups that share a tile's
- * K range (up to 8 x M x N x 4 bytes, tiles rounded up).  A function of the three sizes only. */
+ * Larger M: room for the rotated activations (rows rounded up), grows with M*K; for M > 16 and shapes with
+ * few output tiles (at most 128 tiles of 128 x 256) also the partial sums of the workgroups that share a
+ * tile's K range (up to 8 x M x N x 4 bytes, tiles rounded up).  A function of the three sizes only. */
 size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /* Offline quantization (Alg. 1, Def. 1).  Per block: w' = H w in fp64 (butterfly stages
@@ -96,10 +96,11 @@ int itq3s_dequantize(const uint32_t *codes, const uint32_t *scales, int64_t N, i
                      int64_t ldo, uint32_t *status_flags, void *stream);
 
 /* Fused matmul (problem statement of Alg. 2; Sec. 5.4 for M = 1):  Y[m][n] = sum_k X[m][k] w_hat[n][k].
- * No dequantized weight is written to memory.  M <= 16 takes the bandwidth-bound streaming path
- * (M <= 32: two passes of it), larger M the tiled MFMA path (which accepts K <= 4194304 only:
- * ITQ3S_ERR_SHAPE beyond; the streaming path K <= 2^28); fp32 accumulation in both, the zero-point
- * terms included: an output element is rounded once.
+ * No dequantized weight is written to memory.  M <= 16 takes the bandwidth-bound streaming path, more
+ * rows a second streaming kernel as long as 2 M N K stays below about 36 GFLOP (any N for M <= 64;
+ * K <= 262144), larger calls the tiled MFMA path (M <= 32 beyond that K: two passes of the first).  M > 16
+ * accepts K <= 4194304 only: ITQ3S_ERR_SHAPE beyond; M <= 16 K <= 2^28.  fp32 accumulation in all, the
+ * zero-point terms included: an output element is rounded once.
  * Activation range.  Every 256-channel chunk x of a row of X is replaced by x~ = H x, rounded to
  * fp16, after an intermediate T = X_16x16 H_16 / 4 that is split into fp16 parts.  Both stay
  * finite whenever  max|x| <= 16376  and  |(H x)_k| <= 65504  over the chunk (the second holds if
@@ -132,8 +133,8 @@ int itq3s_matmul_static(const uint32_t *codes, const uint32_t *scales, int64_t N
 
 /* Several weight tensors with the same K against the same activations in ONE call: Y_t = X W_hat_t^T
  * for t = 0..count-1 (1 <= count <= ITQ3S_MAX_GROUP), e.g. the query/key/value projections of a layer,
- * or gate and up.  For M <= 16 all tensors are served by a single launch of the streaming kernel, so
- * the launch latency and the ramp of the memory pipeline are paid once; for larger M the activations
+ * or gate and up.  All tensors that a streaming kernel takes (itq3s_matmul) are served by a single launch, so the
+ * launch latency and the ramp of the memory pipeline are paid once; for the others the activations
  * are rotated once and one tiled launch per tensor follows.  Results are identical to count calls of
  * itq3s_matmul.
  *   w  [in] HOST array of count descriptors (read during the call, not kept): device pointers codes,

@@ -51,8 +51,8 @@ constexpr int64_t kChunkedMaxM = 2 * itq3s::kGemvMaxM;  // up to here M > 16 run
 constexpr int64_t kSubStreamingMaxM = 64;               // sub-block variant: up to here passes of four rows, the tiled weight-side kernel above
 
 WorkspacePlan plan_workspace(int64_t M, int64_t N, int64_t K) {
-    if (M > itq3s::kGemvMaxM && M <= kChunkedMaxM) return plan_workspace(itq3s::kGemvMaxM, N, K);
     WorkspacePlan p;
+    if (M > itq3s::kGemvMaxM && M <= kChunkedMaxM) return plan_workspace(itq3s::kGemvMaxM, N, K);
     if (M <= itq3s::kGemvFusedMaxM) {  // the streaming kernel rotates the activations itself: nothing to park
         p.xt_bytes = p.s_bytes = p.flag_bytes = p.partial_bytes = 0;
         p.total = 256;
@@ -108,7 +108,11 @@ size_t itq3s_scales_bytes(int64_t N, int64_t K) {
 
 size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0 || K % 256 != 0) return 256;
-    return plan_workspace(M, N, K).total;
+    // (what the call needs is the larger of the two for a tensor that the streaming kernel for many rows
+    // takes; a size that held before that kernel was there still holds)
+    const size_t rows = itq3s::rows_path(M, N, K) ? round_up(itq3s::rows_xt_bytes(M, K), 256) + round_up(itq3s::rows_x0_bytes(M, K), 256) : 0;
+    const size_t other = plan_workspace(M, N, K).total;
+    return rows > other ? rows : other;
 }
 
 int itq3s_quantize(const float* W, int64_t N, int64_t K, int64_t ldw, uint32_t* codes, uint32_t* scales, uint32_t* status_flags,
@@ -167,6 +171,26 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
     if (!aligned(workspace, 256)) return ITQ3S_ERR_ALIGN;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
+    // Tensors that the streaming kernel for many rows takes go first, in one launch; what is left is
+    // computed as if it were a call of its own (its scratch lies over theirs: same stream, one after the other).
+    itq3s_weight rest[ITQ3S_MAX_GROUP];
+    if (M > itq3s::kGemvMaxM) {
+        itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
+        int n_rows = 0, n_rest = 0;
+        for (int i = 0; i < count; ++i) {
+            if (itq3s::rows_path(M, w[i].N, K)) gw[n_rows++] = itq3s::GemvWeight{w[i].codes, w[i].scales, w[i].N, w[i].Y, w[i].ldy};
+            else rest[n_rest++] = w[i];
+        }
+        if (n_rows > 0) {
+            unsigned char* const base = static_cast<unsigned char*>(workspace);
+            const int rc = itq3s::launch_rows(gw, n_rows, K, static_cast<const _Float16*>(X), ldx, M, reinterpret_cast<_Float16*>(base),
+                                              reinterpret_cast<_Float16*>(base + round_up(itq3s::rows_xt_bytes(M, K), 256)),
+                                              y_dtype == ITQ3S_F16, status_flags, st);
+            if (rc != 0 || n_rest == 0) return rc;
+            w = rest;
+            count = n_rest;
+        }
+    }
     if (M > itq3s::kGemvMaxM && M <= kChunkedMaxM) {
         // A few rows more than the streaming kernel takes at once: two passes of it over the weights
         // are still faster than the tiled kernel, whose 128-row tiles would be mostly empty.

@@ -36,13 +36,12 @@
 #include <type_traits>
 
 #include "itq3s_kernels.h"
+#include "itq3s_stream.h"
 
 namespace itq3s {
 
 constexpr int kGemvWaves = 8;      // wavefronts per workgroup
 constexpr int kGemvMaxRT = 3;      // row tiles per workgroup, at most (7 registers per tile and buffer; four would cost the second workgroup per compute unit)
-constexpr int kRawBuffer = 0x00027000;  // buffer descriptor word 3: raw buffer of 32-bit elements
-constexpr int kLoadNT = 2;         // cache policy of the weight loads: nontemporal (read once)
 
 static thread_local LaunchTiming g_timing;  // armed and taken on the calling thread
 void set_launch_timing(hipEvent_t start, hipEvent_t stop) { g_timing.start = start; g_timing.stop = stop; }
@@ -51,20 +50,6 @@ LaunchTiming take_launch_timing() {
     g_timing = LaunchTiming{};
     return t;
 }
-
-// One launch serves up to kGemvMaxGroup weight tensors that share K and the activations (the
-// projections of one layer that read the same input).  Their 16-row tiles are numbered as one list,
-// tensor after tensor, and split evenly over the workgroups; a workgroup's tiles may belong to two
-// tensors.
-struct GemvTensor {
-    const uint32_t* codes;
-    const uint32_t* scales;
-    const uint32_t* subscales;  // the 116-byte variant's sub-scale array, or null
-    void* Y;
-    int64_t N, ldy;
-    int v_begin;  // position of this tensor's first row tile in the list (0x7fffffff for unused entries)
-    int pad_;
-};
 
 struct GemvArgs {
     GemvTensor t[kGemvMaxGroup];
@@ -82,11 +67,6 @@ struct TileRegs {
     uint32_t sc;
     uint32_t ss;  // (sub-block variant) the lane's two sub-scales
 };
-
-__device__ __forceinline__ half8 as_half8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-    u32x4 u = {a, b, c, d};
-    return __builtin_bit_cast(half8, u);
-}
 
 // The 256-point transform on the matrix cores.  With the chunk written as a 16 x 16 matrix
 // X[a][b] = x[16a + b], the Sylvester construction gives H_256 = H_16 (x) H_16, i.e.
@@ -507,32 +487,12 @@ int cu_count() {
     return n;
 }
 
-// Fills the tensor list of a launch; returns the number of row tiles, or -1.
-static int64_t fill_tensors(GemvArgs& a, const GemvWeight* w, int count) {
-    int64_t nt_total = 0;
-    for (int i = 0; i < kGemvMaxGroup; ++i) {
-        GemvTensor& t = a.t[i];
-        if (i < count) {
-            t.codes = w[i].codes; t.scales = w[i].scales; t.subscales = w[i].subscales; t.Y = w[i].Y; t.N = w[i].N; t.ldy = w[i].ldy;
-            if (t.subscales != nullptr && count != 1) return -1;
-            if (nt_total > 0x7fffffff) return -1;
-            t.v_begin = (int)nt_total;
-            nt_total += (w[i].N + 15) / 16;
-        } else {
-            t = a.t[0];
-            t.v_begin = 0x7fffffff;
-        }
-        t.pad_ = 0;
-    }
-    return nt_total < 0x7fffffff ? nt_total : -1;
-}
-
 int launch_gemv(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, int y_f16, uint32_t* flags,
                 hipStream_t stream) {
     if (count < 1 || count > kGemvMaxGroup || M < 1 || M > kGemvFusedMaxM) return -2;
     GemvArgs a;
     a.X = X; a.S = nullptr; a.flags = flags; a.ldx = ldx; a.KB = (int)(K / kBlock); a.M = (int)M; a.y_f16 = y_f16;
-    const int64_t nt_total = fill_tensors(a, w, count);
+    const int64_t nt_total = fill_tensors(a.t, w, count);
     if (nt_total < 0) return -2;
     // Row tiles per workgroup (every workgroup rotates all of X for itself, so more tiles per workgroup
     // mean less of that; fewer mean more workgroups in flight).  Measured on the 7B and 70B shapes:
@@ -587,7 +547,7 @@ int launch_gemv_rows(const GemvWeight* w, int count, int64_t K, const _Float16* 
     if (count < 1 || count > kGemvMaxGroup || M <= kGemvFusedMaxM || M > kGemvMaxM || (MP != 8 && MP != 16) || M > MP) return -2;
     GemvArgs a;
     a.X = Xt; a.S = S; a.flags = flags; a.ldx = 0; a.KB = (int)(K / kBlock); a.M = (int)M; a.y_f16 = y_f16;
-    const int64_t nt_total = fill_tensors(a, w, count);
+    const int64_t nt_total = fill_tensors(a.t, w, count);
     if (nt_total < 0) return -2;
     // Every workgroup pulls all of the rotated activations (2 MP K bytes) through its compute unit's
     // L1: as many row tiles per workgroup as keep every compute unit busy, at most four (two steps of

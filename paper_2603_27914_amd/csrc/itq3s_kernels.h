@@ -65,6 +65,20 @@ int launch_gemv(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
 int launch_gemv_rows(const GemvWeight* w, int count, int64_t K, const _Float16* Xt, const float* S, int64_t M, int MP, int y_f16,
                      uint32_t* flags, hipStream_t stream);
 
+// The streaming kernel for more rows than launch_gemv_rows takes (rows_path() says for which calls):
+// rotates the activations into Xt (rows_xt_bytes) and X0 (rows_x0_bytes), both 256-byte aligned, then one
+// launch over all row tiles and groups of up to 64 rows.
+constexpr int64_t kRowsMaxM = 1 << 16;
+constexpr int64_t kRowsMaxK = 1 << 18;
+bool rows_path(int64_t M, int64_t N, int64_t K);
+size_t rows_xt_bytes(int64_t M, int64_t K);
+size_t rows_x0_bytes(int64_t M, int64_t K);
+int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, _Float16* Xt, _Float16* X0, int y_f16,
+                uint32_t* flags, hipStream_t stream);
+// Rotated activations for it: groups x mt tiles of 16 rows, layout at rotate_rows_kernel.
+int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int mt, int groups, _Float16* Xt, _Float16* X0, uint32_t* flags,
+                       hipStream_t stream);
+
 // Compute units of the current device (cached).
 int cu_count();
 

@@ -20,8 +20,7 @@ namespace itq3s {
 // elements e = 64 (l/16) + 16 i + l%16, i = 0..3.
 // Returns false if a rotated value (or the intermediate T, which then turns the result into NaN)
 // leaves the fp16 range.
-// `first` receives x[16 (l%16) + 4 (l/16)], the first of the lane's four inputs (lane 0: x[0]).
-__device__ __forceinline__ bool rotate_chunk(const _Float16* __restrict__ src, int lane, _Float16 out[4], _Float16* first = nullptr) {
+__device__ __forceinline__ bool rotate_operand(half4 xa, int lane, _Float16 out[4]) {
     const int r16 = lane & 15, g = lane >> 4;
     half4 h, q;  // H_16[4g + j][r16] and a quarter of it
 #pragma unroll
@@ -30,8 +29,6 @@ __device__ __forceinline__ bool rotate_chunk(const _Float16* __restrict__ src, i
         h[j] = neg ? (_Float16)(-1.0f) : (_Float16)1.0f;
         q[j] = neg ? (_Float16)(-0.25f) : (_Float16)0.25f;
     }
-    const half4 xa = *reinterpret_cast<const half4*>(src + 16 * r16 + 4 * g);
-    if (first != nullptr) *first = xa[0];
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
     const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, q, zero, 0, 0, 0);
     half4 th, tl;
@@ -49,6 +46,13 @@ __device__ __forceinline__ bool rotate_chunk(const _Float16* __restrict__ src, i
         ok = ok && __builtin_fabsf(U[i]) <= 4.0f * 65504.0f;  // (false for NaN as well)
     }
     return ok;
+}
+
+// The same from memory.  `first` receives the first of the lane's four inputs (lane 0: x[0]).
+__device__ __forceinline__ bool rotate_chunk(const _Float16* __restrict__ src, int lane, _Float16 out[4], _Float16* first = nullptr) {
+    const half4 xa = *reinterpret_cast<const half4*>(src + 16 * (lane & 15) + 4 * (lane >> 4));
+    if (first != nullptr) *first = xa[0];
+    return rotate_operand(xa, lane, out);
 }
 
 // Operand order of the streaming kernel.  The 16x16x32 MFMA of step t (0..7) takes from lane
@@ -96,6 +100,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     }
 }
 
+// Operand order of the streaming kernel for 17 and more rows (itq3s_rows.hip): rows in groups of 16 mt, a
+// group's fragments (t, mt) of a block one after another, 1 KiB each -- lane l = 16 g + r of the MFMA
+// operand finds its eight halves, the same elements as above, at 16 l.
+//   Xt index = ((((group*KB + b)*8 + t)*mts + mt)*64 + l)*8 + i,   row m = (group*mts + mt)*16 + r
+//   X0 index = ((group*KB + b)*4 + q)*stride + 4 mt + i = x[(group*mts + mt)*16 + 4 q + i][256 b], stride 8 for
+//              mts <= 2, else 16
+// Rows past M are zero.  A workgroup rotates 16 rows of one block, four per wavefront, and passes the
+// rounded values through LDS (rows in the channel order in which a lane's eight halves are neighbours),
+// so that every store is 16 bytes and a wavefront's are 1 KiB of consecutive addresses.
+constexpr int kRotRowStride = 264;  // halves; 528 bytes: 16-byte reads of 16 rows touch all banks
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rotate_rows_kernel(const _Float16* __restrict__ X, int M, int KB, int64_t ldx, int mts,
+                                                              _Float16* __restrict__ Xt, _Float16* __restrict__ X0, uint32_t* __restrict__ flags) {
+    __shared__ __align__(16) _Float16 rows[16 * kRotRowStride];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tile = (int)blockIdx.x / KB, b = (int)blockIdx.x - tile * KB;  // tile = group * mts + mt
+    const int group = tile / mts, mt = tile - group * mts;
+    half4 xa[4];
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+        const int m = tile * 16 + wave * 4 + rr;
+        xa[rr] = half4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+        if (m < M) xa[rr] = *reinterpret_cast<const half4*>(X + (int64_t)m * ldx + (int64_t)b * kBlock + 16 * (lane & 15) + 4 * (lane >> 4));
+    }
+    bool ok = true;
+    const int s = lane & 15;
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+        _Float16 r[4];
+        ok = rotate_operand(xa[rr], lane, r) && ok;
+        _Float16* const dst = rows + (wave * 4 + rr) * kRotRowStride + 64 * (lane >> 4) + 2 * (s & 7) + (s >> 3);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dst[16 * j] = r[j];
+    }
+    const int64_t gb = (int64_t)group * KB + b;
+    if (lane == 0) *reinterpret_cast<half4*>(X0 + (gb * 4 + wave) * (mts <= 2 ? 8 : 16) + 4 * mt) = half4{xa[0][0], xa[1][0], xa[2][0], xa[3][0]};
+    if (!ok && flags != nullptr) atomicOr(flags, kFlagActRange);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int t = wave + 4 * u;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(rows + (lane & 15) * kRotRowStride + 64 * (lane >> 4) + 16 * (t >> 1) + 8 * (t & 1));
+        *reinterpret_cast<u32x4*>(Xt + (((gb * 8 + t) * mts + mt) * 64 + lane) * 8) = v;
+    }
+}
+
 // Operand order of the tiled kernel: rows stay rows; inside every group of 16 channels, slot s moves
 // to position 2 (s & 7) + (s >> 3), the order in which the tile loader's unpack emits the weights.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rotate_rowmajor_kernel(const _Float16* __restrict__ X, int64_t M, int64_t K, int64_t ldx,
@@ -121,6 +170,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
 int launch_rotate_frag(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int MP, _Float16* Xt, float* S, uint32_t* flags, hipStream_t stream) {
     const int64_t chunks = (int64_t)MP * (K / kBlock);
     hipLaunchKernelGGL(rotate_frag_kernel, dim3((unsigned)((chunks + 3) / 4)), dim3(256), 0, stream, X, M, K, ldx, MP, Xt, S, flags);
+    return hipGetLastError() == hipSuccess ? 0 : -6;
+}
+
+int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int mt, int groups, _Float16* Xt, _Float16* X0, uint32_t* flags,
+                       hipStream_t stream) {
+    const int64_t tiles = (int64_t)mt * groups * (K / kBlock);
+    hipLaunchKernelGGL(rotate_rows_kernel, dim3((unsigned)tiles), dim3(256), 0, stream, X, (int)M, (int)(K / kBlock), ldx, mt, Xt, X0, flags);
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 

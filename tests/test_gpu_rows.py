@@ -1,0 +1,114 @@
+"""The streaming kernel for 17 and more activation rows at the sizes where its division of the work
+changes (padding of rows and row tiles, wavefronts without a block, several rounds of items, tensors
+that share an item), and the tiled kernel at ragged sizes large enough to reach it.  Checked on the
+device against itq3s_dequantize (held to the oracle within 1e-6 elsewhere) and a dense fp64 product."""
+import numpy as np
+import pytest
+
+from tests.packed_inputs import random_packed
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_27914_amd import binding
+
+    binding.lib()
+    return torch, binding
+
+
+def tensor(torch, binding, N, K, *key, z_fraction=0.02):
+    c, s = (torch.from_numpy(a.view(np.int32)).cuda() for a in random_packed(N, K, *key, z_fraction=z_fraction))
+    return c, s, binding.itq3s_dequantize(c, s, N, K).double()
+
+
+def check(Y, X, What, half):
+    """Per row: 2e-3 relative L2, the bar of every matmul test.  Per element: one rounding to fp16 of the
+    rotated activations (2^-11 relative each) against exact products, so at most 2^-11 ||x|| ||w_hat|| by
+    Cauchy-Schwarz, half as much again for the fp32 sums, and the rounding of the result."""
+    want = X.double() @ What.T
+    err = (Y.double() - want).abs()
+    bound = 1.5 * 2.0**-11 * X.double().norm(dim=1)[:, None] * What.norm(dim=1)[None, :] + 2.0 ** (-11 if half else -22) * want.abs() + 1e-30
+    assert (err / bound).max().item() <= 1.0
+    assert ((Y.double() - want).norm(dim=1) / want.norm(dim=1).clamp_min(1e-300)).max().item() <= 2e-3
+
+
+SIZES = [
+    (17, 16, 256),      # one row tile, one block: seven of eight wavefronts have nothing
+    (33, 1000, 2304),   # nine blocks: one wavefront has two; a ragged last row tile
+    (48, 257, 4096),
+    (49, 4100, 512),    # 64 rows, 15 of them padding
+    (64, 9000, 768),    # 563 row tiles: three per workgroup, the last item one short
+    (65, 300, 2048),    # two groups of 48 rows
+    (97, 17000, 256),   # two rounds of items of four row tiles
+    (130, 1032, 1280),  # three groups
+    (160, 4096, 1024),
+    (257, 333, 11008),
+    (1024, 2048, 512),
+    (70, 40, 262144),   # the longest K the kernel takes at this M is below this: the tiled kernel
+    (64, 40, 262144),   # the longest K
+    (20, 24, 262400),   # one block more: two passes of the kernel for up to 16 rows
+]
+
+
+@pytest.mark.parametrize("M,N,K", SIZES)
+def test_many_rows(gpu, M, N, K):
+    torch, binding = gpu
+    codes, scales, What = tensor(torch, binding, N, K, "rows", M)
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    buf = torch.randn((M, K + 8), generator=gen, device="cuda").half()
+    X = buf[:, :K]
+    for dtype in (torch.float32, torch.float16):
+        out = torch.full((M, N + 3), 7.0, dtype=dtype, device="cuda")
+        flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+        binding.itq3s_matmul(codes, scales, N, K, X, out=out[:, :N], status_flags=flags)
+        assert int(flags.item()) == 0 and bool((out[:, N:] == 7.0).all())
+        check(out[:, :N], X, What, dtype == torch.float16)
+
+
+@pytest.mark.parametrize("M", [24, 40, 64, 100])
+def test_many_rows_grouped_equals_single_calls(gpu, M):
+    """Items that span tensors (16 + 1000 + 17 + 300 rows, and 256-tile tensors with three tiles per item),
+    and a group in which one tensor is large enough for the tiled kernel."""
+    torch, binding = gpu
+    groups = [(512, [16, 1000, 17, 300]), (1024, [4096, 4096, 4096])]
+    if M == 100:
+        groups.append((8192, [24576, 500]))
+    for K, Ns in groups:
+        ts = [tensor(torch, binding, N, K, "rowsg", i) for i, N in enumerate(Ns)]
+        X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
+        outs = binding.itq3s_matmul_grouped([(c, s, N) for (c, s, _), N in zip(ts, Ns)], K, X, dtype=torch.float16)
+        for (c, s, What), N, out in zip(ts, Ns, outs):
+            assert torch.equal(out, binding.itq3s_matmul(c, s, N, K, X, dtype=torch.float16))
+            check(out, X, What, True)
+
+
+def test_many_rows_flags(gpu):
+    torch, binding = gpu
+    M, N, K = 50, 100, 1024
+    codes, scales, _ = tensor(torch, binding, N, K, "rowsf")
+    X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda").half()
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    bad = codes.clone()
+    bad[384 * 9 + 256 + 5] = 1  # a high-plane bit
+    binding.itq3s_matmul(bad, scales, N, K, X, status_flags=flags)
+    assert int(flags.item()) == binding.FLAG_BAD_CODE
+    flags.zero_()
+    X[49, 256:512] = 5000.0  # rotates to a spike of 16 x 5000 > 65504
+    binding.itq3s_matmul(codes, scales, N, K, X, status_flags=flags)
+    assert int(flags.item()) == binding.FLAG_ACT_RANGE
+
+
+# rotated activations of more than 32 MB, or a product too large for the streaming kernel
+@pytest.mark.parametrize("M,N,K,z", [(8200, 100, 2048, 0.02), (2100, 300, 8192, 0.6), (4200, 700, 4096, 0.0), (66000, 17, 256, 0.02), (517, 9300, 4096, 0.02)])
+def test_tiled_kernel_ragged(gpu, M, N, K, z):
+    torch, binding = gpu
+    codes, scales, What = tensor(torch, binding, N, K, "tiled", M, z_fraction=z)
+    X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
+    for dtype in (torch.float32, torch.float16):
+        check(binding.itq3s_matmul(codes, scales, N, K, X, dtype=dtype), X, What, dtype == torch.float16)
