@@ -49,4 +49,15 @@ __device__ __forceinline__ double row_xor_f64(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// H_16[4g + j][r16] / 4, j = 0..3: B operand of the first product, A operand of the second.  The sign of an
+// entry is the parity of (4g + j) & r16: that of 4g & r16, flipped for j = 1, 3 by bit 0 of r16 and for
+// j = 2, 3 by bit 1.
+__device__ __forceinline__ half4 hadamard_quarter(int lane) {
+    const uint32_t r = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4;
+    const uint32_t s = (g & (r >> 2)) ^ ((g >> 1) & (r >> 3));
+    const uint32_t lo = ((s & 1u) << 15) | (((s ^ r) & 1u) << 31);
+    const uint32_t w0 = 0x34003400u ^ lo, w1 = w0 ^ ((r >> 1) & 1u) * 0x80008000u;
+    return __builtin_bit_cast(half4, u32x2{w0, w1});
+}
+
 }  // namespace itq3s

@@ -72,54 +72,39 @@ struct TileRegs {
 // X[a][b] = x[16a + b], the Sylvester construction gives H_256 = H_16 (x) H_16, i.e.
 //     (H x)[16a' + b'] = (H_16 X H_16)[a'][b'] / 16        (H_16 with entries +-1).
 // Two 16x16x16 products do it: T = X (H_16/4) (fp16 inputs, exact products, fp32 sums; the factor
-// keeps |T| <= 4 max|x|), then H_16 T with T split into two halves (T = T_hi + T_lo keeps 22
-// bits), then the remaining factor 1/4.  The accumulator layout of the first product (lane = column
+// keeps |T| <= 4 max|x|), then (H_16/4) T with T split into two halves (T = T_hi + T_lo keeps 22
+// bits).  The accumulator layout of the first product (lane = column
 // b', four rows a per lane) is exactly the B-operand layout of the second, so nothing moves between
 // lanes.  A lane holds x[16 (l%16) + 4 (l/16) + 0..3] on entry and element e = 64 (l/16) + 16 r + l%16,
 // r = 0..3, of the result.
-struct HadamardOperand {
-    half4 h, q;  // H_16[4g + j][r16] and a quarter of it, j = 0..3: B operand of the first product, A operand of the second
-    __device__ __forceinline__ void init(int lane) {
-        const int r16 = lane & 15, g = lane >> 4;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool neg = (__builtin_popcount((4 * g + j) & r16) & 1) != 0;
-            h[j] = neg ? (_Float16)(-1.0f) : (_Float16)1.0f;
-            q[j] = neg ? (_Float16)(-0.25f) : (_Float16)0.25f;
-        }
-    }
-};
-
 // x~ = H x for one 256-chunk, rounded to fp16, scattered into operand order at `dst` (256*MP halves:
-// index ((t*4 + g)*MP + m)*8 + i).  Returns false if a rotated value (or the intermediate T, which
-// then turns the result into NaN) leaves the fp16 range.
+// index ((t*4 + g)*MP + m)*8 + i).  `peak` collects the largest magnitude of a rotated value; a value (or the
+// intermediate T, which then turns the result into NaN) outside the fp16 range leaves it above 65504 or NaN.
+// Every workgroup rotates all of X for itself, so with two to four rows this arithmetic is a good part
+// of the launch: both products take the quarter of H (their factors make up the 1/16 exactly), conversions
+// go in pairs, the residue of T is one mixed-precision multiply-add, and the range is one NaN-propagating
+// three-way maximum per two values -- 12 vector instructions a chunk instead of 26.
 template <int MP>
-__device__ __forceinline__ bool rotate_to_lds(u32x2 raw, const HadamardOperand& H, int lane, int m, _Float16* dst) {
+__device__ __forceinline__ void rotate_to_lds(u32x2 raw, const half4& q, int lane, int m, _Float16* dst, float& peak) {
     const half4 xa = __builtin_bit_cast(half4, raw);
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-    const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, H.q, zero, 0, 0, 0);
-    half4 th, tl;
+    const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, q, zero, 0, 0, 0);
+    const half4 th = __builtin_convertvector(T, half4);
+    floatx4 rest;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        th[j] = (_Float16)T[j];
-        tl[j] = (_Float16)(T[j] - (float)th[j]);
-    }
-    floatx4 U = __builtin_amdgcn_mfma_f32_16x16x16f16(H.h, th, zero, 0, 0, 0);
-    U = __builtin_amdgcn_mfma_f32_16x16x16f16(H.h, tl, U, 0, 0, 0);
-    _Float16 r[4];
-    bool ok = true;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        r[i] = (_Float16)(U[i] * 0.25f);
-        ok = ok && __builtin_fabsf(U[i]) <= 4.0f * 65504.0f;  // (false for NaN as well)
-    }
+    for (int j = 0; j < 4; ++j) rest[j] = __builtin_fmaf((float)th[j], -1.0f, T[j]);  // exact
+    const half4 tl = __builtin_convertvector(rest, half4);
+    floatx4 U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, th, zero, 0, 0, 0);
+    U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, tl, U, 0, 0, 0);
+    const half4 r = __builtin_convertvector(U, half4);
+    peak = __builtin_elementwise_maximum(peak, __builtin_elementwise_maximum(__builtin_fabsf(U[0]), __builtin_fabsf(U[1])));
+    peak = __builtin_elementwise_maximum(peak, __builtin_elementwise_maximum(__builtin_fabsf(U[2]), __builtin_fabsf(U[3])));
     // element e = 64g + 16w + slot (w = r, slot = l%16): quarter g, low-plane word w, code slot `slot`;
     // MFMA step t = 2w + ((slot&7)>>2), position i = 2(slot&3) + (slot>>3)
     const int g = lane >> 4, slot = lane & 15;
     const int tb = (slot & 7) >> 2, i0 = 2 * (slot & 3) + (slot >> 3);
 #pragma unroll
     for (int w = 0; w < 4; ++w) dst[(((2 * w + tb) * 4 + g) * MP + m) * 8 + i0] = r[w];
-    return ok;
 }
 
 // kGrouped: the launch serves several tensors (a single-tensor launch skips the lookup and the
@@ -242,7 +227,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : 4) void gemv_kernel(
 #pragma unroll
     for (int rt = 0; rt < RTW; ++rt) acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
     uint32_t bad = 0;
-    bool in_range = true;
+    float peak = 0.f;  // largest magnitude of the rotated activations
 
     struct Slot {
         TileRegs t[RT];
@@ -269,8 +254,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : 4) void gemv_kernel(
     };
     auto issue = [&](Slot& s, int j) { issue_sg(s, j, std::integral_constant<int, 0>{}); };
 
-    HadamardOperand H;
-    H.init(lane);
+    [[maybe_unused]] const half4 hq = hadamard_quarter(lane);
     const half8 ones = as_half8(0x04000400u, 0x04000400u, 0x04000400u, 0x04000400u);  // 2^-14 each
 
     auto compute_sg = [&](const Slot& s, auto sgc) {
@@ -281,7 +265,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : 4) void gemv_kernel(
             for (int i = 0; i < 4; ++i) ev[i] = ev_r[i];
         } else {
 #pragma unroll
-            for (int m = 0; m < MP; ++m) in_range = rotate_to_lds<MP>(s.xr[m], H, lane, m, xs) && in_range;
+            for (int m = 0; m < MP; ++m) rotate_to_lds<MP>(s.xr[m], hq, lane, m, xs, peak);
             // lane 0 holds x[0..3] of the chunk: E = 16 x_0 (rows m = 4g + i of the accumulators are row i & (MP-1) for M <= 4)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -429,7 +413,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : 4) void gemv_kernel(
         }
     }
     if (a.flags != nullptr) {
-        const uint32_t f = (bad != 0u ? kFlagBadCode : 0u) | (in_range ? 0u : kFlagActRange);
+        const uint32_t f = (bad != 0u ? kFlagBadCode : 0u) | (peak <= 65504.0f ? 0u : kFlagActRange);
         if (f != 0u) atomicOr(a.flags, f);
     }
 }
@@ -503,6 +487,9 @@ int launch_gemv(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
     int64_t grid64;
     if ((a.KB == 8 || a.KB == 16) && a.t[0].subscales == nullptr) {
         int64_t want = (nt_total + 3 * cus - 1) / (3 * cus);
+        // two to four rows: what a workgroup spends on rotating them counts, so one workgroup per unit where
+        // that covers the launch (three 4096x4096, M = 4: 8.4 us in 768 workgroups of one tile, 7.3 in 256 of three)
+        if (M > 1 && (nt_total + cus - 1) / cus <= kGemvMaxRT) want = (nt_total + cus - 1) / cus;
         if (want > kGemvMaxRT) want = kGemvMaxRT;
         grid64 = (nt_total + want - 1) / want;
     } else {

@@ -21,31 +21,23 @@ namespace itq3s {
 // Returns false if a rotated value (or the intermediate T, which then turns the result into NaN)
 // leaves the fp16 range.
 __device__ __forceinline__ bool rotate_operand(half4 xa, int lane, _Float16 out[4]) {
-    const int r16 = lane & 15, g = lane >> 4;
-    half4 h, q;  // H_16[4g + j][r16] and a quarter of it
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool neg = (__builtin_popcount((4 * g + j) & r16) & 1) != 0;
-        h[j] = neg ? (_Float16)(-1.0f) : (_Float16)1.0f;
-        q[j] = neg ? (_Float16)(-0.25f) : (_Float16)0.25f;
-    }
+    const half4 q = hadamard_quarter(lane);
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
     const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, q, zero, 0, 0, 0);
-    half4 th, tl;
+    const half4 th = __builtin_convertvector(T, half4);
+    floatx4 rest;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        th[j] = (_Float16)T[j];
-        tl[j] = (_Float16)(T[j] - (float)th[j]);
-    }
-    floatx4 U = __builtin_amdgcn_mfma_f32_16x16x16f16(h, th, zero, 0, 0, 0);
-    U = __builtin_amdgcn_mfma_f32_16x16x16f16(h, tl, U, 0, 0, 0);
-    bool ok = true;
+    for (int j = 0; j < 4; ++j) rest[j] = __builtin_fmaf((float)th[j], -1.0f, T[j]);  // exact
+    const half4 tl = __builtin_convertvector(rest, half4);
+    floatx4 U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, th, zero, 0, 0, 0);
+    U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, tl, U, 0, 0, 0);
+    const half4 r = __builtin_convertvector(U, half4);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        out[i] = (_Float16)(U[i] * 0.25f);
-        ok = ok && __builtin_fabsf(U[i]) <= 4.0f * 65504.0f;  // (false for NaN as well)
-    }
-    return ok;
+    for (int i = 0; i < 4; ++i) out[i] = r[i];
+    // (a maximum that hands a NaN on)
+    const float peak = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(U[0]), __builtin_fabsf(U[1])),
+                                                     __builtin_elementwise_maximum(__builtin_fabsf(U[2]), __builtin_fabsf(U[3])));
+    return peak <= 65504.0f;
 }
 
 // The same from memory.  `first` receives the first of the lane's four inputs (lane 0: x[0]).

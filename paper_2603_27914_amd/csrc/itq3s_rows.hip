@@ -84,7 +84,12 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void rows_kernel(const RowsArgs
     auto tensor_of = [&](int tile) { return kGrouped ? (tile >= vb1 ? 1 : 0) + (tile >= vb2 ? 1 : 0) + (tile >= vb3 ? 1 : 0) : 0; };
     auto place = [&](int it) {
         const bool have = it < item_end;  // (no such item: empty descriptors, loads return zeros without touching memory)
-        const int rg = have ? it / a.m_groups : 0, mg = have ? it - rg * a.m_groups : 0;
+        int rg = have ? it : 0, mg = 0;
+        if (a.m_groups > 1) {  // (an integer division: 30 scalar instructions in front of the first load)
+            const int i = rg;
+            rg = i / a.m_groups;
+            mg = i - rg * a.m_groups;
+        }
         Place p;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
