@@ -222,20 +222,19 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
         if (rc != 0) return rc;
         return itq3s::launch_gemv_rows(gw, count, K, Xt, S, M, MP, y_f16, status_flags, st);
     }
-    // tiled path: one rotation, then one contraction launch per tensor
+    // tiled path: one rotation, then one contraction launch for all tensors that do not split K
     unsigned char* const base = static_cast<unsigned char*>(workspace);
     uint32_t* zflags = reinterpret_cast<uint32_t*>(base + p.xt_bytes);
     float* partial = reinterpret_cast<float*>(base + p.xt_bytes + p.flag_bytes);
     const size_t partial_room = workspace_bytes - p.xt_bytes - p.flag_bytes;  // (checked above: every tensor's shares fit)
     static_assert(itq3s::kGemmFlagWords * 4 <= 512, "flag words fit their slot");
-    int rc = itq3s::launch_rotate_rowmajor(Xh, M, K, ldx, Xt, zflags, itq3s::kGemmFlagWords, status_flags, st);
-    for (int i = 0; i < count && rc == 0; ++i) {
-        rc = itq3s::launch_gemm(w[i].codes, w[i].scales, w[i].N, K, Xt, Xh, ldx, M, w[i].Y, y_f16, w[i].ldy, partial, partial_room, zflags,
-                                status_flags, st);
-        // (the tensors of a group share the flag words: a flag left by an earlier tensor only costs the
-        // later one a needless scan of its scale words)
-    }
-    return rc;
+    const int rc = itq3s::launch_rotate_rowmajor(Xh, M, K, ldx, Xt, zflags, itq3s::kGemmFlagWords, status_flags, st);
+    if (rc != 0) return rc;
+    itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
+    for (int i = 0; i < count; ++i) gw[i] = itq3s::GemvWeight{w[i].codes, w[i].scales, w[i].N, w[i].Y, w[i].ldy};
+    // (the tensors of a group share the flag words: a flag left by an earlier tensor only costs the
+    // later one a needless scan of its scale words)
+    return itq3s::launch_gemm(gw, count, K, Xt, Xh, ldx, M, y_f16, partial, partial_room, zflags, status_flags, st);
 }
 
 int itq3s_matmul(const uint32_t* codes, const uint32_t* scales, int64_t N, int64_t K, const void* X, int64_t M, int64_t ldx, void* Y,

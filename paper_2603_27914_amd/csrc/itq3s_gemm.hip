@@ -45,6 +45,21 @@ struct GemmArgs {
     int splits;
 };
 
+// One launch serves up to kGemvMaxGroup tensors that do not split K: their tiles form one list.  Two
+// tensors of 172 tiles each (11008 columns, 512 rows) leave a third of the compute units without work and
+// the others with one workgroup instead of two when each has a launch of its own.
+struct GemmTensor {
+    const uint32_t* codes;
+    const uint32_t* scales;
+    void* Y;
+    int64_t N, ldy;
+    int first_item, tiles_n;  // first_item: 0x7fffffff for unused entries
+};
+struct GemmGroup {
+    GemmArgs common;  // codes, scales, Y, N, ldy and NT are the tensor's
+    GemmTensor t[kGemvMaxGroup];
+};
+
 // LDS accesses by raw byte address, hidden from the compiler like every other LDS read of this file
 // (it would order visible LDS accesses after all outstanding global -> LDS copies).
 __device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v) { asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
@@ -87,20 +102,18 @@ __device__ __forceinline__ void zero_point_terms(const GemmArgs& a, int64_t n_fi
         for (int u = 0; u < 16; ++u) {
             const bool hit = (w[u] & 0x7fff0000u) != 0u && n < a.N && b0 + u < a.KB;
             unsigned long long todo = __builtin_amdgcn_ballot_w64(hit);
+            if (todo == 0ull) continue;  // uniform
+            // the row's first element of the block: fetched once for all columns (an outlier channel at the start
+            // of a block gives every column a zero-point there; one fetch per column cost 65 us a launch)
+            static_assert(ROWS <= kWave, "one row per lane");
+            const bool row_ok = m_first + lane < a.M && lane < ROWS;
+            const float x16 = row_ok ? 16.0f * (float)a.X[(m_first + lane) * a.ldx + (int64_t)(b0 + u) * kBlock] : 0.0f;
             while (todo != 0ull) {  // uniform
                 const int src = __builtin_ctzll(todo);
                 todo &= todo - 1ull;
                 const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)w[u], src);
                 const float dz = f16_bits_to_f32(word & 0xffffu) * f16_bits_to_f32(word >> 16);
-#pragma unroll 1
-                for (int r = 0; r < ROWS; r += kWave) {
-                    const int row = r + lane;
-                    const int64_t m = m_first + row;
-                    if (m < a.M && row < ROWS) {
-                        const float t = dz * (16.0f * (float)a.X[m * a.ldx + (int64_t)(b0 + u) * kBlock]);
-                        lds_add_f32(table + (uint32_t)(row * 64 + ((src + row) & 63)) * 4u, t);
-                    }
-                }
+                if (row_ok) lds_add_f32(table + (uint32_t)(lane * 64 + ((src + lane) & 63)) * 4u, dz * x16);
             }
         }
     }
@@ -139,6 +152,14 @@ __device__ __forceinline__ bool zero_point_terms_few_columns(const GemmArgs& a, 
         for (int u = 0; u < 16; ++u) {
             const bool hit = (w[u] & 0x7fff0000u) != 0u && n < a.N && b0 + u < a.KB;
             unsigned long long todo = __builtin_amdgcn_ballot_w64(hit);
+            if (todo == 0ull) continue;  // uniform
+            if (__builtin_popcountll(todo) > kStrips) return false;  // before anything is fetched
+            float x16[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int64_t m = m_first + r * kWave + lane;
+                x16[r] = m < a.M ? 16.0f * (float)a.X[m * a.ldx + (int64_t)(b0 + u) * kBlock] : 0.0f;
+            }
             while (todo != 0ull) {  // uniform
                 const int src = __builtin_ctzll(todo);
                 todo &= todo - 1ull;
@@ -156,14 +177,7 @@ __device__ __forceinline__ bool zero_point_terms_few_columns(const GemmArgs& a, 
                 const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)w[u], src);
                 const float dz = f16_bits_to_f32(word & 0xffffu) * f16_bits_to_f32(word >> 16);
 #pragma unroll
-                for (int r = 0; r < 128; r += kWave) {
-                    const int row = r + lane;
-                    const int64_t m = m_first + row;
-                    if (m < a.M) {
-                        const float t = dz * (16.0f * (float)a.X[m * a.ldx + (int64_t)(b0 + u) * kBlock]);
-                        lds_add_f32(strips + strip_offset(slot) + (uint32_t)(4 * row), t);
-                    }
-                }
+                for (int r = 0; r < 2; ++r) lds_add_f32(strips + strip_offset(slot) + (uint32_t)(4 * (r * kWave + lane)), dz * x16[r]);
             }
         }
     }
@@ -309,14 +323,25 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const floatx16 (&a
 }
 
 // (two wavefronts per SIMD: at most 256 registers)
-__global__ __launch_bounds__(GT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_kernel(const GemmArgs a, int tiles_m, int tiles_n, int per_chiplet) {
+__global__ __launch_bounds__(GT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_kernel(const GemmGroup group, int tiles_m, int items, int per_chiplet) {
     extern __shared__ __align__(1024) char lds[];
     // LDS byte address of the buffer, for the read instructions below that take raw addresses
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int item = xcd * per_chiplet + slot;
-    if (slot >= per_chiplet || item >= tiles_m * tiles_n * a.splits) return;
+    int item = xcd * per_chiplet + slot;
+    if (slot >= per_chiplet || item >= items) return;
+    const auto* const kargs = (const __attribute__((address_space(4))) GemmGroup*)__builtin_amdgcn_kernarg_segment_ptr();
+    const int ti = (item >= group.t[1].first_item ? 1 : 0) + (item >= group.t[2].first_item ? 1 : 0) + (item >= group.t[3].first_item ? 1 : 0);
+    GemmArgs a = group.common;
+    a.codes = kargs->t[ti].codes;
+    a.scales = kargs->t[ti].scales;
+    a.Y = kargs->t[ti].Y;
+    a.N = kargs->t[ti].N;
+    a.ldy = kargs->t[ti].ldy;
+    a.NT = (int)((a.N + 15) >> 4);
+    const int tiles_n = kargs->t[ti].tiles_n;
+    item -= kargs->t[ti].first_item;
     // the splits of a tile are neighbours in the list
     const int t = item / a.splits, split = item - t * a.splits;
     int tm, tn;
@@ -664,30 +689,63 @@ size_t gemm_partial_bytes(int64_t M, int64_t N, int64_t K) {
     return s > 1 ? (size_t)s * (size_t)(((M + GM - 1) / GM) * ((N + GN - 1) / GN)) * (GM * GN * 4) : 0;
 }
 
-int launch_gemm(const uint32_t* codes, const uint32_t* scales, int64_t N, int64_t K, const _Float16* Xt, const _Float16* X, int64_t ldx,
-                int64_t M, void* Y, int y_f16, int64_t ldy, float* partial, size_t partial_bytes, uint32_t* zflags, uint32_t* flags,
-                hipStream_t stream) {
-    GemmArgs a;
-    a.codes = codes; a.scales = scales; a.Xt = Xt; a.X = X; a.ldx = ldx; a.Y = Y; a.flags = flags;
-    a.N = N; a.K = K; a.M = M; a.ldy = ldy; a.NT = (int)((N + 15) / 16); a.KB = (int)(K / kBlock); a.y_f16 = y_f16;
-    a.partial = partial; a.zflags = zflags;
-    // split only if the caller's workspace has room for the shares (a grouped call sizes it for its largest tensor)
-    a.splits = partial != nullptr && zflags != nullptr && gemm_partial_bytes(M, N, K) <= partial_bytes ? gemm_splits(M, N, K) : 1;
-    const LaunchTiming tm = take_launch_timing();
-    const int64_t tiles_m = (M + GM - 1) / GM, tiles_n = (N + GN - 1) / GN;
-    if (K > kGemmMaxK || tiles_m * tiles_n >= 0x7fffffff / 8 / kGemmMaxSplits) return -2;
-    const int per = (int)((tiles_m * tiles_n * a.splits + 7) / 8);
-    const dim3 g((unsigned)(per * 8));
+int launch_gemm(const GemvWeight* w, int count, int64_t K, const _Float16* Xt, const _Float16* X, int64_t ldx, int64_t M, int y_f16, float* partial,
+                size_t partial_bytes, uint32_t* zflags, uint32_t* flags, hipStream_t stream) {
+    const int64_t tiles_m = (M + GM - 1) / GM;
+    if (K > kGemmMaxK) return -2;
     static std::atomic<bool> lds_limit_raised{false};
     if (!lds_limit_raised) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) != hipSuccess) return -6;
         lds_limit_raised = true;
     }
-    if (tm.start != nullptr) hipExtLaunchKernelGGL(gemm_kernel, g, dim3(GT), kGemmLds, stream, tm.start, tm.stop, 0, a, (int)tiles_m, (int)tiles_n, per);
-    else hipLaunchKernelGGL(gemm_kernel, g, dim3(GT), kGemmLds, stream, a, (int)tiles_m, (int)tiles_n, per);
-    if (hipGetLastError() != hipSuccess) return -6;
-    if (a.splits > 1) {
-        hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)(tiles_m * tiles_n * 4)), dim3(GT), 0, stream, a, (int)tiles_m, (int)tiles_n);
+    GemmGroup group;
+    GemmArgs& a = group.common;
+    a.codes = nullptr; a.scales = nullptr; a.Y = nullptr; a.N = 0; a.ldy = 0; a.NT = 0;
+    a.Xt = Xt; a.X = X; a.ldx = ldx; a.flags = flags; a.K = K; a.M = M; a.KB = (int)(K / kBlock); a.y_f16 = y_f16;
+    a.partial = partial; a.zflags = zflags;
+    int64_t items = 0;
+    int n = 0;
+    auto add = [&](const GemvWeight& v) {
+        group.t[n++] = GemmTensor{v.codes, v.scales, v.Y, v.N, v.ldy, (int)items, (int)((v.N + GN - 1) / GN)};
+        items += tiles_m * ((v.N + GN - 1) / GN) * a.splits;
+    };
+    auto launch = [&]() -> int {
+        if (items >= 0x7fffffff / 8) return -2;
+        for (int i = n; i < kGemvMaxGroup; ++i) {
+            group.t[i] = group.t[0];
+            group.t[i].first_item = 0x7fffffff;
+        }
+        const int per = (int)((items + 7) / 8);
+        const dim3 g((unsigned)(per * 8));
+        const LaunchTiming tm = take_launch_timing();
+        if (tm.start != nullptr) hipExtLaunchKernelGGL(gemm_kernel, g, dim3(GT), kGemmLds, stream, tm.start, tm.stop, 0, group, (int)tiles_m, (int)items, per);
+        else hipLaunchKernelGGL(gemm_kernel, g, dim3(GT), kGemmLds, stream, group, (int)tiles_m, (int)items, per);
+        return hipGetLastError() == hipSuccess ? 0 : -6;
+    };
+    // a tensor that splits K has a launch of its own (the room for shares is one tensor's), and only if the
+    // caller's workspace has room for its shares (a grouped call sizes it for its largest tensor)
+    auto splits_of = [&](const GemvWeight& v) {
+        return partial != nullptr && zflags != nullptr && gemm_partial_bytes(M, v.N, K) <= partial_bytes ? gemm_splits(M, v.N, K) : 1;
+    };
+    a.splits = 1;
+    for (int i = 0; i < count; ++i)
+        if (splits_of(w[i]) == 1) add(w[i]);
+    if (n > 0) {
+        const int rc = launch();
+        if (rc != 0) return rc;
+    }
+    for (int i = 0; i < count; ++i) {
+        a.splits = splits_of(w[i]);
+        if (a.splits == 1) continue;
+        n = 0;
+        items = 0;
+        add(w[i]);
+        const int rc = launch();
+        if (rc != 0) return rc;
+        GemmArgs r = a;
+        r.codes = w[i].codes; r.scales = w[i].scales; r.Y = w[i].Y; r.N = w[i].N; r.ldy = w[i].ldy; r.NT = (int)((w[i].N + 15) / 16);
+        const int tiles_n = (int)((w[i].N + GN - 1) / GN);
+        hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)(tiles_m * tiles_n * 4)), dim3(GT), 0, stream, r, (int)tiles_m, tiles_n);
         if (hipGetLastError() != hipSuccess) return -6;
     }
     return 0;

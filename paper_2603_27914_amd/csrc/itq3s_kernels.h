@@ -84,7 +84,7 @@ int cu_count();
 
 // Tiled matmul, M > 16.  Xt = rotated activations (launch_rotate_rowmajor); X, ldx = the activations
 // themselves (zero-point term).  Shapes with few output tiles split K over several workgroups per tile
-// and add the shares in a second launch (gemm_splits > 1): those use `partial` (gemm_partial_bytes,
+// and add the shares in a second launch (gemm_splits > 1); all others share one launch.  The former use `partial` (gemm_partial_bytes,
 // 16-byte aligned; partial_bytes = what is there -- too little, or none, means no split) and
 // `zflags` (kGemmFlagWords words, all zero at launch).
 constexpr int kGemmMaxSplits = 8;
@@ -92,9 +92,8 @@ constexpr int kGemmSplitMaxTiles = 128;  // more tiles than this: no split
 constexpr int kGemmFlagWords = 128;
 int gemm_splits(int64_t M, int64_t N, int64_t K);
 size_t gemm_partial_bytes(int64_t M, int64_t N, int64_t K);
-int launch_gemm(const uint32_t* codes, const uint32_t* scales, int64_t N, int64_t K, const _Float16* Xt, const _Float16* X, int64_t ldx,
-                int64_t M, void* Y, int y_f16, int64_t ldy, float* partial, size_t partial_bytes, uint32_t* zflags, uint32_t* flags,
-                hipStream_t stream);
+int launch_gemm(const GemvWeight* w, int count, int64_t K, const _Float16* Xt, const _Float16* X, int64_t ldx, int64_t M, int y_f16, float* partial,
+                size_t partial_bytes, uint32_t* zflags, uint32_t* flags, hipStream_t stream);
 
 // Tiled matmul with the inverse transform applied to the weights inside the tile loader (Alg. 2 as
 // printed); X = the activations themselves.  Any M.  subscales: the 116-byte variant's array, or null.

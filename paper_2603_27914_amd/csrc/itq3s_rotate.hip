@@ -139,23 +139,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
 
 // Operand order of the tiled kernel: rows stay rows; inside every group of 16 channels, slot s moves
 // to position 2 (s & 7) + (s >> 3), the order in which the tile loader's unpack emits the weights.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rotate_rowmajor_kernel(const _Float16* __restrict__ X, int64_t M, int64_t K, int64_t ldx,
+// A wavefront rotates four consecutive chunks (of the list row by row), loads first, and passes the rounded
+// values through a corner of LDS of its own, so that it stores 1 KiB of consecutive addresses per
+// instruction: bound by memory, not by the number of 2-byte stores (2048 x 14336: 31 -> 24 us, at the
+// 5.1 TB/s of a large copy).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rotate_rowmajor_kernel(const _Float16* __restrict__ X, int64_t chunks, int KB, int64_t ldx,
                                                               _Float16* __restrict__ Xt, uint32_t* __restrict__ zero_words, int n_zero, uint32_t* __restrict__ flags) {
-    const int64_t KB = K / kBlock;
-    const int lane = lane_id();
+    __shared__ __align__(16) _Float16 lds[4][4 * kBlock];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // the split-K flags of the contraction that follows start from zero
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < n_zero; i += 256) zero_words[i] = 0u;
-    const int64_t chunk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (chunk >= M * KB) return;
-    const int64_t m = chunk / KB, b = chunk - m * KB;
-    _Float16 r[4];
-    if (!rotate_chunk(X + m * ldx + b * kBlock, lane, r) && flags != nullptr) atomicOr(flags, kFlagActRange);
-    _Float16* dst = Xt + m * K + b * kBlock;
+    const int64_t first = ((int64_t)blockIdx.x * 4 + wave) * 4;
+    const int n = chunks - first < 4 ? (int)(chunks - first) : 4;
+    if (n <= 0) return;
+    half4 xa[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int e = 64 * (lane >> 4) + 16 * j + (lane & 15), s = e & 15;
-        dst[(e & ~15) | (2 * (s & 7) + (s >> 3))] = r[j];
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t chunk = (uint32_t)(first + (c < n ? c : 0)), m = chunk / (uint32_t)KB, b = chunk - m * (uint32_t)KB;  // (M K / 256 is below 2^31)
+        xa[c] = *reinterpret_cast<const half4*>(X + (int64_t)m * ldx + (int64_t)b * kBlock + 16 * (lane & 15) + 4 * (lane >> 4));
+    }
+    const int s = lane & 15;
+    bool ok = true;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        _Float16 r[4];
+        ok = rotate_operand(xa[c], lane, r) && ok;
+        _Float16* const dst = lds[wave] + c * kBlock + 64 * (lane >> 4) + 2 * (s & 7) + (s >> 3);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dst[16 * j] = r[j];
+    }
+    if (!ok && flags != nullptr) atomicOr(flags, kFlagActRange);
+    // (one wavefront writes and reads: the LDS instructions of a wavefront stay in order)
+    __builtin_amdgcn_wave_barrier();
+    u32x4* const out = reinterpret_cast<u32x4*>(Xt + first * kBlock);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(lds[wave] + (64 * u + lane) * 8);
+        if (2 * u + (lane >> 5) < n) out[64 * u + lane] = v;
     }
 }
 
@@ -175,7 +196,7 @@ int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int
 int launch_rotate_rowmajor(const _Float16* X, int64_t M, int64_t K, int64_t ldx, _Float16* Xt, uint32_t* zero_words, int n_zero, uint32_t* flags,
                            hipStream_t stream) {
     const int64_t chunks = M * (K / kBlock);
-    hipLaunchKernelGGL(rotate_rowmajor_kernel, dim3((unsigned)((chunks + 3) / 4)), dim3(256), 0, stream, X, M, K, ldx, Xt, zero_words, n_zero, flags);
+    hipLaunchKernelGGL(rotate_rowmajor_kernel, dim3((unsigned)((chunks + 15) / 16)), dim3(256), 0, stream, X, chunks, (int)(K / kBlock), ldx, Xt, zero_words, n_zero, flags);
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
