@@ -673,13 +673,17 @@ __global__ __launch_bounds__(GT) void gemm_reduce_kernel(const GemmArgs a, int t
     store_rows<0>(a, acc, m_first, n0, wn, lane);
 }
 
-// Splits of K per tile: when the tiles alone leave three quarters of the chip idle, enough workgroups
-// for its 512 slots (two per compute unit), each split at least four blocks long.  A function of the
-// shape only.
+// Splits of K per tile, each at least four blocks long, when the tiles alone leave half of the chip idle.  A
+// workgroup alone on a compute unit does nearly the work of two that share it, and every share costs its
+// way through memory twice, so one workgroup per unit is the aim where the tiles divide the units well and K
+// is not so long that the shares do not count; else two per unit.  One / two per unit, 512 rows, us: 11008x4096
+// 63 / 72, 14336x4096 75 / 83, 8192x8192 79 / 83, but 28672x8192 232 / 223; 14336x4096 with 700 rows (96
+// tiles: 192 or 480 workgroups) 109 / 104.  A function of the shape only.
 int gemm_splits(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + GM - 1) / GM) * ((N + GN - 1) / GN);
     if (tiles > kGemmSplitMaxTiles) return 1;
-    int64_t s = 512 / tiles;
+    int64_t s = 256 / tiles;
+    if (K > 20480 || s * tiles < 208) s = 512 / tiles;
     if (s > kGemmMaxSplits) s = kGemmMaxSplits;
     if (s > K / kBlock / 4) s = K / kBlock / 4;
     return s < 1 ? 1 : (int)s;
