@@ -64,64 +64,66 @@ struct GemmGroup {
 // (it would order visible LDS accesses after all outstanding global -> LDS copies).
 __device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v) { asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 __device__ __forceinline__ void lds_add_f32(uint32_t addr, float v) { asm volatile("ds_add_f32 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
-__device__ __forceinline__ uint32_t lds_read_f32_bits_now(uint32_t addr) {
-    uint32_t r;
-    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(addr) : "memory");
-    return r;
-}
-__device__ __forceinline__ float lds_read_f32_now(uint32_t addr) {
-    float r;
-    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(addr) : "memory");
-    return r;
-}
 
-// Zero-point terms of a wavefront's output block, columns n_first .. n_first + 63, rows m_first ..
-// m_first + ROWS - 1, summed in fp32 into a wavefront-private LDS table (ROWS x 64 floats at byte
-// address `table`; element (row, col) at word 64 row + (col + row) % 64, which spreads a column over
-// the banks) -- they are subtracted from the accumulators BEFORE the output is rounded: with fp16
-// outputs, correcting the stored value instead would round a sum that still contains the +z offset of
+// Zero-point terms of 32 rows (m_first ..) of a wavefront's 64 columns (n_first ..), summed in fp32 in the
+// accumulators' layout -- they are subtracted from the accumulators BEFORE the output is rounded: with
+// fp16 outputs, correcting the stored value instead would round a sum that still contains the +z offset of
 // every code and lose up to 2^-11 of that larger number.  Lane l walks the scale words of column
-// n_first + l, sixteen blocks per batch (independent loads).  For each block with z != 0 -- a fraction
-// of a percent on real weights -- the whole wavefront adds d z 16 x[m][256 b] to that column of the
-// table, one row per lane.  Per element the blocks are added in ascending order by one lane at a
-// time, so the result does not depend on scheduling.
-template <int ROWS>
-__device__ __forceinline__ void zero_point_terms(const GemmArgs& a, int64_t n_first, int64_t m_first, int lane, uint32_t table) {
-#pragma unroll 8
-    for (int i = 0; i < ROWS; ++i) lds_write_b32(table + (uint32_t)(i * 64 + lane) * 4u, 0u);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+// n_first + l, eight blocks per batch (independent loads).  For each block in which a column has z != 0 the
+// lanes exchange their columns' d z (lane -> accumulator column) and add d z 16 x[m][256 b], the 32 row
+// values through 128 bytes of LDS at `xbuf` (the wavefront's own): about 60 instructions a block however many
+// of its columns are concerned.  (An outlier channel at the start of a block gives every column a
+// zero-point there.  Adding one column at a time to a table in LDS, as the first version did, made a launch
+// of two 11008x4096 tensors with 512 rows take 174 us on such weights instead of 107.)  Per element
+// the blocks are added in ascending order, so the result does not depend on scheduling.
+__device__ __forceinline__ void zero_point_terms(const GemmArgs& a, int64_t n_first, int64_t m_first, int lane, uint32_t xbuf, floatx16 (&terms)[2]) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) terms[j][v] = 0.f;
     const int64_t n = n_first + lane;
     const int64_t nc = n < a.N ? n : a.N - 1;
     const uint32_t* sc = a.scales + (nc >> 4) * a.KB * kTileRows + (nc & 15);
+    const bool row_ok = lane < 32 && m_first + lane < a.M;
+    const _Float16* const xrow = a.X + (row_ok ? m_first + lane : 0) * a.ldx;
+    const uint32_t xread = xbuf + (uint32_t)((lane >> 5) * 16);  // rows 8 q + 4 (lane / 32) + 0..3
 #pragma unroll 1
-    for (int b0 = 0; b0 < a.KB; b0 += 16) {
-        uint32_t w[16];
+    for (int b0 = 0; b0 < a.KB; b0 += 8) {
+        uint32_t w[8];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) w[u] = sc[(int64_t)(b0 + u < a.KB ? b0 + u : a.KB - 1) * kTileRows];
+        for (int u = 0; u < 8; ++u) w[u] = sc[(int64_t)(b0 + u < a.KB ? b0 + u : a.KB - 1) * kTileRows];
+        uint32_t any = 0;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const bool hit = (w[u] & 0x7fff0000u) != 0u && n < a.N && b0 + u < a.KB;
-            unsigned long long todo = __builtin_amdgcn_ballot_w64(hit);
-            if (todo == 0ull) continue;  // uniform
-            // the row's first element of the block: fetched once for all columns (an outlier channel at the start
-            // of a block gives every column a zero-point there; one fetch per column cost 65 us a launch)
-            static_assert(ROWS <= kWave, "one row per lane");
-            const bool row_ok = m_first + lane < a.M && lane < ROWS;
-            const float x16 = row_ok ? 16.0f * (float)a.X[(m_first + lane) * a.ldx + (int64_t)(b0 + u) * kBlock] : 0.0f;
-            while (todo != 0ull) {  // uniform
-                const int src = __builtin_ctzll(todo);
-                todo &= todo - 1ull;
-                const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)w[u], src);
-                const float dz = f16_bits_to_f32(word & 0xffffu) * f16_bits_to_f32(word >> 16);
-                if (row_ok) lds_add_f32(table + (uint32_t)(lane * 64 + ((src + lane) & 63)) * 4u, dz * x16);
-            }
+        for (int u = 0; u < 8; ++u) {
+            if (n >= a.N || b0 + u >= a.KB) w[u] = 0u;
+            any |= w[u] & 0x7fff0000u;
+        }
+        if (__builtin_amdgcn_ballot_w64(any != 0u) == 0ull) continue;  // uniform
+        _Float16 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = xrow[(int64_t)(b0 + u < a.KB ? b0 + u : a.KB - 1) * kBlock];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (__builtin_amdgcn_ballot_w64((w[u] & 0x7fff0000u) != 0u) == 0ull) continue;  // uniform
+            if (lane < 32) lds_write_b32(xbuf + (uint32_t)(4 * lane), __builtin_bit_cast(uint32_t, row_ok ? 16.0f * (float)x[u] : 0.0f));
+            const float dz = f16_bits_to_f32(w[u] & 0xffffu) * f16_bits_to_f32(w[u] >> 16);
+            float dzc[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                dzc[j] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * (32 * j + (lane & 31)), __builtin_bit_cast(int, dz)));
+            floatx4 xr[4];
+            asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:32\n\tds_read_b128 %2, %4 offset:64\n\tds_read_b128 %3, %4 offset:96\n\t"
+                         "s_waitcnt lgkmcnt(0)" : "=&v"(xr[0]), "=&v"(xr[1]), "=&v"(xr[2]), "=&v"(xr[3]) : "v"(xread) : "memory");
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) terms[j][v] = __builtin_fmaf(dzc[j], xr[v >> 2][v & 3], terms[j][v]);
         }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
-// The common case of the above -- the zero-points of a wavefront's 64 columns sit in at most eight of
-// them -- needs no table of all columns: one 128-row strip of floats per such column (strip_offset())
+// The common case -- the zero-points of a wavefront's 64 columns sit in at most eight of them -- needs
+// one scan for all 128 rows instead of four: one 128-row strip of floats per such column (strip_offset())
 // fits the wavefront's own corner of the weight ring (1 KiB of each of its four stages: two strips
 // each), so nothing is shared, nobody is waited for, and one scan serves all 128 rows.  cols receives
 // the columns (0..63, -1: slot unused).  Returns false, with the strips in an undefined state, if a
@@ -236,8 +238,7 @@ constexpr int kWRingBase = kXStages * kXStageBytes;         // 49152
 constexpr int kWStageBytes = 4 * 1024;                      // 4 wavefronts x 64 lanes x 16 bytes
 constexpr int kSRingBase = kWRingBase + kWStages * kWStageBytes;  // 65536
 constexpr int kSStageBytes = 4 * 256;                       // 4 wavefronts x 64 lanes x 4 bytes
-constexpr int kDoneWord = kSRingBase + kWStages * kSStageBytes;   // 69632: count of wavefronts that are done with the rings
-constexpr int kGemmLds = kDoneWord + 16;
+constexpr int kGemmLds = kSRingBase + kWStages * kSStageBytes;    // 69632
 constexpr int kPanel = 4;                                   // tile rows per panel
 
 template <int OFF>
@@ -272,36 +273,34 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 
 // Store 32 rows (m_first ..) of a wavefront's 64 columns (n0 + 64 wn ..).  Accumulator register v of a
 // 32x32 block: row = 8*(v/4) + 4*(lane/32) + v%4, column = lane%32.  kTerms: minus the zero-point
-// terms of these rows, which start at row `row0` of the wavefront's LDS table (zero_point_terms()).
-template <int kTerms>  // 0: none; 1: table of all columns (row0: its row of m_first); 2: strips of a few columns (row0 likewise)
+// terms of these rows, from registers (1) or from a few columns' strips in LDS, whose row of m_first is row0 (2).
+template <int kTerms>
 __device__ __forceinline__ void store_rows(const GemmArgs& a, const floatx16 (&acc)[2], int64_t m_first, int64_t n0, int wn, int lane,
-                                           int row0 = 0, uint32_t table = 0, const StripColumns* cols = nullptr) {
+                                           const floatx16 (*in_regs)[2] = nullptr, int row0 = 0, uint32_t strips = 0, const StripColumns* cols = nullptr) {
     const int l32 = lane & 31, kg = lane >> 5;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int64_t n = n0 + wn * 64 + j * 32 + l32;
         floatx16 terms;
-        if constexpr (kTerms != 0) {
+        if constexpr (kTerms == 1) terms = (*in_regs)[j];
+        if constexpr (kTerms == 2) {
             const int col = 32 * j + l32;
-            int slot = -1;  // (strips only)
-            if constexpr (kTerms == 2) {
+            int slot = -1;
 #pragma unroll
-                for (int q = 0; q < kStrips; ++q) slot = cols->c[q] == col ? q : slot;
-            }
+            for (int q = 0; q < kStrips; ++q) slot = cols->c[q] == col ? q : slot;
             // sixteen reads in flight, one wait
             uint32_t t[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = row0 + 8 * (v >> 2) + 4 * kg + (v & 3);
-                const uint32_t addr = kTerms == 1 ? table + (uint32_t)(row * 64 + ((col + row) & 63)) * 4u
-                                                  : table + strip_offset(slot < 0 ? 0 : slot) + (uint32_t)(4 * row);
+                const uint32_t addr = strips + strip_offset(slot < 0 ? 0 : slot) + (uint32_t)(4 * row);
                 asm volatile("ds_read_b32 %0, %1" : "=v"(t[v]) : "v"(addr) : "memory");
             }
             asm volatile("s_waitcnt lgkmcnt(0)"
                          : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]), "+v"(t[8]), "+v"(t[9]),
                            "+v"(t[10]), "+v"(t[11]), "+v"(t[12]), "+v"(t[13]), "+v"(t[14]), "+v"(t[15]));
 #pragma unroll
-            for (int v = 0; v < 16; ++v) terms[v] = (kTerms == 2 && slot < 0) ? 0.0f : __builtin_bit_cast(float, t[v]);
+            for (int v = 0; v < 16; ++v) terms[v] = slot < 0 ? 0.0f : __builtin_bit_cast(float, t[v]);
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -557,10 +556,6 @@ __global__ __launch_bounds__(GT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(2)" ::: "memory");  // quarter 1 has landed as well; only the two copies of copy_w(2) may be in flight
-    if (tid == 0) {
-        lds_write_b32(lds_base + kDoneWord, 0u);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    }
     __builtin_amdgcn_s_barrier();
     // The two register sets of the weights alternate by name, so trips come in pairs: the first trip
     // on its own, pairs (1,2), (3,4), ..., and the last trip (K is a multiple of 256: the number of
@@ -577,10 +572,6 @@ __global__ __launch_bounds__(GT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // last step of the last quarter (the words it unpacks are never used)
     step(af1, wa0.x, wa1.x);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the look-ahead copies past the last quarter still target this workgroup's LDS
-    // ... and this wavefront reads the rings no more.  Counted rather than met at a barrier: only a
-    // wavefront that needs the rings' space for its zero-point table waits for the other three, and
-    // every wavefront gets here without waiting for anything.
-    if (lane == 0) asm volatile("ds_add_u32 %0, %1" ::"v"(lds_base + kDoneWord), "v"(1u) : "memory");
 
     // Format check, apart from the arithmetic: the high plane of the workgroup's 16 tile rows must be
     // zero (128 words per tile, a quarter of the packed bytes, read once more here).
@@ -618,21 +609,17 @@ __global__ __launch_bounds__(GT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             StripColumns cols;
             if (zero_point_terms_few_columns(a, n0 + wn * 64, m0, lane, strips, cols)) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) store_rows<2>(a, acc[i], m0 + 32 * i, n0, wn, lane, 32 * i, strips, &cols);
+                for (int i = 0; i < 4; ++i) store_rows<2>(a, acc[i], m0 + 32 * i, n0, wn, lane, nullptr, 32 * i, strips, &cols);
                 return;
             }
         }
-        // otherwise a table of all 64 columns, 32 rows at a time, in the activation ring (which does not
-        // overlap any wavefront's strips) -- once all four wavefronts have drained their copies and left
-        // the main loop
+        // otherwise 32 rows at a time in registers
         static_assert(kWStageBytes == 4096 && kWStages * 2 >= kStrips, "two strips of 128 floats in the wavefront's KiB of every stage");
-        static_assert(4 * 32 * 64 * 4 <= kWRingBase, "four tables of 32 x 64 floats inside the activation ring");
-        const uint32_t table = lds_base + (uint32_t)wave * (32 * 64 * 4);
-        while (__builtin_amdgcn_readfirstlane((int)lds_read_f32_bits_now(lds_base + kDoneWord)) != GT / kWave) __builtin_amdgcn_s_sleep(2);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            zero_point_terms<32>(a, n0 + wn * 64, m0 + 32 * i, lane, table);
-            store_rows<1>(a, acc[i], m0 + 32 * i, n0, wn, lane, 0, table);
+            floatx16 terms[2];
+            zero_point_terms(a, n0 + wn * 64, m0 + 32 * i, lane, lds_base + kWRingBase + (uint32_t)wave * 1024u, terms);
+            store_rows<1>(a, acc[i], m0 + 32 * i, n0, wn, lane, &terms);
         }
         return;
     }
@@ -664,10 +651,10 @@ __global__ __launch_bounds__(GT) void gemm_reduce_kernel(const GemmArgs a, int t
         }
     const int64_t m_first = (int64_t)tm * GM + i * 32, n0 = (int64_t)tn * GN;
     if (a.zflags[t] != 0u) {
-        __shared__ __align__(16) float tables[4 * 32 * 64];  // one per wavefront
-        const uint32_t table = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)tables + (uint32_t)wn * (32 * 64 * 4);
-        zero_point_terms<32>(a, n0 + wn * 64, m_first, lane, table);
-        store_rows<1>(a, acc, m_first, n0, wn, lane, 0, table);
+        __shared__ __align__(16) float row_values[4][32];  // of each wavefront
+        floatx16 terms[2];
+        zero_point_terms(a, n0 + wn * 64, m_first, lane, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)row_values[wn], terms);
+        store_rows<1>(a, acc, m_first, n0, wn, lane, &terms);
         return;
     }
     store_rows<0>(a, acc, m_first, n0, wn, lane);
