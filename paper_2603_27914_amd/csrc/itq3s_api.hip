@@ -292,8 +292,8 @@ int itq3s_matmul_sub(const uint32_t* codes, const uint32_t* scales, const uint32
         if ((M + 511) / 512 > 65535) return ITQ3S_ERR_SHAPE;
         return itq3s::launch_gemm_weight_side(codes, scales, subscales, N, K, static_cast<const _Float16*>(X), ldx, M, Y, y_f16, ldy, status_flags, st);
     }
-    // the streaming kernel: passes of up to 16 rows; a pass of up to four rows rotates the activations
-    // itself, a longer one takes them from a rotation launch through the workspace
+    // the streaming kernel: passes of up to 16 rows; a pass of up to four rows (eight for small tensors) rotates
+    // the activations itself, a longer one takes them from a rotation launch through the workspace
     const WorkspacePlan p = plan_workspace(M < itq3s::kGemvMaxM ? M : itq3s::kGemvMaxM, N, K);
     if (M > itq3s::kGemvFusedMaxM) {
         if (!workspace || workspace_bytes < p.total) return ITQ3S_ERR_WORKSPACE;
@@ -305,7 +305,7 @@ int itq3s_matmul_sub(const uint32_t* codes, const uint32_t* scales, const uint32
         const _Float16* Xh = static_cast<const _Float16*>(X) + m0 * ldx;
         itq3s::GemvWeight gw{codes, scales, N, static_cast<unsigned char*>(Y) + (size_t)m0 * (size_t)ldy * y_bytes, ldy, subscales};
         int rc;
-        if (rows <= itq3s::kGemvFusedMaxM) {
+        if (itq3s::gemv_sub_fused(rows, N, K, ldx)) {
             rc = itq3s::launch_gemv(&gw, 1, K, Xh, ldx, rows, y_f16, status_flags, st);
         } else {
             const int MP = pad_m(rows) < 8 ? 8 : pad_m(rows);

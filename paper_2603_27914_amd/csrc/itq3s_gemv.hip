@@ -130,10 +130,11 @@ __device__ __forceinline__ void rotate_to_lds(u32x2 raw, const half4& q, int lan
 template <int MP, int RT, bool kGrouped, int NBC, bool kSub = false, bool kRotated = false, int NSG = 1>
 // (launch bounds: the second figure is a lower bound on wavefronts per SIMD: 4 = two workgroups per
 // compute unit = at most 128 registers, which every instantiation of the general pipeline meets
-// without scratch; the straight-line kernels use 57..92 registers on their own)
-__global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : 4) void gemv_kernel(const GemvArgs a) {
+// without scratch; the straight-line kernels use 57..92 registers on their own; eight rows rotated here
+// run with one workgroup per compute unit)
+__global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotated) ? 2 : 4) void gemv_kernel(const GemvArgs a) {
     static_assert(!kRotated || (NBC == 0 && MP >= 8), "rotated activations: general pipeline");
-    static_assert(kRotated || MP <= 4, "in-kernel rotation: at most four rows");
+    static_assert(kRotated || MP <= 8, "in-kernel rotation: at most eight rows");
     static_assert(NSG == 1 || (NSG == 2 && kRotated), "row sub-groups: with rotated activations only");
     constexpr int RTW = RT * NSG;  // row tiles of the workgroup
     constexpr int W = kGemvWaves;
@@ -266,11 +267,15 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : 4) void gemv_kernel(
         } else {
 #pragma unroll
             for (int m = 0; m < MP; ++m) rotate_to_lds<MP>(s.xr[m], hq, lane, m, xs, peak);
-            // lane 0 holds x[0..3] of the chunk: E = 16 x_0 (rows m = 4g + i of the accumulators are row i & (MP-1) for M <= 4)
+            // lane 0 holds x[0..3] of the chunk: E = 16 x_0 (rows m = 4g + i of the accumulators are row m & (MP-1))
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.xr[i & (MP - 1)].x);
                 ev[i] = 16.0f * f16_bits_to_f32(w0 & 0xffffu);
+                if constexpr (MP == 8) {
+                    const uint32_t w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.xr[4 + i].x);
+                    ev[i] = (g & 1) != 0 ? 16.0f * f16_bits_to_f32(w1 & 0xffffu) : ev[i];
+                }
             }
         }
         // the block sums S come from the matrix cores as well: the same fragments against an operand of ones
@@ -473,7 +478,7 @@ int cu_count() {
 
 int launch_gemv(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, int y_f16, uint32_t* flags,
                 hipStream_t stream) {
-    if (count < 1 || count > kGemvMaxGroup || M < 1 || M > kGemvFusedMaxM) return -2;
+    if (count < 1 || count > kGemvMaxGroup || M < 1) return -2;
     GemvArgs a;
     a.X = X; a.S = nullptr; a.flags = flags; a.ldx = ldx; a.KB = (int)(K / kBlock); a.M = (int)M; a.y_f16 = y_f16;
     const int64_t nt_total = fill_tensors(a.t, w, count);
@@ -503,11 +508,30 @@ int launch_gemv(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
     const int rt = (int)((nt_total + grid - 1) / grid);
     a.nt_q = (int)(nt_total / grid);
     a.nt_r = (int)(nt_total % grid);
+    if (M > kGemvFusedMaxM) {
+        if (M > kGemvSubFusedMaxM || a.t[0].subscales == nullptr) return -2;
+        switch (rt) {
+            case 1: return launch_kernel<8, 1, false, 0, true>(a, grid, stream);
+            case 2: return launch_kernel<8, 2, false, 0, true>(a, grid, stream);
+            case 3: return launch_kernel<8, 3, false, 0, true>(a, grid, stream);
+        }
+        return -2;
+    }
     switch (M) {
         case 1: return launch_blocks<1>(a, grid, rt, stream);
         case 2: return launch_blocks<2>(a, grid, rt, stream);
         default: return launch_blocks<4>(a, grid, rt, stream);
     }
+}
+
+// Five to eight rows: rotating them in every workgroup is 128 chunks per 4096 channels, about 1 us where a
+// compute unit has one workgroup, against 2.7 us for the launch in front: 4096x11008 10.5 -> 9.8 us, 4096x4096
+// 6.7 -> 6.3, but 11008x4096 10.5 -> 11.7 and 28672x8192 30 -> 34.  (Both ways compute the same bits.  The
+// 100-byte format keeps to the launch: its block sums come out of it rounded differently, and a
+// grouped call, which may have several workgroups per unit, must equal the single ones.)
+bool gemv_sub_fused(int64_t M, int64_t N, int64_t K, int64_t ldx) {
+    if (M <= kGemvFusedMaxM) return true;
+    return M <= kGemvSubFusedMaxM && K <= 4096 && (N + 15) / 16 <= (int64_t)kGemvMaxRT * cu_count() && (M - 1) * ldx + K <= (1LL << 29);
 }
 
 template <int MP>

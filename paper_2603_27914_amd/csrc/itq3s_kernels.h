@@ -60,6 +60,11 @@ struct GemvWeight {
 int launch_gemv(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, int y_f16, uint32_t* flags,
                 hipStream_t stream);
 
+// Whether launch_gemv takes a tensor of the 116-byte variant with M rows: up to kGemvFusedMaxM always, up to
+// kGemvSubFusedMaxM where a launch of its own for the rotation costs more than rotating in every workgroup.
+constexpr int kGemvSubFusedMaxM = 8;
+bool gemv_sub_fused(int64_t M, int64_t N, int64_t K, int64_t ldx);
+
 // The same for kGemvFusedMaxM < M <= kGemvMaxM: Xt = rotated activations in operand order with MP
 // columns and S = their block sums, both from launch_rotate_frag.
 int launch_gemv_rows(const GemvWeight* w, int count, int64_t K, const _Float16* Xt, const float* S, int64_t M, int MP, int y_f16,
