@@ -343,14 +343,14 @@ static int launch_rows_mt(const RowsArgs& a, int rt, hipStream_t stream) {
     return -2;
 }
 
-// Activation rows padded to whole groups of 32, 48 or 64: the least of the three.
+// Activation rows padded to whole groups of 32, 48 or 64: the most of the three.
 static int64_t rows_padded(int64_t M) {
-    int64_t best = INT64_MAX;
+    int64_t most = 0;
     for (int mt = 2; mt <= 4; ++mt) {
         const int64_t rows = (M + 16 * mt - 1) / (16 * mt) * (16 * mt);
-        if (rows < best) best = rows;
+        if (rows > most) most = rows;
     }
-    return best;
+    return most;
 }
 size_t rows_xt_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)K * 2; }
 size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)(K / kBlock) * 3; }  // 64 bytes per 32 rows, 128 per 48 or 64
@@ -375,8 +375,7 @@ int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
     a.Xt = Xt; a.X0 = X0; a.flags = flags; a.KB = (int)(K / kBlock); a.M = (int)M; a.y_f16 = y_f16;
     const int64_t nt_total = fill_tensors(a.t, w, count);
     if (nt_total < 0) return -2;
-    // Rows per group (16 mt, without more padding than needed) and row tiles per item (rt): the pair that
-    // takes the least time in rounds of one workgroup per compute unit (eight wavefronts of up to 256
+    // Rows per group (16 mt) and row tiles per item (rt): the pair that takes the least time in rounds of one workgroup per compute unit (eight wavefronts of up to 256
     // registers).  An item costs per block of its wavefronts 23 for a row tile and 56 for 16 activation rows
     // (their fragments' way through the L1), then 60 per row tile and 100 for its end: fitted to launches
     // with every rt and mt (11008x4096, one round: 16.9 / 18.9 / 21.3 / 24.2 us for rt = 1..4 with mt = 2,
@@ -387,7 +386,6 @@ int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
     int64_t best = INT64_MAX;
     for (int m = 2; m <= 4; ++m) {
         const int64_t n_groups = (M + 16 * m - 1) / (16 * m);
-        if (n_groups * 16 * m > rows_padded(M)) continue;
         for (int r = 1; r <= kRowsMaxRT; ++r) {
             const int64_t n_items = (nt_total + r - 1) / r * n_groups;
             const int64_t cost = (n_items + cus - 1) / cus * (steps * (23 * r + 56 * m) + 60 * r + 100);
