@@ -122,19 +122,22 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void rows_kernel(const RowsArgs
             s.sc[rt] = __builtin_amdgcn_raw_buffer_load_b32(p.s[rt], off_sc, b * 64, kLoadNT);
         }
     };
-    auto issue_x = [&](half8 (&x)[S][MT], const Place& p, int b, auto partc) {
+    // the fragments of one step of a part (and, with a block's first step, its first elements)
+    auto issue_x_step = [&](half8 (&x)[S][MT], const Place& p, int b, auto partc, int t) {
         constexpr int part = decltype(partc)::value;
-        if constexpr (part == 0) {
+        if (part == 0 && t == 0) {
 #pragma unroll
             for (int q = 0; q < kX0Stride / 8; ++q) x0[q] = __builtin_amdgcn_raw_buffer_load_b128(p.e, off_e + 16 * q, b * (kX0Stride * 8), 0);
         }
 #pragma unroll
-        for (int t = 0; t < S; ++t)
+        for (int mt = 0; mt < MT; ++mt) {
+            const int f = (S * part + t) * MT + mt;  // fragment of the block: 1 KiB each
+            x[t][mt] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(p.x, off16 + (f & 3) * 1024, b * (MT * 8192) + (f >> 2) * 4096, 0));
+        }
+    };
+    auto issue_x = [&](half8 (&x)[S][MT], const Place& p, int b, auto partc) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int f = (S * part + t) * MT + mt;  // fragment of the block: 1 KiB each
-                x[t][mt] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(p.x, off16 + (f & 3) * 1024, b * (MT * 8192) + (f >> 2) * 4096, 0));
-            }
+        for (int t = 0; t < S; ++t) issue_x_step(x, p, b, partc, t);
     };
 
     floatx4 acc[RT][MT];
@@ -182,11 +185,12 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void rows_kernel(const RowsArgs
     };
     // One part of a block.  The products of a step are issued between the unpack instructions of the next
     // step's operands.
-    auto compute = [&](const Tiles& s, const half8 (&x)[S][MT], auto partc) {
+    auto compute = [&](const Tiles& s, const half8 (&x)[S][MT], auto partc, auto&& loads) {
         constexpr int part = decltype(partc)::value;
 #pragma unroll
         for (int t = 0; t < S; ++t) {
             const int next = S * part + t + 1;  // step of the block whose operands are unpacked here
+            loads(t);
             half8 nop[RT];
             if (next < 8) {
 #pragma unroll
@@ -205,6 +209,7 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void rows_kernel(const RowsArgs
                 for (int r = 0; r < RT * MT; ++r) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x002, kPerProduct, 0);
+                    if (r % RT == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
                 }
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) op[rt] = nop[rt];
@@ -272,21 +277,16 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void rows_kernel(const RowsArgs
             ITQ3S_FENCE;
             begin(w);
             ITQ3S_FENCE;
-            compute(w, xa, p0);
+            compute(w, xa, p0, [](int) {});
+            ITQ3S_FENCE;
             if constexpr (P == 2) {
-                issue_x(xa, nxt, bn, p0);
-                ITQ3S_FENCE;
-                compute(w, xb, p1);
+                compute(w, xb, p1, [&](int t) { issue_x_step(xa, nxt, bn, p0, t); });
             } else {
-                issue_x(xa, cur, b, p2);
+                compute(w, xb, p1, [&](int t) { issue_x_step(xa, cur, b, p2, t); });
                 ITQ3S_FENCE;
-                compute(w, xb, p1);
-                issue_x(xb, cur, b, p3);
+                compute(w, xa, p2, [&](int t) { issue_x_step(xb, cur, b, p3, t); });
                 ITQ3S_FENCE;
-                compute(w, xa, p2);
-                issue_x(xa, nxt, bn, p0);
-                ITQ3S_FENCE;
-                compute(w, xb, p3);
+                compute(w, xb, p3, [&](int t) { issue_x_step(xa, nxt, bn, p0, t); });
             }
             ITQ3S_FENCE;
             cur = nxt;
