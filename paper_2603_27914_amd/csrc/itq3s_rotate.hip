@@ -98,43 +98,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
 //   Xt index = ((((group*KB + b)*8 + t)*mts + mt)*64 + l)*8 + i,   row m = (group*mts + mt)*16 + r
 //   X0 index = ((group*KB + b)*4 + q)*stride + 4 mt + i = x[(group*mts + mt)*16 + 4 q + i][256 b], stride 8 for
 //              mts <= 2, else 16
-// Rows past M are zero.  A workgroup rotates 16 rows of one block, four per wavefront, and passes the
+// Rows past M are zero.  A workgroup rotates 16 rows of one block, two per wavefront, and passes the
 // rounded values through LDS (rows in the channel order in which a lane's eight halves are neighbours),
 // so that every store is 16 bytes and a wavefront's are 1 KiB of consecutive addresses.
 constexpr int kRotRowStride = 264;  // halves; 528 bytes: 16-byte reads of 16 rows touch all banks
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rotate_rows_kernel(const _Float16* __restrict__ X, int M, int KB, int64_t ldx, int mts,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void rotate_rows_kernel(const _Float16* __restrict__ X, int M, int KB, int64_t ldx, int mts,
                                                               _Float16* __restrict__ Xt, _Float16* __restrict__ X0, uint32_t* __restrict__ flags) {
     __shared__ __align__(16) _Float16 rows[16 * kRotRowStride];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int tile = (int)blockIdx.x / KB, b = (int)blockIdx.x - tile * KB;  // tile = group * mts + mt
     const int group = tile / mts, mt = tile - group * mts;
-    half4 xa[4];
+    half4 xa[2];
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const int m = tile * 16 + wave * 4 + rr;
+    for (int rr = 0; rr < 2; ++rr) {
+        const int m = tile * 16 + wave * 2 + rr;
         xa[rr] = half4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
         if (m < M) xa[rr] = *reinterpret_cast<const half4*>(X + (int64_t)m * ldx + (int64_t)b * kBlock + 16 * (lane & 15) + 4 * (lane >> 4));
     }
     bool ok = true;
     const int s = lane & 15;
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
+    for (int rr = 0; rr < 2; ++rr) {
         _Float16 r[4];
         ok = rotate_operand(xa[rr], lane, r) && ok;
-        _Float16* const dst = rows + (wave * 4 + rr) * kRotRowStride + 64 * (lane >> 4) + 2 * (s & 7) + (s >> 3);
+        _Float16* const dst = rows + (wave * 2 + rr) * kRotRowStride + 64 * (lane >> 4) + 2 * (s & 7) + (s >> 3);
 #pragma unroll
         for (int j = 0; j < 4; ++j) dst[16 * j] = r[j];
     }
     const int64_t gb = (int64_t)group * KB + b;
-    if (lane == 0) *reinterpret_cast<half4*>(X0 + (gb * 4 + wave) * (mts <= 2 ? 8 : 16) + 4 * mt) = half4{xa[0][0], xa[1][0], xa[2][0], xa[3][0]};
+    if (lane == 0) *reinterpret_cast<half2v*>(X0 + (gb * 4 + (wave >> 1)) * (mts <= 2 ? 8 : 16) + 4 * mt + 2 * (wave & 1)) = half2v{xa[0][0], xa[1][0]};
     if (!ok && flags != nullptr) atomicOr(flags, kFlagActRange);
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int t = wave + 4 * u;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(rows + (lane & 15) * kRotRowStride + 64 * (lane >> 4) + 16 * (t >> 1) + 8 * (t & 1));
-        *reinterpret_cast<u32x4*>(Xt + (((gb * 8 + t) * mts + mt) * 64 + lane) * 8) = v;
-    }
+    const u32x4 v = *reinterpret_cast<const u32x4*>(rows + (lane & 15) * kRotRowStride + 64 * (lane >> 4) + 16 * (wave >> 1) + 8 * (wave & 1));
+    *reinterpret_cast<u32x4*>(Xt + (((gb * 8 + wave) * mts + mt) * 64 + lane) * 8) = v;  // step t = wave
 }
 
 // Operand order of the tiled kernel: rows stay rows; inside every group of 16 channels, slot s moves
@@ -189,7 +185,7 @@ int launch_rotate_frag(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int
 int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int mt, int groups, _Float16* Xt, _Float16* X0, uint32_t* flags,
                        hipStream_t stream) {
     const int64_t tiles = (int64_t)mt * groups * (K / kBlock);
-    hipLaunchKernelGGL(rotate_rows_kernel, dim3((unsigned)tiles), dim3(256), 0, stream, X, (int)M, (int)(K / kBlock), ldx, mt, Xt, X0, flags);
+    hipLaunchKernelGGL(rotate_rows_kernel, dim3((unsigned)tiles), dim3(512), 0, stream, X, (int)M, (int)(K / kBlock), ldx, mt, Xt, X0, flags);
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
