@@ -1,5 +1,5 @@
-// Tiled matmul for M > 16 activation rows (the prefill path): a dense contraction on the matrix
-// cores.  Alg. 2 dequantizes a weight tile into on-chip memory and multiplies from there; here the
+// Tiled matmul for the calls with more activation rows or larger products than the streaming kernels take
+// (the prefill path): a dense contraction on the matrix cores.  Alg. 2 dequantizes a weight tile into on-chip memory and multiplies from there; here the
 // operand fed to the matrix cores holds the un-rotated grid values d (q - z) in fp16 (exact for
 // z = 0), the rotation having been moved to the activations (Sec. 2.3: <H v, x> = <v, H x>), so the
 // weight path needs three packed-fp16 operations per pair of weights and no butterflies.

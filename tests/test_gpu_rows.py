@@ -50,9 +50,10 @@ SIZES = [
     (160, 4096, 1024),
     (257, 333, 11008),
     (1024, 2048, 512),
-    (70, 40, 262144),   # the longest K the kernel takes at this M is below this: the tiled kernel
-    (64, 40, 262144),   # the longest K
-    (20, 24, 262400),   # one block more: two passes of the kernel for up to 16 rows
+    (64, 40, 165376),   # nearly the longest K at 64 rows (rotated activations of 32 MB)
+    (20, 24, 250112),   # ... and at 20
+    (64, 40, 196608),   # beyond: the tiled kernel
+    (20, 24, 262400),   # beyond: two passes of the kernel for up to 16 rows
 ]
 
 
