@@ -96,11 +96,12 @@ int itq3s_dequantize(const uint32_t *codes, const uint32_t *scales, int64_t N, i
                      int64_t ldo, uint32_t *status_flags, void *stream);
 
 /* Fused matmul (problem statement of Alg. 2; Sec. 5.4 for M = 1):  Y[m][n] = sum_k X[m][k] w_hat[n][k].
- * No dequantized weight is written to memory.  M <= 16 takes the bandwidth-bound streaming path, more
- * rows a second streaming kernel as long as 2 M N K stays below about 36 GFLOP (any N for M <= 64) and the
- * rotated activations (rows rounded up to groups of 32 to 64) below 32 MB, larger calls the tiled MFMA
- * path (M <= 32 with more than that: two passes of the first).  M > 16 accepts K <= 4194304 only: ITQ3S_ERR_SHAPE beyond; M <= 16 K <= 2^28.  fp32 accumulation in all, the
- * zero-point terms included: an output element is rounded once.
+ * No dequantized weight is written to memory.  M <= 16 takes the bandwidth-bound streaming path; more
+ * rows a second streaming kernel as long as 2 M N K stays below about 36 GFLOP and M N below 3.4 million
+ * (any N for M <= 64) and the rotated activations (rows rounded up to groups of 32 to 64) below 32 MB;
+ * larger calls the tiled MFMA path (M <= 32 with more rotated activations: two passes of the first).
+ * M > 16 accepts K <= 4194304 only (ITQ3S_ERR_SHAPE beyond), M <= 16 K <= 2^28.  fp32 accumulation in
+ * all, the zero-point terms included: an output element is rounded once.
  * Activation range.  Every 256-channel chunk x of a row of X is replaced by x~ = H x, rounded to
  * fp16, after an intermediate T = X_16x16 H_16 / 4 that is split into fp16 parts.  Both stay
  * finite whenever  max|x| <= 16376  and  |(H x)_k| <= 65504  over the chunk (the second holds if

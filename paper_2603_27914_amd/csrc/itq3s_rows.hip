@@ -21,8 +21,8 @@
 // busy, and K is shared out inside the workgroup.  The tiled kernel at these sizes has its 128 x 256 tiles
 // partly empty and leaves most units idle, or splits K and pays the shares' way through memory.
 // Measured, whole call with the rotation launch, before (two passes of the kernel for 16 rows up to 32,
-// tiled kernel above) / now, us: 4096x4096 M = 32 14.3 / 9.8, M = 48 30 / 11, M = 512 38 / 31; three such
-// tensors in one group M = 48 86 / 16; two of 4096x11008 M = 48 66 / 24; 11008x4096 M = 48 40 / 20;
+// tiled kernel above) / now, us (K x N): 4096x4096 M = 32 14.3 / 9.2, M = 48 30 / 10.8, M = 512 38 / 31; three such
+// tensors in one group M = 48 86 / 15; two of 4096x11008 M = 48 66 / 23; 11008x4096 M = 48 40 / 18.9;
 // 8192x28672 M = 48 76 / 43.
 //
 // Order of the loads: a wavefront's load counter is in order, so the weights of the next block are issued
@@ -356,14 +356,16 @@ size_t rows_xt_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (si
 size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)(K / kBlock) * 3; }  // 64 bytes per 32 rows, 128 per 48 or 64
 
 // When the streaming kernel takes a tensor's call.  Its time over 2 M N K grows about 1.4 times as fast
-// as the tiled kernel's (0.7 against 1.0 PFLOP/s once the chip is full), but it starts 16 us earlier
-// (no 128 x 256 tiles that leave the chip empty, no shares of K to write and add): measured here / there
-// in us, 4096x4096 M = 64 12 / 31, 512 31 / 38, 768 45 / 48, 1024 59 / 56; 28672x8192 M = 64 49 / 76,
-// 96 68 / 77, 128 80 / 79, 256 150 / 131; 2048x2048 M = 1024 24 / 34.  The lines meet at about 36
-// GFLOP.  A rule on the sizes of one tensor: a grouped call computes every tensor as a call of its own does.
+// as the tiled kernel's (0.7 against 1.0 PFLOP/s once the chip is full), but it starts 10 to 15 us earlier
+// (no 128 x 256 tiles that leave the chip empty, no shares of K to write and add).  Measured here / there, us
+// (K x N): 8192x8192 M = 128 28 / 37, 256 49 / 51, 300 67 / 69; 11008x4096 M = 256 36 / 43, 500 63 / 63;
+// 28672x8192 M = 96 68 / 77, 128 79 / 78: the lines meet at about 36 GFLOP.  With short K the ends of the items count
+// as well, and they meet at fewer outputs: 4096x4096 M = 512 31 / 36, 768 44 / 47, 900 57 / 50; 4096x14336
+// M = 192 39 / 47, 256 50 / 47; 2048x2048 M = 1024 23 / 34, 1536 36 / 34: 3.4 million.  A rule on the
+// sizes of one tensor: a grouped call computes every tensor as a call of its own does.
 bool rows_path(int64_t M, int64_t N, int64_t K) {
     if (M <= kGemvMaxM || K > kRowsMaxK || M > kRowsMaxM) return false;
-    if (M > 64 && (double)M * (double)N * (double)K > 18e9) return false;
+    if (M > 64 && ((double)M * (double)N * (double)K > 18e9 || (double)M * (double)N > 3.4e6)) return false;
     // the padded rows must not take a call over a scratch limit that the tiled path keeps
     return rows_xt_bytes(M, K) + rows_x0_bytes(M, K) <= (32u << 20);
 }
