@@ -116,11 +116,9 @@ def _check(status):
         raise Itq3sError("libitq3s: %s (status %d)" % (lib().itq3s_strerror(status).decode(), status))
 
 
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-
-
 def _stream():
-    return _raw_stream(_device())
+    # (looked up per call: a torch without device support has neither, and this module still imports there)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):

@@ -4,6 +4,8 @@ launching anything (these calls return before the first HIP call, so they run wi
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -98,6 +100,21 @@ def test_binding_refuses_cpu_tensors():
 
     with pytest.raises(binding.Itq3sError):
         binding.itq3s_quantize(torch.zeros(16, 256))
+
+
+def test_binding_imports_on_a_torch_without_device_support():
+    """Such a torch has no stream accessors; only the calls that need a device fail there."""
+    code = (
+        "import torch\n"
+        "for name in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+        "    if hasattr(torch._C, name): delattr(torch._C, name)\n"
+        "from paper_2603_27914_amd import binding\n"
+        "assert binding.itq3s_codes_bytes(16, 256) == 1536\n"
+        "try: binding.itq3s_quantize(torch.zeros(16, 256))\n"
+        "except binding.Itq3sError: pass\n"
+        "else: raise AssertionError('a CPU tensor was accepted')\n"
+    )
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
 
 
 def test_binding_checks_packed_tensors_against_the_shape():
