@@ -27,6 +27,10 @@
 
 namespace itq3s {
 
+// Sixteen bytes that promise the alignment of eight: ldo need only be a multiple of four elements, so rows of
+// fp16 output may start between two 16-byte boundaries.
+typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+
 // Rows per wavefront.  fp32: four -- with eight, 11008x4096 took 34 us instead of 30 and 28672x8192 171 instead
 // of 144 (more rows of one wavefront open at a time); fp16: eight (28672x8192 84 us with four, 78 with eight).
 constexpr int dq_rows(bool out_f16) { return out_f16 ? 8 : 4; }
@@ -134,8 +138,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void d
             const auto s0 = __builtin_amdgcn_permlane16_swap(a.x, c.x, false, false), s1 = __builtin_amdgcn_permlane16_swap(a.y, c.y, false, false);
             const int64_t n = n0 + R + (g & 1);
             if (n < N)
-                __builtin_nontemporal_store(u32x4{s0[0], s1[0], s0[1], s1[1]},
-                                            reinterpret_cast<u32x4*>(reinterpret_cast<_Float16*>(out) + n * ldo + col + 16 * r16 + 8 * (g >> 1)));
+                __builtin_nontemporal_store(u32x4_a8{s0[0], s1[0], s0[1], s1[1]},
+                                            reinterpret_cast<u32x4_a8*>(reinterpret_cast<_Float16*>(out) + n * ldo + col + 16 * r16 + 8 * (g >> 1)));
         } else {
             float* const dst = reinterpret_cast<float*>(out) + (n0 + R) * ldo + col + 16 * r16 + 4 * g;
             if (n0 + R < N) __builtin_nontemporal_store(f0, reinterpret_cast<floatx4*>(dst));

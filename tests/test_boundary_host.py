@@ -148,3 +148,17 @@ def test_binding_checks_packed_tensors_against_the_shape():
         binding._need_flags(torch.zeros(1, dtype=torch.float32))
     binding._need_flags(None)
     binding._need_flags(torch.zeros(1, dtype=torch.int32))
+
+
+def test_dequantize_stores_promise_no_more_alignment_than_the_header():
+    """The output's rows start at multiples of four elements: 16 bytes in fp32, eight in fp16.  The fp16 kernels
+    store four 32-bit words at once, which must not claim 16-byte alignment (read from the compiler's
+    intermediate code: the hardware accepts the access either way)."""
+    from paper_2603_27914_amd import build
+
+    src = os.path.join(build.CSRC, "itq3s_dequantize.hip")
+    cmd = ["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-emit-llvm", src, "-o", "-"]
+    ir = subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
+    stores = re.findall(r"store <4 x (i32|float)> .*, align (\d+),.* !nontemporal", ir)
+    assert {t for t, _ in stores} == {"i32", "float"}
+    assert {a for t, a in stores if t == "i32"} == {"8"} and {a for t, a in stores if t == "float"} == {"16"}

@@ -36,3 +36,30 @@ def test_dequantize_row_edges(N, K):
         # integers up to fp32's 24 bits, one rounding of the product, one to fp16 (2^-25 below its normal range)
         assert np.all(np.abs(got[:, :K] - want) <= ulp * np.abs(want) + (2.0**-25 if dtype == torch.float16 else 0.0))
         assert int(flags.item()) == (binding.FLAG_BAD_CODE if N > 1 else 0)
+
+
+@pytest.mark.parametrize("sub", [False, True])
+def test_dequantize_rows_between_two_16_byte_boundaries(sub):
+    """A row stride that is a multiple of four elements but not of eight: in fp16 every other row starts eight
+    bytes behind a 16-byte boundary.  Against the contiguous output, and the padding columns stay."""
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_27914_amd import binding
+
+    N, K = 41, 1280
+    codes, scales = random_packed(N, K, "dqa", z_fraction=0.3)
+    cd, sd = (torch.from_numpy(a.view(np.int32)).cuda() for a in (codes, scales))
+    s = np.random.default_rng(5).uniform(0.25, 2.0, size=(codes.size // 384 * 64, 2)).astype(np.float16)
+    ud = torch.from_numpy(s.view(np.int32).reshape(-1)).cuda()
+    L = binding.lib()
+    for dtype, code in ((torch.float32, binding.F32), (torch.float16, binding.F16)):
+        want = binding.itq3s_dequantize_sub(cd, sd, ud, N, K, dtype=dtype) if sub else binding.itq3s_dequantize(cd, sd, N, K, dtype=dtype)
+        buf = torch.full((N, K + 4), 7.0, dtype=dtype, device="cuda")
+        if sub:
+            rc = L.itq3s_dequantize_sub(cd.data_ptr(), sd.data_ptr(), ud.data_ptr(), N, K, buf.data_ptr(), code, K + 4, None, binding._stream())
+            assert rc == 0
+        else:
+            binding.itq3s_dequantize(cd, sd, N, K, out=buf[:, :K])
+        assert torch.equal(buf[:, :K], want) and bool((buf[:, K:] == 7.0).all())
