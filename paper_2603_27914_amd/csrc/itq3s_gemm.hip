@@ -21,8 +21,6 @@
 #include <type_traits>
 
 #include "itq3s_dev.h"
-#include <atomic>
-
 #include "itq3s_kernels.h"
 
 namespace itq3s {
@@ -684,11 +682,8 @@ int launch_gemm(const GemvWeight* w, int count, int64_t K, const _Float16* Xt, c
                 size_t partial_bytes, uint32_t* zflags, uint32_t* flags, hipStream_t stream) {
     const int64_t tiles_m = (M + GM - 1) / GM;
     if (K > kGemmMaxK) return -2;
-    static std::atomic<bool> lds_limit_raised{false};
-    if (!lds_limit_raised) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) != hipSuccess) return -6;
-        lds_limit_raised = true;
-    }
+    static DeviceOnce lds_limit;
+    if (!raise_lds_limit(lds_limit, reinterpret_cast<const void*>(gemm_kernel), kGemmLds)) return -6;
     GemmGroup group;
     GemmArgs& a = group.common;
     a.codes = nullptr; a.scales = nullptr; a.Y = nullptr; a.N = 0; a.ldy = 0; a.NT = 0;

@@ -28,8 +28,6 @@
 #include <hip/hip_ext.h>
 
 #include "itq3s_dev.h"
-#include <atomic>
-
 #include "itq3s_kernels.h"
 
 namespace itq3s {
@@ -215,11 +213,8 @@ __global__ __launch_bounds__(512) void gemm_ws_kernel(const GemmWsArgs a) {
 
 template <bool kSub>
 static int launch_ws(const GemmWsArgs& a, dim3 grid, hipStream_t stream) {
-    static std::atomic<bool> lds_limit_raised{false};
-    if (!lds_limit_raised) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ws_kernel<kSub>), hipFuncAttributeMaxDynamicSharedMemorySize, kGemmWsLds) != hipSuccess) return -6;
-        lds_limit_raised = true;
-    }
+    static DeviceOnce lds_limit;
+    if (!raise_lds_limit(lds_limit, reinterpret_cast<const void*>(gemm_ws_kernel<kSub>), kGemmWsLds)) return -6;
     const LaunchTiming tm = take_launch_timing();
     if (tm.start != nullptr) hipExtLaunchKernelGGL(gemm_ws_kernel<kSub>, grid, dim3(512), kGemmWsLds, stream, tm.start, tm.stop, 0, a);
     else hipLaunchKernelGGL(gemm_ws_kernel<kSub>, grid, dim3(512), kGemmWsLds, stream, a);

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "itq3s_once.h"
+
 namespace itq3s {
 
 constexpr uint32_t kFlagNonFinite = 1u, kFlagScaleSat = 2u, kFlagZClamp = 4u, kFlagBadCode = 8u, kFlagActRange = 16u;
@@ -86,6 +88,13 @@ int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int
 
 // Compute units of the current device (cached).
 int cu_count();
+
+// Lets `kernel` take `bytes` of dynamic LDS on the current device.
+inline bool raise_lds_limit(DeviceOnce& once, const void* kernel, int bytes) {
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess) return false;
+    return once(device, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; });
+}
 
 // Tiled matmul, M > 16.  Xt = rotated activations (launch_rotate_rowmajor); X, ldx = the activations
 // themselves (zero-point term).  Shapes with few output tiles split K over several workgroups per tile

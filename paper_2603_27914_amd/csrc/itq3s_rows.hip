@@ -33,7 +33,6 @@
 // the nontemporal hint (2..7 % slower with one group of rows, even with several).
 #include <hip/hip_ext.h>
 
-#include <atomic>
 #include <type_traits>
 
 #include "itq3s_dev.h"
@@ -313,11 +312,8 @@ static int launch_rows_kernel(const RowsArgs& a, hipStream_t stream) {
     auto kern = rows_kernel<MT, RT, kGrouped>;
     constexpr int kLds = kRowsWaves * RT * MT * 1024;
     if constexpr (kLds > 65536) {
-        static std::atomic<bool> lds_limit_raised{false};
-        if (!lds_limit_raised) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess) return -6;
-            lds_limit_raised = true;
-        }
+        static DeviceOnce lds_limit;
+        if (!raise_lds_limit(lds_limit, reinterpret_cast<const void*>(kern), kLds)) return -6;
     }
     const LaunchTiming tm = take_launch_timing();
     const dim3 grid((unsigned)a.wg_per_chiplet * 8u), block(kRowsWaves * 64);

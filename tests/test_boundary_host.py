@@ -162,3 +162,33 @@ def test_dequantize_stores_promise_no_more_alignment_than_the_header():
     stores = re.findall(r"store <4 x (i32|float)> .*, align (\d+),.* !nontemporal", ir)
     assert {t for t, _ in stores} == {"i32", "float"}
     assert {a for t, a in stores if t == "i32"} == {"8"} and {a for t, a in stores if t == "float"} == {"16"}
+
+
+def test_settings_kept_per_device_are_made_on_every_device(tmp_path):
+    """A kernel's limit of dynamic LDS belongs to one device: each device that the process runs on gets it
+    once, a failure is not remembered, devices beyond the remembered ones get it on every call."""
+    main = tmp_path / "once.cpp"
+    main.write_text(
+        '#include "itq3s_once.h"\n'
+        "#include <cstdio>\n"
+        "int main() {\n"
+        "    static itq3s::DeviceOnce once;\n"
+        "    const int devices[] = {0, 0, 1, 0, 1, 63, 63, 64, 64, 2, 2, 2};\n"
+        "    int calls = 0;\n"
+        "    for (int d : devices) {\n"
+        "        bool called = false;\n"
+        "        const bool ok = once(d, [&] { called = true; return d != 2 || ++calls > 1; });\n"
+        '        std::printf("%d%d ", (int)called, (int)ok);\n'
+        "    }\n"
+        "}\n"
+    )
+    from paper_2603_27914_amd import build
+
+    exe = tmp_path / "once"
+    subprocess.run(["g++", "-std=c++17", "-I", build.CSRC, str(main), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()
+    #                    0     0     1     0     1     63    63    64    64    2 (fails) 2     2
+    assert out == ["11", "01", "11", "01", "01", "11", "01", "11", "11", "10", "11", "01"]
+    for name in os.listdir(build.CSRC):  # ... and nothing raises the limit in another way
+        if name.endswith((".hip", ".h")) and name != "itq3s_kernels.h":
+            assert "hipFuncSetAttribute" not in open(os.path.join(build.CSRC, name)).read(), name
