@@ -49,7 +49,7 @@ extern "C" {
 #define ITQ3S_ERR_SHAPE (-2)     /* N, K, M <= 0, K % 256 != 0, or a leading dimension too small   */
 #define ITQ3S_ERR_ALIGN (-3)     /* a pointer or leading dimension breaks the stated alignment     */
 #define ITQ3S_ERR_DTYPE (-4)     /* dtype argument is not ITQ3S_F32 / ITQ3S_F16                    */
-#define ITQ3S_ERR_WORKSPACE (-5) /* workspace NULL or smaller than itq3s_matmul_workspace_bytes    */
+#define ITQ3S_ERR_WORKSPACE (-5) /* workspace NULL or too small (itq3s_matmul_workspace_bytes)     */
 #define ITQ3S_ERR_LAUNCH (-6)    /* the HIP runtime refused a launch (see hipGetLastError)         */
 
 #define ITQ3S_F32 0
@@ -73,7 +73,11 @@ size_t itq3s_scales_bytes(int64_t N, int64_t K);
  * M <= 4: 256 (the streaming kernel rotates inside the kernel; the workspace is not touched).
  * Larger M: room for the rotated activations (rows rounded up), grows with M*K; for M > 16 and shapes with
  * few output tiles (at most 128 tiles of 128 x 256) also the partial sums of the workgroups that share a
- * tile's K range (up to 8 x M x N x 4 bytes, tiles rounded up).  A function of the three sizes only. */
+ * tile's K range (up to 8 x M x N x 4 bytes, tiles rounded up).  A function of the three sizes only, and
+ * NOT monotone in M: a workspace for calls with several M needs the largest of their sizes.
+ * It is the room for the fastest route.  For M > 16 a call still succeeds with less, as long as the activation
+ * rows as they are fit (for M <= 32 those of a pass of 16) and the partial sums do: it then takes the tiled
+ * path, for M <= 32 two passes of the streaming one, with results that differ in the last bits. */
 size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /* Offline quantization (Alg. 1, Def. 1).  Per block: w' = H w in fp64 (butterfly stages
@@ -142,7 +146,8 @@ int itq3s_matmul_static(const uint32_t *codes, const uint32_t *scales, int64_t N
  *           scales (as for itq3s_matmul), rows N, output Y (M x N of y_dtype, row stride ldy >= N)
  *   X, M, ldx, y_dtype, status_flags, stream: as for itq3s_matmul
  *   workspace: at least the largest itq3s_matmul_workspace_bytes(M, N_t, K) over the tensors of the call
- *           (ITQ3S_ERR_WORKSPACE otherwise: how a tensor is computed never depends on the room given) */
+ *           (with that much, how a tensor is computed never depends on the room given; with less as described
+ *           there, ITQ3S_ERR_WORKSPACE where the largest tensor's partial sums do not fit) */
 #define ITQ3S_MAX_GROUP 4
 typedef struct itq3s_weight {
     const uint32_t *codes;

@@ -50,9 +50,10 @@ struct WorkspacePlan {
 constexpr int64_t kChunkedMaxM = 2 * itq3s::kGemvMaxM;  // up to here M > 16 runs as passes of the streaming kernel
 constexpr int64_t kSubStreamingMaxM = 64;               // sub-block variant: up to here passes of four rows, the tiled weight-side kernel above
 
+// (of the routes that every call can take; the many-row kernel's own need: rows_workspace)
 WorkspacePlan plan_workspace(int64_t M, int64_t N, int64_t K) {
-    WorkspacePlan p;
     if (M > itq3s::kGemvMaxM && M <= kChunkedMaxM) return plan_workspace(itq3s::kGemvMaxM, N, K);
+    WorkspacePlan p;
     if (M <= itq3s::kGemvFusedMaxM) {  // the streaming kernel rotates the activations itself: nothing to park
         p.xt_bytes = p.s_bytes = p.flag_bytes = p.partial_bytes = 0;
         p.total = 256;
@@ -68,6 +69,9 @@ WorkspacePlan plan_workspace(int64_t M, int64_t N, int64_t K) {
     p.total = p.xt_bytes + p.s_bytes + p.flag_bytes + p.partial_bytes + 256;
     return p;
 }
+
+// Scratch of the streaming kernel for many rows: the same for every tensor of a call.
+size_t rows_workspace(int64_t M, int64_t K) { return round_up(itq3s::rows_xt_bytes(M, K), 256) + round_up(itq3s::rows_x0_bytes(M, K), 256); }
 
 }  // namespace
 
@@ -108,9 +112,8 @@ size_t itq3s_scales_bytes(int64_t N, int64_t K) {
 
 size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0 || K % 256 != 0) return 256;
-    // (what the call needs is the larger of the two for a tensor that the streaming kernel for many rows
-    // takes; a size that held before that kernel was there still holds)
-    const size_t rows = itq3s::rows_path(M, N, K) ? round_up(itq3s::rows_xt_bytes(M, K), 256) + round_up(itq3s::rows_x0_bytes(M, K), 256) : 0;
+    // room for the fastest route and for the one that a call with less room falls back to
+    const size_t rows = itq3s::rows_path(M, N, K) ? rows_workspace(M, K) : 0;
     const size_t other = plan_workspace(M, N, K).total;
     return rows > other ? rows : other;
 }
@@ -163,7 +166,7 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
         if (!w[i].codes || !w[i].scales || !w[i].Y) return ITQ3S_ERR_NULL;
         if (w[i].N <= 0 || w[i].ldy < w[i].N || (w[i].N + 15) / 16 > 0x7fffffffLL / (K / 256)) return ITQ3S_ERR_SHAPE;
         if (!aligned(w[i].codes, 16) || !aligned(w[i].scales, 16) || !aligned(w[i].Y, y_dtype == ITQ3S_F16 ? 2 : 4)) return ITQ3S_ERR_ALIGN;
-        const size_t need_i = itq3s_matmul_workspace_bytes(M, w[i].N, K);
+        const size_t need_i = plan_workspace(M, w[i].N, K).total;
         if (need_i > need) need = need_i;
     }
     if (!aligned(X, 16) || ldx % 8 != 0 || (status_flags && !aligned(status_flags, 4))) return ITQ3S_ERR_ALIGN;
@@ -173,8 +176,10 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
     hipStream_t st = static_cast<hipStream_t>(stream);
     // Tensors that the streaming kernel for many rows takes go first, in one launch; what is left is
     // computed as if it were a call of its own (its scratch lies over theirs: same stream, one after the other).
+    // That kernel pads the activation rows, up to four times as many at M = 17: room that a call sized for the
+    // other routes, or for another M, may not have.  Such a call takes those routes.
     itq3s_weight rest[ITQ3S_MAX_GROUP];
-    if (M > itq3s::kGemvMaxM) {
+    if (M > itq3s::kGemvMaxM && workspace_bytes >= rows_workspace(M, K)) {
         itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
         int n_rows = 0, n_rest = 0;
         for (int i = 0; i < count; ++i) {

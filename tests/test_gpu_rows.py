@@ -105,6 +105,32 @@ def test_many_rows_flags(gpu):
     assert int(flags.item()) == binding.FLAG_ACT_RANGE
 
 
+@pytest.mark.parametrize("M,N,K,less", [(17, 1000, 4096, "pass"), (32, 100, 11008, "pass"), (64, 33000, 256, "tiled")])
+def test_room_for_the_other_routes_is_still_enough(gpu, M, N, K, less):
+    """A call whose workspace has room for the passes of 16 rows or for the tiled kernel (no padded rows: sized
+    for those routes, or for another M) is computed by them: alone, in a group, twice on one workspace of
+    garbage.  One byte less is refused."""
+    torch, binding = gpu
+    codes, scales, What = tensor(torch, binding, N, K, "room", M)
+    X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
+    if less == "pass":
+        room = binding.itq3s_matmul_workspace_bytes(16, N, K)
+        want = torch.cat([binding.itq3s_matmul(codes, scales, N, K, X[m : m + 16]) for m in range(0, M, 16)])
+    else:  # 129 tiles do not split K: the activation rows, 512 bytes of flags, 256 bytes
+        room = (M * K * 2 + 255) // 256 * 256 + 768
+        want = None
+    assert room < binding.itq3s_matmul_workspace_bytes(M, N, K)
+    ws = torch.randint(0, 255, (room,), dtype=torch.uint8, device="cuda")
+    first = binding.itq3s_matmul(codes, scales, N, K, X, workspace=ws).clone()
+    check(first, X, What, False)
+    assert want is None or torch.equal(first, want)
+    assert torch.equal(first, binding.itq3s_matmul(codes, scales, N, K, X, workspace=ws))
+    for out in binding.itq3s_matmul_grouped([(codes, scales, N), (codes, scales, N)], K, X, dtype=torch.float32, workspace=ws):
+        assert torch.equal(first, out)
+    with pytest.raises(binding.Itq3sError, match="workspace"):
+        binding.itq3s_matmul(codes, scales, N, K, X, workspace=ws[: room - 1])
+
+
 # rotated activations of more than 32 MB, or a product too large for the streaming kernel
 @pytest.mark.parametrize("M,N,K,z", [(8200, 100, 2048, 0.02), (2100, 300, 8192, 0.6), (4200, 700, 4096, 0.0), (66000, 17, 256, 0.02), (517, 9300, 4096, 0.02)])
 def test_tiled_kernel_ragged(gpu, M, N, K, z):
