@@ -272,8 +272,13 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 // Store 32 rows (m_first ..) of a wavefront's 64 columns (n0 + 64 wn ..).  Accumulator register v of a
 // 32x32 block: row = 8*(v/4) + 4*(lane/32) + v%4, column = lane%32.  kTerms: minus the zero-point
 // terms of these rows, from registers (1) or from a few columns' strips in LDS, whose row of m_first is row0 (2).
-template <int kTerms>
-__device__ __forceinline__ void store_rows(const GemmArgs& a, const floatx16 (&acc)[2], int64_t m_first, int64_t n0, int wn, int lane,
+// Bound by instructions, fetched once each: 128 stores a lane in straight-line code.  With the output type asked
+// for and a 64-bit row product at every store (14 instructions), the wavefronts of a second, partly filled round
+// came up to each other's delay and the launch lost what the shorter main loop had gained: K x N = 1024x11008, M = 2048,
+// fp16, one block in a thousand with a zero-point 74.5 us; with the type as a template and one pointer moved
+// from row to row 59.1 (without zero-points 58.2 -> 53.5).
+template <int kTerms, typename Out>
+__device__ __forceinline__ void store_rows_as(const GemmArgs& a, const floatx16 (&acc)[2], int64_t m_first, int64_t n0, int wn, int lane,
                                            const floatx16 (*in_regs)[2] = nullptr, int row0 = 0, uint32_t strips = 0, const StripColumns* cols = nullptr) {
     const int l32 = lane & 31, kg = lane >> 5;
 #pragma unroll
@@ -300,17 +305,26 @@ __device__ __forceinline__ void store_rows(const GemmArgs& a, const floatx16 (&a
 #pragma unroll
             for (int v = 0; v < 16; ++v) terms[v] = slot < 0 ? 0.0f : __builtin_bit_cast(float, t[v]);
         }
+        const int rows = a.M - m_first < 32 ? (int)(a.M - m_first) : 32;  // of this block that exist
+        Out* dst = reinterpret_cast<Out*>(a.Y) + (m_first + 4 * kg) * a.ldy + n;
+        if (n < a.N) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t m = m_first + 8 * (v >> 2) + 4 * kg + (v & 3);
-            if (m < a.M && n < a.N) {
+            for (int v = 0; v < 16; ++v) {
+                const int row = 8 * (v >> 2) + 4 * kg + (v & 3);
                 float y = acc[j][v];
                 if constexpr (kTerms != 0) y = y - terms[v];
-                if (a.y_f16) reinterpret_cast<_Float16*>(a.Y)[m * a.ldy + n] = (_Float16)y;
-                else reinterpret_cast<float*>(a.Y)[m * a.ldy + n] = y;
+                if (row < rows) *dst = (Out)y;
+                dst += (v & 3) == 3 ? 5 * a.ldy : a.ldy;
             }
         }
     }
+}
+
+template <int kTerms>
+__device__ __forceinline__ void store_rows(const GemmArgs& a, const floatx16 (&acc)[2], int64_t m_first, int64_t n0, int wn, int lane,
+                                           const floatx16 (*in_regs)[2] = nullptr, int row0 = 0, uint32_t strips = 0, const StripColumns* cols = nullptr) {
+    if (a.y_f16) store_rows_as<kTerms, _Float16>(a, acc, m_first, n0, wn, lane, in_regs, row0, strips, cols);
+    else store_rows_as<kTerms, float>(a, acc, m_first, n0, wn, lane, in_regs, row0, strips, cols);
 }
 
 // Store a wavefront's 128 x 64 block (rows m0.., columns n0 + 64 wn ..).
