@@ -192,3 +192,16 @@ def test_settings_kept_per_device_are_made_on_every_device(tmp_path):
     for name in os.listdir(build.CSRC):  # ... and nothing raises the limit in another way
         if name.endswith((".hip", ".h")) and name != "itq3s_kernels.h":
             assert "hipFuncSetAttribute" not in open(os.path.join(build.CSRC, name)).read(), name
+
+
+@pytest.mark.parametrize("source", ["gemv", "rows", "rotate", "gemm", "gemm_ws", "dequantize", "quantize"])
+def test_kernels_keep_their_registers(source):
+    """No kernel of the path parks registers in scratch memory (a spill in one of the many instantiations of a
+    kernel costs time and nothing else, so no other test sees it)."""
+    from paper_2603_27914_amd import build
+
+    src = os.path.join(build.CSRC, "itq3s_%s.hip" % source)
+    cmd = ["hipcc", *build.FLAGS, "--cuda-device-only", "-S", src, "-o", "-"]
+    asm = subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
+    kernels = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_private_segment_fixed_size (\d+)", asm, flags=re.S)
+    assert kernels and [k for k in kernels if k[1] != "0"] == []
