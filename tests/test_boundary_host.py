@@ -157,7 +157,7 @@ def test_dequantize_stores_promise_no_more_alignment_than_the_header():
     from paper_2603_27914_amd import build
 
     src = os.path.join(build.CSRC, "itq3s_dequantize.hip")
-    cmd = ["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-emit-llvm", src, "-o", "-"]
+    cmd = ["hipcc", *build.flags(src), "--cuda-device-only", "-S", "-emit-llvm", src, "-o", "-"]
     ir = subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
     stores = re.findall(r"store <4 x (i32|float)> .*, align (\d+),.* !nontemporal", ir)
     assert {t for t, _ in stores} == {"i32", "float"}
@@ -201,7 +201,7 @@ def test_kernels_keep_their_registers(source):
     from paper_2603_27914_amd import build
 
     src = os.path.join(build.CSRC, "itq3s_%s.hip" % source)
-    cmd = ["hipcc", *build.FLAGS, "--cuda-device-only", "-S", src, "-o", "-"]
+    cmd = ["hipcc", *build.flags(src), "--cuda-device-only", "-S", src, "-o", "-"]
     asm = subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
     kernels = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_private_segment_fixed_size (\d+)", asm, flags=re.S)
     assert kernels and [k for k in kernels if k[1] != "0"] == []
