@@ -12,7 +12,7 @@
 // layout of the second, and the transposed result leaves every lane with four consecutive output
 // elements, e = 16 (l%16) + 4 (l/16) + 0..3: a wavefront stores one contiguous row segment.
 //
-// What bounds it: the stores (2 or 4 bytes per weight against 0.39 read).  A wavefront takes eight rows of a
+// What bounds it: the stores (2 or 4 bytes per weight against 0.39 read).  A wavefront takes eight or four rows of a
 // 16-row tile: it loads the tile's words once, coalesced (its lane of the rows' operand layout: 16 + 8 + 4
 // bytes), and hands a row's words to the lanes that need them inside the 16-lane rows of the vector ALU.
 // (Loading every row's words where they are needed -- four different addresses per instruction, twelve
@@ -32,8 +32,11 @@ namespace itq3s {
 typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
 
 // Rows per wavefront.  fp32: four -- with eight, 11008x4096 took 34 us instead of 30 and 28672x8192 171 instead
-// of 144 (more rows of one wavefront open at a time); fp16: eight (28672x8192 84 us with four, 78 with eight).
-constexpr int dq_rows(bool out_f16) { return out_f16 ? 8 : 4; }
+// of 144 (more rows of one wavefront open at a time).  fp16: eight (28672x8192 84 us with four, 78 with eight;
+// 4096x4096 8.1 and 7.4), but four for up to 1024 tiles: all wavefronts are resident at once then, and what
+// counts is the length of one (4096x256 3.76 us with eight, 3.47 with four; 1000x4096 4.50 and 4.31, 2048x4096,
+// which is beyond, 5.17 and 5.29).
+constexpr int64_t kDqShortTiles = 1024;  // 4096 wavefronts of four rows: four per SIMD
 
 // value of lane R of the lane's own 16-lane row
 template <int R>
@@ -49,7 +52,7 @@ __device__ __forceinline__ float row_lane(float v) {
 // four digits belong to sub-blocks 2g (the first two) and 2g+1, whose scales are the two halves of
 // the lane's own word of the sub-scale array; s q is exact in fp16, the first product (16 terms of one
 // sub-block: a 16-bit number) is carried in two fp16 parts, the second adds 16 such terms in fp32.
-struct DqTile {  // a lane's words of the wavefront's eight rows: storage lane 16 g + row of the tile for r16 = row - first row
+struct DqTile {  // a lane's words of the wavefront's rows: storage lane 16 g + row of the tile for r16 = row - first row
     u32x4 lo;
     u32x2 hi;
     uint32_t ss;
@@ -95,14 +98,14 @@ __device__ __forceinline__ floatx4 dequantize_row(const DqTile& t, bool any_hi, 
     return floatx4{d16 * U[0], d16 * U[1], d16 * U[2], d16 * U[3]};
 }
 
-template <bool kOutF16, bool kSub>
+template <bool kOutF16, bool kSub, int kRows>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void dequantize_kernel(const uint32_t* __restrict__ codes, const uint32_t* __restrict__ scales,
                                                          const uint32_t* __restrict__ subscales, int64_t N, int KB, int64_t parts, void* __restrict__ out, int64_t ldo,
                                                          uint32_t* __restrict__ flags) {
     const int lane = lane_id();
     const int64_t part = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // kParts per tile
     if (part >= parts) return;
-    constexpr int kRows = dq_rows(kOutF16), kParts = kTileRows / kRows;
+    constexpr int kParts = kTileRows / kRows;
     const uint32_t tile = (uint32_t)(part / kParts), nt = tile / (uint32_t)KB, b = tile - nt * (uint32_t)KB;
     const int first = (int)(part % kParts) * kRows;
     const int r16 = lane & 15, g = lane >> 4;
@@ -154,20 +157,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void d
     }
 }
 
+template <bool kOutF16, int kRows>
+static int launch_dequantize_rows(const uint32_t* codes, const uint32_t* scales, const uint32_t* subscales, int64_t N, int64_t tiles, int KB, void* out,
+                                  int64_t ldo, uint32_t* flags, hipStream_t stream) {
+    const int64_t parts = tiles * (kTileRows / kRows);
+    const dim3 grid((unsigned)((parts + 3) / 4)), block(256);
+    if (subscales != nullptr) hipLaunchKernelGGL((dequantize_kernel<kOutF16, true, kRows>), grid, block, 0, stream, codes, scales, subscales, N, KB, parts, out, ldo, flags);
+    else hipLaunchKernelGGL((dequantize_kernel<kOutF16, false, kRows>), grid, block, 0, stream, codes, scales, subscales, N, KB, parts, out, ldo, flags);
+    return hipGetLastError() == hipSuccess ? 0 : -6;
+}
+
 int launch_dequantize(const uint32_t* codes, const uint32_t* scales, const uint32_t* subscales, int64_t N, int64_t K, void* out, int out_f16,
                       int64_t ldo, uint32_t* flags, hipStream_t stream) {
     const int64_t tiles = ((N + 15) / 16) * (K / kBlock);
     const int KB = (int)(K / kBlock);
-    const int64_t parts = tiles * (kTileRows / dq_rows(out_f16));
-    const dim3 grid((unsigned)((parts + 3) / 4)), block(256);
-    if (subscales != nullptr) {
-        if (out_f16) hipLaunchKernelGGL((dequantize_kernel<true, true>), grid, block, 0, stream, codes, scales, subscales, N, KB, parts, out, ldo, flags);
-        else hipLaunchKernelGGL((dequantize_kernel<false, true>), grid, block, 0, stream, codes, scales, subscales, N, KB, parts, out, ldo, flags);
-    } else {
-        if (out_f16) hipLaunchKernelGGL((dequantize_kernel<true, false>), grid, block, 0, stream, codes, scales, subscales, N, KB, parts, out, ldo, flags);
-        else hipLaunchKernelGGL((dequantize_kernel<false, false>), grid, block, 0, stream, codes, scales, subscales, N, KB, parts, out, ldo, flags);
-    }
-    return hipGetLastError() == hipSuccess ? 0 : -6;
+    if (!out_f16) return launch_dequantize_rows<false, 4>(codes, scales, subscales, N, tiles, KB, out, ldo, flags, stream);
+    if (tiles <= kDqShortTiles) return launch_dequantize_rows<true, 4>(codes, scales, subscales, N, tiles, KB, out, ldo, flags, stream);
+    return launch_dequantize_rows<true, 8>(codes, scales, subscales, N, tiles, KB, out, ldo, flags, stream);
 }
 
 }  // namespace itq3s

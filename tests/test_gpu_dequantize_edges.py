@@ -63,3 +63,25 @@ def test_dequantize_rows_between_two_16_byte_boundaries(sub):
         else:
             binding.itq3s_dequantize(cd, sd, N, K, out=buf[:, :K])
         assert torch.equal(buf[:, :K], want) and bool((buf[:, K:] == 7.0).all())
+
+
+@pytest.mark.parametrize("N", [16377, 16384, 16385, 16391, 16393, 16400])
+@pytest.mark.parametrize("sub", [False, True])
+def test_fp16_rows_per_wavefront_on_both_sides_of_the_line(N, sub):
+    """Up to 1024 tiles four rows per wavefront, beyond eight: either way each value is the fp32 output's (one
+    rounding of the same product) rounded to fp16."""
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_27914_amd import binding
+
+    K = 256
+    cd, sd = (torch.from_numpy(a.view(np.int32)).cuda() for a in random_packed(N, K, "dql", z_fraction=0.3))
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    ud = (0.25 + 1.75 * torch.rand((cd.numel() // 384 * 64, 2), generator=gen, device="cuda")).half().view(torch.int32).reshape(-1)
+    if sub:
+        full, half = (binding.itq3s_dequantize_sub(cd, sd, ud, N, K, dtype=t) for t in (torch.float32, torch.float16))
+    else:
+        full, half = (binding.itq3s_dequantize(cd, sd, N, K, dtype=t) for t in (torch.float32, torch.float16))
+    assert torch.equal(full.half(), half)
