@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "itq3s_once.h"
+#include "itq3s_rows_rule.h"
 
 namespace itq3s {
 
@@ -75,11 +76,6 @@ int launch_gemv_rows(const GemvWeight* w, int count, int64_t K, const _Float16* 
 // The streaming kernel for more rows than launch_gemv_rows takes (rows_path() says for which calls):
 // rotates the activations into Xt (rows_xt_bytes) and X0 (rows_x0_bytes), both 256-byte aligned, then one
 // launch over all row tiles and groups of up to 64 rows.
-constexpr int64_t kRowsMaxM = 1 << 16;
-constexpr int64_t kRowsMaxK = 1 << 18;
-bool rows_path(int64_t M, int64_t N, int64_t K);
-size_t rows_xt_bytes(int64_t M, int64_t K);
-size_t rows_x0_bytes(int64_t M, int64_t K);
 int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, _Float16* Xt, _Float16* X0, int y_f16,
                 uint32_t* flags, hipStream_t stream);
 // Rotated activations for it: groups x mt tiles of 16 rows, layout at rotate_rows_kernel.

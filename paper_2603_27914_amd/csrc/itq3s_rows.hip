@@ -41,8 +41,7 @@
 
 namespace itq3s {
 
-constexpr int kRowsWaves = 8;
-constexpr int kRowsMaxRT = 4;  // row tiles per item, at most (256 registers with 64 rows)
+static_assert(kRowsMinM == kGemvMaxM + 1 && kBlock == 256, "the host side counts blocks of 256");
 
 struct RowsArgs {
     GemvTensor t[kGemvMaxGroup];
@@ -339,33 +338,6 @@ static int launch_rows_mt(const RowsArgs& a, int rt, hipStream_t stream) {
     return -2;
 }
 
-// Activation rows padded to whole groups of 32, 48 or 64: the most of the three.
-static int64_t rows_padded(int64_t M) {
-    int64_t most = 0;
-    for (int mt = 2; mt <= 4; ++mt) {
-        const int64_t rows = (M + 16 * mt - 1) / (16 * mt) * (16 * mt);
-        if (rows > most) most = rows;
-    }
-    return most;
-}
-size_t rows_xt_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)K * 2; }
-size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)(K / kBlock) * 3; }  // 64 bytes per 32 rows, 128 per 48 or 64
-
-// When the streaming kernel takes a tensor's call.  Its time over 2 M N K grows about 1.4 times as fast
-// as the tiled kernel's (0.7 against 1.0 PFLOP/s once the chip is full), but it starts 10 to 15 us earlier
-// (no 128 x 256 tiles that leave the chip empty, no shares of K to write and add).  Measured here / there, us
-// (K x N): 8192x8192 M = 128 28 / 37, 256 49 / 51, 300 67 / 69; 11008x4096 M = 256 36 / 43, 500 63 / 63;
-// 28672x8192 M = 96 68 / 77, 128 79 / 78: the lines meet at about 36 GFLOP.  With short K the ends of the items count
-// as well, and they meet at fewer outputs: 4096x4096 M = 512 31 / 36, 768 44 / 47, 900 57 / 50; 4096x14336
-// M = 192 39 / 47, 256 50 / 47; 2048x2048 M = 1024 23 / 34, 1536 36 / 34: 3.4 million.  A rule on the
-// sizes of one tensor: a grouped call computes every tensor as a call of its own does.
-bool rows_path(int64_t M, int64_t N, int64_t K) {
-    if (M <= kGemvMaxM || K > kRowsMaxK || M > kRowsMaxM) return false;
-    if (M > 64 && ((double)M * (double)N * (double)K > 18e9 || (double)M * (double)N > 3.4e6)) return false;
-    // the padded rows must not take a call over a scratch limit that the tiled path keeps
-    return rows_xt_bytes(M, K) + rows_x0_bytes(M, K) <= (32u << 20);
-}
-
 int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, _Float16* Xt, _Float16* X0, int y_f16,
                 uint32_t* flags, hipStream_t stream) {
     if (count < 1 || count > kGemvMaxGroup || M < 1 || M > kRowsMaxM || K > kRowsMaxK) return -2;
@@ -373,23 +345,9 @@ int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
     a.Xt = Xt; a.X0 = X0; a.flags = flags; a.KB = (int)(K / kBlock); a.M = (int)M; a.y_f16 = y_f16;
     const int64_t nt_total = fill_tensors(a.t, w, count);
     if (nt_total < 0) return -2;
-    // Rows per group (16 mt) and row tiles per item (rt): the pair that takes the least time in rounds of one workgroup per compute unit (eight wavefronts of up to 256
-    // registers).  An item costs per block of its wavefronts 23 for a row tile and 56 for 16 activation rows
-    // (their fragments' way through the L1), then 60 per row tile and 100 for its end: fitted to launches
-    // with every rt and mt (11008x4096, one round: 16.9 / 18.9 / 21.3 / 24.2 us for rt = 1..4 with mt = 2,
-    // 23.8 us for rt = 1, mt = 4).
     const int cus = cu_count();
-    const int64_t steps = (a.KB + kRowsWaves - 1) / kRowsWaves;
-    int mt = 2, rt = 1;
-    int64_t best = INT64_MAX;
-    for (int m = 2; m <= 4; ++m) {
-        const int64_t n_groups = (M + 16 * m - 1) / (16 * m);
-        for (int r = 1; r <= kRowsMaxRT; ++r) {
-            const int64_t n_items = (nt_total + r - 1) / r * n_groups;
-            const int64_t cost = (n_items + cus - 1) / cus * (steps * (23 * r + 56 * m) + 60 * r + 100);
-            if (cost < best) { best = cost; mt = m; rt = r; }
-        }
-    }
+    const RowsSplit split = rows_split(nt_total, M, K, cus);
+    const int mt = split.mt, rt = split.rt;
     const int groups = (int)((M + 16 * mt - 1) / (16 * mt));
     a.m_groups = groups;
     const int64_t row_groups = (nt_total + rt - 1) / rt;

@@ -1,0 +1,78 @@
+// Host side of the streaming kernel for many rows (itq3s_rows.hip): how a launch is divided, what scratch it
+// takes, and which calls are its.  Plain C++, no HIP.
+#pragma once
+#include <cstddef>
+#include <cstdint>
+
+namespace itq3s {
+
+constexpr int64_t kRowsMinM = 17;  // fewer rows: the streaming kernel of itq3s_gemv.hip
+constexpr int64_t kRowsMaxM = 1 << 16;
+constexpr int64_t kRowsMaxK = 1 << 18;
+constexpr int kRowsWaves = 8;  // wavefronts per workgroup
+constexpr int kRowsMaxRT = 4;  // row tiles per item, at most (256 registers with 64 rows)
+
+// Rows per group (16 mt) and row tiles per item (rt): the pair that takes the least time in rounds of one
+// workgroup per compute unit (eight wavefronts of up to 256 registers).  An item costs per block of its
+// wavefronts 23 for a row tile and 56 for 16 activation rows (their fragments' way through the L1), then 60 per
+// row tile and 100 for its end: fitted to launches with every rt and mt (11008x4096, one round: 16.9 / 18.9 / 21.3 /
+// 24.2 us for rt = 1..4 with mt = 2, 23.8 us for rt = 1, mt = 4).
+struct RowsSplit {
+    int mt, rt;
+    int64_t items, rounds, cost;
+};
+inline RowsSplit rows_split(int64_t row_tiles, int64_t M, int64_t K, int units) {
+    const int64_t steps = (K / 256 + kRowsWaves - 1) / kRowsWaves;
+    RowsSplit best{2, 1, 0, 0, INT64_MAX};
+    for (int m = 2; m <= 4; ++m) {
+        const int64_t groups = (M + 16 * m - 1) / (16 * m);
+        for (int r = 1; r <= kRowsMaxRT; ++r) {
+            const int64_t items = (row_tiles + r - 1) / r * groups, rounds = (items + units - 1) / units;
+            const int64_t cost = rounds * (steps * (23 * r + 56 * m) + 60 * r + 100);
+            if (cost < best.cost) best = RowsSplit{m, r, items, rounds, cost};
+        }
+    }
+    return best;
+}
+
+// Activation rows padded to whole groups of 32, 48 or 64: the most of the three.
+inline int64_t rows_padded(int64_t M) {
+    int64_t most = 0;
+    for (int mt = 2; mt <= 4; ++mt) {
+        const int64_t rows = (M + 16 * mt - 1) / (16 * mt) * (16 * mt);
+        if (rows > most) most = rows;
+    }
+    return most;
+}
+inline size_t rows_xt_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)K * 2; }
+inline size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)(K / 256) * 3; }  // 64 bytes per 32 rows, 128 per 48 or 64
+
+// When this kernel takes a tensor's call.  Its time over 2 M N K grows faster than the tiled kernel's (0.7 against
+// 1.0 PFLOP/s once the chip is full), but it starts 10 to 15 us earlier (no 128 x 256 tiles that leave the chip
+// empty, no shares of K to write and add).  Beyond 64 rows it is asked up to 36 GFLOP and 3.4 million
+// outputs, a line between sizes like these (us here / there, K x N): 11008x4096 M = 256 36 / 43, 500 63 / 63;
+// 8192x8192 M = 256 49 / 51; 4096x4096 M = 900 57 / 50.  It is no exact one: 28672x8192 M = 96 68 / 77 lies beyond.
+// Within, where the tiled kernel is the faster one all the same:
+//  - short K: the ends of the items count, so a launch of more than so much cost (rows_split) loses.  K = 256:
+//    cost 1719 16.3 / 16.6, 2400 20.2 / 16.1 (N = 28672, M = 65); K = 512: 2400 20.7 / 19.7, 2624 23.8 / 20.8; K = 1024:
+//    2624 34.0 / 31.1 (it wins elsewhere: 0.84 to 0.99), 3280 a tenth slower; up to 64 rows, where the
+//    other kernel's tiles are half empty, 4800 39.7 / 40.5, 5248 48.5 / 41.5 (N = 128256, M = 56).
+//  - more than 1024 rows: a second round reads the rotated activations through every chiplet's L2 again, which
+//    does not hold them.  N = 1000, K = 4096: M = 1024 (one round) 23 / 33, 2048 (two) 52 / 41; N = 1500, K = 2048,
+//    M = 2048 (three) 43.5 / 34.6, two rounds there 32 / 34.
+//  - 17 rows of a thin tensor with long K: two passes of the kernel for 16 rows, whose second rotates its one row
+//    in the kernel, are 4 to 10 % faster (N = 16, K = 28672 30.5 / 27.8).
+// A rule on the sizes of one tensor (counted for 256 units): a grouped call computes every tensor as a call
+// of its own does.
+inline bool rows_path(int64_t M, int64_t N, int64_t K) {
+    if (M < kRowsMinM || K > kRowsMaxK || M > kRowsMaxM) return false;
+    // the padded rows must not take a call over a scratch limit that the tiled path keeps
+    if (rows_xt_bytes(M, K) + rows_x0_bytes(M, K) > (32u << 20)) return false;
+    if (M <= 32) return M > 17 || N > 1024 || K < 20480;
+    if (M > 64 && ((double)M * (double)N * (double)K > 18e9 || (double)M * (double)N > 3.4e6)) return false;
+    const RowsSplit s = rows_split((N + 15) / 16, M, K, 256);
+    if (K < 2048) return s.cost <= (K <= 256 ? 1800 : K < 1024 ? 2400 : M > 64 ? 3000 : 4800);
+    return M <= 1024 || s.rounds <= (K == 2048 ? 2 : 1);
+}
+
+}  // namespace itq3s

@@ -205,3 +205,38 @@ def test_kernels_keep_their_registers(source):
     asm = subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
     kernels = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_private_segment_fixed_size (\d+)", asm, flags=re.S)
     assert kernels and [k for k in kernels if k[1] != "0"] == []
+
+
+# us a call (weights cycled through memory): M, N, K, the tiled kernel (17 rows: two passes of the kernel for 16
+# rows) before the many-row kernel was there, the same now, the many-row kernel
+ROUTES = [
+    (3200, 1000, 256, 22.4, 17.1, 25.2), (300, 11008, 256, 22.1, 17.1, 23.5), (65, 28672, 256, 18.4, 16.1, 20.2), (112, 28672, 256, 21.0, 16.7, 23.4),
+    (33, 57344, 256, 17.1, 16.5, 19.6), (64, 128256, 256, 24.0, 22.0, 41.7), (64, 57344, 512, 22.6, 20.9, 23.9), (33, 128256, 512, 28.5, 27.6, 36.4),
+    (56, 128256, 1024, 43.4, 41.5, 48.5), (4096, 600, 2048, 40.9, 35.8, 43.6), (3200, 1000, 2048, 40.2, 35.8, 50.9), (2048, 1500, 2048, 38.4, 34.6, 43.5),
+    (1500, 1000, 4096, 39.5, 35.9, 41.2), (2048, 1000, 4096, 44.6, 40.5, 52.1), (2048, 1500, 4096, 55.8, 51.8, 71.8), (1500, 2048, 4096, 53.5, 50.1, 58.7),
+    (1800, 600, 8192, 61.8, 52.6, 68.8), (1800, 1000, 8192, 71.3, 59.8, 83.8), (17, 16, 28672, 27.8, 26.7, 30.5), (17, 300, 28672, 32.4, 31.5, 33.8),
+    (33, 11008, 256, 16.1, 15.4, 8.4), (64, 20000, 256, 18.2, 15.8, 12.1), (384, 3072, 256, 21.4, 16.4, 12.0), (1024, 2048, 512, 25.0, 20.0, 16.0),
+    (64, 28672, 1024, 27.3, 25.6, 16.1), (512, 4096, 1024, 31.5, 26.6, 17.1), (1024, 2048, 2048, 36.5, 34.0, 24.4), (1024, 1000, 4096, 36.6, 33.5, 24.1),
+    (1024, 2048, 4096, 41.4, 38.6, 36.4), (300, 11008, 4096, 67.8, 62.4, 52.1), (64, 28672, 8192, 78.5, 80.3, 52.2), (64, 11008, 14336, 67.2, 63.0, 39.5),
+    (24, 4096, 28672, 44.7, 44.2, 35.4), (512, 600, 28672, 79.5, 73.5, 56.8), (1800, 16, 8192, 42.3, 36.0, 27.4), (6000, 128, 2048, 41.0, 34.5, 23.4),
+]
+
+
+def test_no_call_goes_to_the_slower_kernel(tmp_path):
+    """The many-row kernel takes a call only where it beats what computed it before, and wherever it
+    clearly does (sizes on both sides of each line of the rule, with the times that were measured)."""
+    from paper_2603_27914_amd import build
+
+    main = tmp_path / "rule.cpp"
+    main.write_text(
+        '#include "itq3s_rows_rule.h"\n#include <cstdio>\n'
+        "int main() { long long M, N, K;\n"
+        '    while (std::scanf("%lld %lld %lld", &M, &N, &K) == 3) std::printf("%d ", (int)itq3s::rows_path(M, N, K)); }\n'
+    )
+    exe = tmp_path / "rule"
+    subprocess.run(["g++", "-std=c++17", "-I", build.CSRC, str(main), "-o", str(exe)], check=True)
+    sizes = "".join("%d %d %d\n" % r[:3] for r in ROUTES)
+    taken = [int(v) for v in subprocess.run([str(exe)], input=sizes, check=True, stdout=subprocess.PIPE, text=True).stdout.split()]
+    for (M, N, K, before, other, rows), many in zip(ROUTES, taken):
+        chosen = rows if many else other
+        assert chosen <= before * 1.03 and chosen <= 1.05 * min(rows, other), (M, N, K, many)
