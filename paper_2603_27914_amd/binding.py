@@ -116,9 +116,12 @@ def _check(status):
         raise Itq3sError("libitq3s: %s (status %d)" % (lib().itq3s_strerror(status).decode(), status))
 
 
+# (a torch without device support has neither: only calls fail there, for want of a device tensor)
+_raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    # (looked up per call: a torch without device support has neither, and this module still imports there)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_device())
 
 
 def _ptr(t):
