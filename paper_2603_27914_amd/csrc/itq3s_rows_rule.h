@@ -58,10 +58,10 @@ inline size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M
 //    2624 34.0 / 31.1 (it wins elsewhere: 0.84 to 0.99), 3280 a tenth slower; up to 64 rows, where the
 //    other kernel's tiles are half empty, 4800 39.7 / 40.5, 5248 48.5 / 41.5 (N = 128256, M = 56).
 //  - more than 1280 rows: every round more reads the rotated activations through every chiplet's L2 again, which
-//    does not hold them.  N = 1000, K = 4096: M = 1024 (one round) 24 / 34, 2048 (two) 52 / 41; N = 1500, K = 2048,
-//    M = 2048 (three) 43.5 / 34.6, two rounds there (N = 1000) 32.9 / 33.2.  Two rounds of few outputs stay up to
-//    K = 8192: they win where thin tensors share a launch that the other kernel would split K for one by one
-//    (three of 79 to 632 columns, K = 4864, M = 1696 67 / 92; one of 600, K = 4096, M = 2048 39 / 37).
+//    does not hold them.  N = 1000, K = 4096: M = 1024 (one round) 24 / 34, 1500 (two) 41 / 36, 2048 (two) 52 / 41;
+//    N = 766, K = 6912, M = 1532 (two) 59 / 44; K = 2048: N = 1000, M = 2048 (two) 32.9 / 33.2, N = 1500, M = 2048
+//    (three) 43.5 / 34.6.  (Thin tensors of a group lose by it: they would share one launch here, there each
+//    splits K for itself: M = 1696, 632 + 632 + 79 columns, K = 4864 67 / 92.)
 //  - 17 rows of a thin tensor with long K: two passes of the kernel for 16 rows, whose second rotates its one row
 //    in the kernel, are 4 to 10 % faster (N = 16, K = 28672 30.5 / 27.8).
 // A rule on the sizes of one tensor (counted for 256 units): a grouped call computes every tensor as a call
@@ -74,7 +74,7 @@ inline bool rows_path(int64_t M, int64_t N, int64_t K) {
     if (M > 64 && ((double)M * (double)N * (double)K > 18e9 || (double)M * (double)N > 3.4e6)) return false;
     const RowsSplit s = rows_split((N + 15) / 16, M, K, 256);
     if (K < 2048) return s.cost <= (K <= 256 ? 1800 : K < 1024 ? 2400 : M > 64 ? 3000 : 4800);
-    return M <= 1280 || s.rounds <= (K < 4096 || (K < 8192 && M * N <= 1250000) ? 2 : 1);
+    return M <= 1280 || s.rounds <= (K < 4096 ? 2 : 1);
 }
 
 }  // namespace itq3s

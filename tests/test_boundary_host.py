@@ -219,6 +219,7 @@ ROUTES = [
     (64, 28672, 1024, 27.3, 25.6, 16.1), (512, 4096, 1024, 31.5, 26.6, 17.1), (1024, 2048, 2048, 36.5, 34.0, 24.4), (1024, 1000, 4096, 36.6, 33.5, 24.1),
     (1024, 2048, 4096, 41.4, 38.6, 36.4), (300, 11008, 4096, 67.8, 62.4, 52.1), (64, 28672, 8192, 78.5, 80.3, 52.2), (64, 11008, 14336, 67.2, 63.0, 39.5),
     (24, 4096, 28672, 44.7, 44.2, 35.4), (512, 600, 28672, 79.5, 73.5, 56.8), (1800, 16, 8192, 42.3, 36.0, 27.4), (6000, 128, 2048, 41.0, 34.5, 23.4),
+    (1200, 2048, 2048, 37.0, 34.3, 31.9), (1800, 1000, 2048, 37.2, 33.6, 30.8), (4096, 300, 2048, 39.7, 33.8, 33.2), (2600, 600, 4096, 46.3, 41.6, 47.5),
 ]
 
 
