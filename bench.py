@@ -281,7 +281,7 @@ def main():
     if "prefill" in legs:
         out["prefill"] = prefill_leg(torch, binding, synth, gen, [int(m) for m in args.prefill_m.split(",")])
         best = max((r for r in out["prefill"] if r["M"] == max(x["M"] for x in out["prefill"])), key=lambda r: r["kernel_TFLOPs"])
-        out["roofline_gemm"] = {"bound": "mfma", "kernel": "gemm_kernel (itq3s_matmul, M>16 path)", "achieved": best["kernel_TFLOPs"], "peak": MFMA_F16_PEAK_TFLOPS,
+        out["roofline_gemm"] = {"bound": "mfma", "kernel": "gemm_kernel (itq3s_matmul, tiled path)", "achieved": best["kernel_TFLOPs"], "peak": MFMA_F16_PEAK_TFLOPS,
                                 "unit": "TFLOP/s", "frac": round(best["kernel_TFLOPs"] / MFMA_F16_PEAK_TFLOPS, 4),
                                 "workload": "X fp16 [%d, %d] x ITQ3_S W %dx%d, fp16 out" % (best["M"], best["K"], best["N"], best["K"]),
                                 "whole_call_TFLOPs": best["TFLOPs"], "whole_call_frac": best["frac_of_mfma_peak"]}

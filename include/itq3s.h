@@ -101,9 +101,10 @@ int itq3s_dequantize(const uint32_t *codes, const uint32_t *scales, int64_t N, i
 
 /* Fused matmul (problem statement of Alg. 2; Sec. 5.4 for M = 1):  Y[m][n] = sum_k X[m][k] w_hat[n][k].
  * No dequantized weight is written to memory.  M <= 16 takes the bandwidth-bound streaming path; more
- * rows a second streaming kernel as long as 2 M N K stays below about 36 GFLOP and M N below 3.4 million
- * (any N for M <= 64) and the rotated activations (rows rounded up to groups of 32 to 64) below 32 MB;
- * larger calls the tiled MFMA path (M <= 32 with more rotated activations: two passes of the first).
+ * rows a second streaming kernel up to the sizes where the tiled MFMA path is the faster one (from 65 rows
+ * on at the latest at 2 M N K = 36 GFLOP or M N = 3.4 million) and where the rotated activations (rows
+ * rounded up to groups of 32 to 64) take up to 32 MB; larger calls the tiled MFMA path (M <= 32: two passes
+ * of the first).  Which path is a function of the three sizes (and of the room, see above).
  * M > 16 accepts K <= 4194304 only (ITQ3S_ERR_SHAPE beyond), M <= 16 K <= 2^28.  fp32 accumulation in
  * all, the zero-point terms included: an output element is rounded once.
  * Activation range.  Every 256-channel chunk x of a row of X is replaced by x~ = H x, rounded to
@@ -140,8 +141,8 @@ int itq3s_matmul_static(const uint32_t *codes, const uint32_t *scales, int64_t N
  * for t = 0..count-1 (1 <= count <= ITQ3S_MAX_GROUP), e.g. the query/key/value projections of a layer,
  * or gate and up.  All tensors that a streaming kernel takes (itq3s_matmul) are served by a single launch, so the
  * launch latency and the ramp of the memory pipeline are paid once; for the others the activations
- * are rotated once and one tiled launch per tensor follows.  Results are identical to count calls of
- * itq3s_matmul.
+ * are rotated once, one tiled launch for all that do not split K follows, and for each that does a launch
+ * for its shares and one that adds them.  Results are identical to count calls of itq3s_matmul.
  *   w  [in] HOST array of count descriptors (read during the call, not kept): device pointers codes,
  *           scales (as for itq3s_matmul), rows N, output Y (M x N of y_dtype, row stride ldy >= N)
  *   X, M, ldx, y_dtype, status_flags, stream: as for itq3s_matmul

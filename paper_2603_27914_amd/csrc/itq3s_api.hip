@@ -47,7 +47,7 @@ struct WorkspacePlan {
 };
 
 // N = the largest tensor of the call (sizes the split-K shares of the tiled path)
-constexpr int64_t kChunkedMaxM = 2 * itq3s::kGemvMaxM;  // up to here M > 16 runs as passes of the streaming kernel
+constexpr int64_t kChunkedMaxM = 2 * itq3s::kGemvMaxM;  // up to here M > 16 runs as two passes of the streaming kernel where the one for many rows does not take it
 constexpr int64_t kSubStreamingMaxM = 64;               // sub-block variant: up to here passes of four rows, the tiled weight-side kernel above
 
 // (of the routes that every call can take; the many-row kernel's own need: rows_workspace)
@@ -197,8 +197,9 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
         }
     }
     if (M > itq3s::kGemvMaxM && M <= kChunkedMaxM) {
-        // A few rows more than the streaming kernel takes at once: two passes of it over the weights
-        // are still faster than the tiled kernel, whose 128-row tiles would be mostly empty.
+        // What the kernel for many rows left (more than 32 MB of rotated activations: K above about
+        // 250,000; 17 rows of thin tensors; less room): two passes of the kernel for 16 rows.  The tiled
+        // kernel's 128-row tiles would be mostly empty.
         const size_t y_bytes = y_dtype == ITQ3S_F16 ? 2 : 4;
         for (int64_t m0 = 0; m0 < M; m0 += itq3s::kGemvMaxM) {
             itq3s_weight part[ITQ3S_MAX_GROUP];

@@ -12,7 +12,8 @@ namespace itq3s {
 
 constexpr uint32_t kFlagNonFinite = 1u, kFlagScaleSat = 2u, kFlagZClamp = 4u, kFlagBadCode = 8u, kFlagActRange = 16u;
 
-// Streaming path handles up to this many activation rows; more rows go to the tiled MFMA path.
+// The streaming kernel of itq3s_gemv.hip handles up to this many activation rows; more go to that of
+// itq3s_rows.hip or to the tiled one.
 constexpr int kGemvMaxM = 16;
 // Up to this many rows the streaming kernel rotates the activations itself (one launch, no workspace).
 constexpr int kGemvFusedMaxM = 4;
@@ -75,7 +76,7 @@ int launch_gemv_rows(const GemvWeight* w, int count, int64_t K, const _Float16* 
 
 // The streaming kernel for more rows than launch_gemv_rows takes (rows_path() says for which calls):
 // rotates the activations into Xt (rows_xt_bytes) and X0 (rows_x0_bytes), both 256-byte aligned, then one
-// launch over all row tiles and groups of up to 64 rows.
+// launch over all row tiles and groups of up to 64 rows (itq3s_rows_rule.h).
 int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, _Float16* Xt, _Float16* X0, int y_f16,
                 uint32_t* flags, hipStream_t stream);
 // Rotated activations for it: groups x mt tiles of 16 rows, layout at rotate_rows_kernel.
@@ -92,11 +93,11 @@ inline bool raise_lds_limit(DeviceOnce& once, const void* kernel, int bytes) {
     return once(device, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; });
 }
 
-// Tiled matmul, M > 16.  Xt = rotated activations (launch_rotate_rowmajor); X, ldx = the activations
+// Tiled matmul for what the streaming kernels do not take.  Xt = rotated activations (launch_rotate_rowmajor); X, ldx = the activations
 // themselves (zero-point term).  Shapes with few output tiles split K over several workgroups per tile
-// and add the shares in a second launch (gemm_splits > 1); all others share one launch.  The former use `partial` (gemm_partial_bytes,
-// 16-byte aligned; partial_bytes = what is there -- too little, or none, means no split) and
-// `zflags` (kGemmFlagWords words, all zero at launch).
+// and add the shares in a second launch (gemm_splits > 1); all others share one launch.  The former use
+// `partial` (gemm_partial_bytes, 16-byte aligned; partial_bytes = what is there -- too little, or none,
+// means no split) and `zflags` (kGemmFlagWords words, all zero at launch).
 constexpr int kGemmMaxSplits = 8;
 constexpr int kGemmSplitMaxTiles = 128;  // more tiles than this: no split
 constexpr int kGemmFlagWords = 128;

@@ -20,6 +20,7 @@
 // large as the registers allow -- a fragment fetched serves RT tiles -- but no larger than keeps every unit
 // busy, and K is shared out inside the workgroup.  The tiled kernel at these sizes has its 128 x 256 tiles
 // partly empty and leaves most units idle, or splits K and pays the shares' way through memory.
+// Which calls it takes and how a launch is divided: itq3s_rows_rule.h.
 // Measured, whole call with the rotation launch, before (two passes of the kernel for 16 rows up to 32,
 // tiled kernel above) / now, us (K x N): 4096x4096 M = 32 14.3 / 9.2, M = 48 30 / 10.8, M = 512 38 / 31; three such
 // tensors in one group M = 48 86 / 15; two of 4096x11008 M = 48 66 / 23; 11008x4096 M = 48 40 / 18.9;

@@ -243,7 +243,7 @@ def check_elements(Y, want, codes, scales, N, K, X, out_f16=False):
     assert worst <= 1.0, "an element misses its bound by a factor %.2f" % worst
 
 
-@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 11, 16, 17, 25, 32])  # 17..32: two passes of the streaming kernel
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 11, 16, 17, 25, 32])  # 17..32: the many-row kernel, or two passes of the other (17 rows, long K)
 @pytest.mark.parametrize("N,K", [(16, 256), (48, 512), (1000, 1024), (2048, 2048), (1160, 4096), (272, 11008), (100, 20480), (40, 36864)])
 def test_matmul_small_m(gpu, ref, M, N, K):
     torch, binding = gpu
@@ -334,7 +334,7 @@ GROUPS = [
     (11008, [4096, 40], (1, 3)),                 # long K (rotation launch for M = 3), a tensor with 3 row tiles
     (512, [16, 1000, 17, 300], (1, 5)),          # four ragged tensors, one with a single row tile
     (1024, [200, 48], (33,)),                    # tiled path
-    (2048, [300, 48, 1000], (20, 32, 300)),      # two passes of the streaming kernel; tiled path with split K and without
+    (2048, [300, 48, 1000], (20, 32, 300)),      # the many-row kernel
     (8192, [12304, 12304], (1,)),                # many row tiles per compute unit, the launch shape of 70B gate / up
     (8192, [8192, 1024, 1024], (1,)),            # the q + k + v launch of the 70B step, as the benchmark launches it
     (8192, [28672, 28672], (1,)),                # its gate + up launch
@@ -459,7 +459,7 @@ def test_matmul_activation_magnitudes(gpu, ref, scale):
         assert rel_rows(got, want) <= MATMUL_TOL
 
 
-@pytest.mark.parametrize("M", [1, 3, 8, 16, 40])  # in-kernel rotation, rotation launch + streaming kernel, tiled path
+@pytest.mark.parametrize("M", [1, 3, 8, 16, 40])  # in-kernel rotation, rotation launch + streaming kernel, many-row kernel (tiled: test_gpu_tiled.py)
 def test_matmul_activation_range_edge_and_flag(gpu, ref, M):
     """The stated activation domain (max|x| <= 16376 and |H x| <= 65504 per 256-channel chunk): at
     its edge the product is finite and matches the oracle with the flag clear; beyond it the library
@@ -506,9 +506,10 @@ def test_matmul_activation_range_edge_and_flag(gpu, ref, M):
 
 
 def test_matmul_grouped_tiled_path_splits_by_shape_only(gpu, ref):
-    """M > 16 with one tensor above 128 output tiles (never split) and one far below (split over K)
-    in the same group: each gets exactly what a single call gives it (bit for bit), whatever the
-    other tensors are, and a workspace that is too small for the tensor that splits is refused."""
+    """M > 16 with one tensor above 128 output tiles of the tiled kernel and one far below, whose room covers
+    shares of K: both go to the many-row kernel, each gets exactly what a single call gives it (bit for
+    bit), and a workspace without the second one's shares is refused.  (Groups that reach the tiled kernel:
+    test_gpu_tiled.py.)"""
     torch, binding = gpu
     K, M = 2048, 300
     Ns = [11008, 600]  # 3 x 43 = 129 tiles; 3 x 3 = 9 tiles
@@ -566,8 +567,8 @@ def test_matmul_fp16_output_with_zero_points_in_most_blocks(gpu, ref, M, N, K):
 
 
 def test_calls_captured_in_a_graph_replay_like_eager(gpu, ref):
-    """Every entry point, on every path of the matmul (in-kernel rotation, rotation launch, two passes,
-    tiled with and without split-K, grouped), captured once into a HIP graph; between replays the outputs
+    """Every entry point, on the streaming paths of the matmul (in-kernel rotation, rotation launch, many
+    rows, grouped; the tiled path: test_gpu_tiled.py), captured once into a HIP graph; between replays the outputs
     and the workspace are overwritten with garbage and eager work runs; every replay must reproduce the
     eager results bit for bit (nothing may depend on state a previous replay left behind)."""
     torch, binding = gpu
@@ -619,7 +620,8 @@ def test_calls_captured_in_a_graph_replay_like_eager(gpu, ref):
 
 def test_matmul_from_two_host_threads(gpu, ref):
     """Two host threads call the library at the same time, each with its own workspace and outputs
-    (streaming, two-pass and tiled shapes, one thread through the timed entry point): every result
+    (streaming and many-row shapes, one thread through the timed entry point; tiled ones:
+    test_gpu_tiled.py): every result
     equals the one computed alone, bit for bit."""
     import threading
 
@@ -663,7 +665,7 @@ def test_matmul_from_two_host_threads(gpu, ref):
 
 @pytest.mark.parametrize("M,N,K", [(40, 300, 4096), (512, 384, 4096), (200, 1000, 8192), (300, 256, 2048), (1024, 512, 2048)])
 def test_matmul_few_tiles_long_k(gpu, ref, M, N, K):
-    """Few output tiles and a long K.  The workspace arrives full of garbage, is used three times in a
+    """Few output tiles and a long K (all on the many-row kernel).  The workspace arrives full of garbage, is used three times in a
     row without clearing, and every result equals the first bit for bit and the oracle within
     tolerance; one block in a hundred has a zero-point."""
     torch, binding = gpu
@@ -684,8 +686,8 @@ def test_matmul_few_tiles_long_k(gpu, ref, M, N, K):
 
 
 def test_matmul_tiled_shapes_share_a_workspace(gpu, ref):
-    """Tiled-path shapes with different tile counts follow each other on the same workspace with no
-    host synchronisation in between."""
+    """Shapes with different tile counts follow each other on the same workspace with no host synchronisation
+    in between (the many-row kernel's; the tiled one's: test_gpu_tiled.py)."""
     torch, binding = gpu
     cases = [(512, 384, 4096), (64, 2048, 1024), (300, 256, 2048), (17, 4096, 4096), (1024, 512, 2048), (512, 384, 4096)]
     packed, xs = [], []

@@ -1,4 +1,5 @@
-"""Seeded random shapes through every matmul path, checked on the device against a second route:
+"""Seeded random shapes through the matmul paths (three of them through the tiled kernel, which has its own
+in test_gpu_tiled.py), checked on the device against a second route:
 itq3s_dequantize (itself held to the oracle within 1e-6 elsewhere) followed by a dense fp64 product.
 Cheap enough to visit hundreds of (M, N, K, dtype, zero-point pattern) combinations that the
 oracle-based tests cannot afford; the bar is the same per-row relative L2."""

@@ -1,8 +1,8 @@
 """itq3s_matmul_static (scratch in the library's static device array, nothing allocated) against
 itq3s_matmul with a caller-provided workspace: same kernels, so the outputs are bit-identical.  Two
 calls in a row on the shared array, the second with a smaller input; paths that use the scratch
-(5..16 rows: rotated activations; more rows: rotated activations, split-K shares and their flags)
-and the one that does not (M <= 4)."""
+(5..16 rows and the many-row path: rotated activations) and the one that does not (M <= 4).  The tiled
+path with its shares and flags: test_gpu_tiled.py."""
 import ctypes
 
 import numpy as np
@@ -39,9 +39,9 @@ def static_call(torch, binding, cd, sd, N, K, X, out):
     return rc
 
 
-@pytest.mark.parametrize("first,second", [((300, 600, 2048), (40, 200, 1024)),   # tiled path with split-K shares, twice
+@pytest.mark.parametrize("first,second", [((300, 600, 2048), (40, 200, 1024)),   # many-row path, twice (its room also covers the tiled path's shares)
                                           ((16, 1000, 4096), (7, 333, 1024)),    # rotation launch + streaming kernel
-                                          ((512, 4096, 4096), (3, 96, 512)),     # large tiled call, then the path without scratch
+                                          ((512, 4096, 4096), (3, 96, 512)),     # a large many-row call, then the path without scratch
                                           ((64, 272, 11008), (9, 48, 768))])
 def test_static_scratch_matches_workspace_variant(gpu, ref, first, second):
     torch, binding = gpu
