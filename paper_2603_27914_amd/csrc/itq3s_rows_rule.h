@@ -72,9 +72,10 @@ inline bool rows_path(int64_t M, int64_t N, int64_t K) {
     if (rows_xt_bytes(M, K) + rows_x0_bytes(M, K) > (32u << 20)) return false;
     if (M <= 32) return M > 17 || N > 1024 || K < 20480;
     if (M > 64 && ((double)M * (double)N * (double)K > 18e9 || (double)M * (double)N > 3.4e6)) return false;
+    if (K >= 2048 && M <= 1280) return true;
     const RowsSplit s = rows_split((N + 15) / 16, M, K, 256);
     if (K < 2048) return s.cost <= (K <= 256 ? 1800 : K < 1024 ? 2400 : M > 64 ? 3000 : 4800);
-    return M <= 1280 || s.rounds <= (K < 4096 ? 2 : 1);
+    return s.rounds <= (K < 4096 ? 2 : 1);
 }
 
 }  // namespace itq3s
