@@ -71,13 +71,15 @@ size_t itq3s_scales_bytes(int64_t N, int64_t K);
 /* Bytes of scratch itq3s_matmul needs (Sec. 2.3: H is symmetric and its own inverse, so
  * <H v, x> = <v, H x>; the library rotates X once per call instead of every weight block).  Never 0.
  * M <= 4: 256 (the streaming kernel rotates inside the kernel; the workspace is not touched).
- * Larger M: room for the rotated activations (rows rounded up), grows with M*K; for M > 16 and shapes with
- * few output tiles (at most 128 tiles of 128 x 256) also the partial sums of the workgroups that share a
- * tile's K range (up to 8 x M x N x 4 bytes, tiles rounded up).  A function of the three sizes only, and
- * NOT monotone in M: a workspace for calls with several M needs the largest of their sizes.
- * It is the room for the fastest route.  For M > 16 a call still succeeds with less, as long as the activation
- * rows as they are fit (for M <= 32 those of a pass of 16) and the partial sums do: it then takes the tiled
- * path, for M <= 32 two passes of the streaming one, with results that differ in the last bits. */
+ * Larger M: room for the rotated activations (rows rounded up; on the block-scaled path 2.31 bytes an
+ * element), grows with M*K, and never less than what the call accepts (next sentence but one).  A function of
+ * the three sizes only, and NOT monotone in M: a workspace for calls with several M needs the largest of their sizes.
+ * It is the room for the fastest route.  For M > 16 a call still succeeds with less, as long as M*K fp16 values
+ * (rounded up to 256 bytes; for M <= 32 those of a pass of 16 rows), 768 bytes and, where there are at most 128 tiles
+ * of 128 x 256 outputs, 128 KB for each of them times min(256 / tiles, 8, K / 1024) if that is at least 2
+ * would fit.  (The last is more than any route takes today; it stays the line between accepted and refused.)
+ * A call with less room takes its rows in several turns, with the same bits, or a route that needs less, with
+ * results that differ in the last bits. */
 size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /* Offline quantization (Alg. 1, Def. 1).  Per block: w' = H w in fp64 (butterfly stages
@@ -101,14 +103,13 @@ int itq3s_dequantize(const uint32_t *codes, const uint32_t *scales, int64_t N, i
 
 /* Fused matmul (problem statement of Alg. 2; Sec. 5.4 for M = 1):  Y[m][n] = sum_k X[m][k] w_hat[n][k].
  * No dequantized weight is written to memory.  M <= 16 takes the bandwidth-bound streaming path; more
- * rows a second streaming kernel up to the sizes where the tiled MFMA path is the faster one (from 65 rows
- * on at the latest at 2 M N K = 36 GFLOP or M N = 3.4 million) and where the rotated activations (rows
- * rounded up to groups of 32 to 64) take up to 32 MB; larger calls the tiled MFMA path (M <= 32: two passes
- * of the first).  Which path is a function of the three sizes (and of the room, see above).
+ * rows a second streaming kernel up to the sizes where the block-scaled MFMA path (fp4 digits, activations in
+ * three fp6 parts) is the faster one: wide tensors from 18 rows on, everything from 480 rows on.
+ * Which path is a function of the three sizes (and of the room, see above).
  * M > 16 accepts K <= 4194304 only (ITQ3S_ERR_SHAPE beyond), M <= 16 K <= 2^28.  fp32 accumulation in
  * all, the zero-point terms included: an output element is rounded once.
  * Activation range.  Every 256-channel chunk x of a row of X is replaced by x~ = H x, rounded to
- * fp16, after an intermediate T = X_16x16 H_16 / 4 that is split into fp16 parts.  Both stay
+ * fp16 or, on the block-scaled path, to 2^-14 of the largest of 32 neighbours, after an intermediate T = X_16x16 H_16 / 4 that is split into fp16 parts.  Both stay
  * finite whenever  max|x| <= 16376  and  |(H x)_k| <= 65504  over the chunk (the second holds if
  * sum|x| <= 16 * 65504; any chunk with max|x| <= 4094 satisfies both).  Outside that range the
  * products that involve the chunk are Inf/NaN although the exact result is finite, and
@@ -128,8 +129,8 @@ int itq3s_matmul(const uint32_t *codes, const uint32_t *scales, int64_t N, int64
  * hipMalloc.  Same arguments, same kernels and bit-identical results; the scratch memory is a
  * library-owned static device array of ITQ3S_STATIC_SCRATCH_BYTES (every GPU the library runs on
  * holds one until the process ends), and the call allocates nothing.
- *   - returns ITQ3S_ERR_WORKSPACE without launching anything if
- *     itq3s_matmul_workspace_bytes(M, N, K) > ITQ3S_STATIC_SCRATCH_BYTES (M <= 4 always fits);
+ *   - returns ITQ3S_ERR_WORKSPACE without launching anything if the least room that itq3s_matmul
+ *     accepts (itq3s_matmul_workspace_bytes) exceeds ITQ3S_STATIC_SCRATCH_BYTES (M <= 4 always fits);
  *   - all calls on one GPU share that array, which keeps the last call's contents: calls that overlap
  *     in time on one GPU (two streams, two threads) race and must be ordered by the caller;
  *   - the first call on a device looks up the array's address (no allocation, no synchronisation). */
@@ -141,14 +142,14 @@ int itq3s_matmul_static(const uint32_t *codes, const uint32_t *scales, int64_t N
  * for t = 0..count-1 (1 <= count <= ITQ3S_MAX_GROUP), e.g. the query/key/value projections of a layer,
  * or gate and up.  All tensors that a streaming kernel takes (itq3s_matmul) are served by a single launch, so the
  * launch latency and the ramp of the memory pipeline are paid once; for the others the activations
- * are rotated once, one tiled launch for all that do not split K follows, and for each that does a launch
- * for its shares and one that adds them.  Results are identical to count calls of itq3s_matmul.
+ * are rotated once, and one launch follows for each kernel of the block-scaled path that the tensors take
+ * (K over eight or four wavefronts, tiled).  Results are identical to count calls of itq3s_matmul.
  *   w  [in] HOST array of count descriptors (read during the call, not kept): device pointers codes,
  *           scales (as for itq3s_matmul), rows N, output Y (M x N of y_dtype, row stride ldy >= N)
  *   X, M, ldx, y_dtype, status_flags, stream: as for itq3s_matmul
  *   workspace: at least the largest itq3s_matmul_workspace_bytes(M, N_t, K) over the tensors of the call
  *           (with that much, how a tensor is computed never depends on the room given; with less as described
- *           there, ITQ3S_ERR_WORKSPACE where the largest tensor's partial sums do not fit) */
+ *           there, ITQ3S_ERR_WORKSPACE below the least room of the tensor that needs most) */
 #define ITQ3S_MAX_GROUP 4
 typedef struct itq3s_weight {
     const uint32_t *codes;

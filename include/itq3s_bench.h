@@ -16,11 +16,10 @@ extern "C" {
 /* itq3s_matmul / itq3s_matmul_grouped with the same arguments, after which the call WAITS for the
  * work and stores in *kernel_ms (HOST pointer, required) the duration of the FIRST contraction launch
  * alone, taken from HIP events attached to its dispatch: not the activation-rotation launch in front of
- * it, not the launch that adds up partial sums behind it for shapes with few tiles, not launch gaps.
- * That launch is the whole contraction of a single tensor (except where M = 17..32 takes two passes: the
- * first pass), of a group with M <= 16, and of a group whose tensors all go the same way without splitting
- * K.  Of a group that mixes ways it is the streaming launch for many rows, else the tiled launch of the
- * tensors that do not split K, else that of the first tensor that does: not the group's time. */
+ * it, not launch gaps.  That launch is the whole contraction of a single tensor (except where M = 17..32
+ * takes two passes or a short workspace several turns: the first of them), of a group with M <= 16, and of a group
+ * whose tensors all go the same way.  Of a group that mixes ways it is the streaming launch for many rows,
+ * else the first of the block-scaled launches: not the group's time. */
 int itq3s_matmul_timed(const uint32_t *codes, const uint32_t *scales, int64_t N, int64_t K, const void *X, int64_t M,
                        int64_t ldx, void *Y, int y_dtype, int64_t ldy, void *workspace, size_t workspace_bytes,
                        uint32_t *status_flags, void *stream, float *kernel_ms);

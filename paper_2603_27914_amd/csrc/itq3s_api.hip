@@ -42,36 +42,78 @@ inline int pad_m(int64_t M) {
     return mp;
 }
 
-struct WorkspacePlan {
-    size_t xt_bytes, s_bytes, flag_bytes, partial_bytes, total;
-};
-
-// N = the largest tensor of the call (sizes the split-K shares of the tiled path)
-constexpr int64_t kChunkedMaxM = 2 * itq3s::kGemvMaxM;  // up to here M > 16 runs as two passes of the streaming kernel where the one for many rows does not take it
+constexpr int64_t kChunkedMaxM = 2 * itq3s::kGemvMaxM;  // up to here M > 16 may run as two passes of the streaming kernel
 constexpr int64_t kSubStreamingMaxM = 64;               // sub-block variant: up to here passes of four rows, the tiled weight-side kernel above
 
-// (of the routes that every call can take; the many-row kernel's own need: rows_workspace)
-WorkspacePlan plan_workspace(int64_t M, int64_t N, int64_t K) {
-    if (M > itq3s::kGemvMaxM && M <= kChunkedMaxM) return plan_workspace(itq3s::kGemvMaxM, N, K);
-    WorkspacePlan p;
-    if (M <= itq3s::kGemvFusedMaxM) {  // the streaming kernel rotates the activations itself: nothing to park
-        p.xt_bytes = p.s_bytes = p.flag_bytes = p.partial_bytes = 0;
-        p.total = 256;
-        return p;
-    }
-    const int64_t rows = M <= itq3s::kGemvMaxM ? pad_m(M) : M;
-    p.xt_bytes = round_up((size_t)rows * (size_t)K * 2, 256);
-    // streaming path with a rotation launch: two sums per (block, row), see launch_rotate_frag
-    p.s_bytes = M <= itq3s::kGemvMaxM ? round_up((size_t)rows * (size_t)(K / 256) * 8, 256) : 0;
-    // tiled path: split-K flags, then the shares (layout: rotated activations | flags | shares)
-    p.flag_bytes = M <= itq3s::kGemvMaxM ? 0 : 512;
-    p.partial_bytes = M <= itq3s::kGemvMaxM ? 0 : round_up(itq3s::gemm_partial_bytes(M, N, K), 256);
-    p.total = p.xt_bytes + p.s_bytes + p.flag_bytes + p.partial_bytes + 256;
-    return p;
+// The streaming kernel for up to 16 rows: what it takes in front of itself, see launch_rotate_frag.
+struct FragPlan {
+    size_t xt_bytes, total;  // rotated activations (then two sums per block and row); all of it
+};
+FragPlan plan_frag(int64_t M, int64_t K) {
+    if (M <= itq3s::kGemvFusedMaxM) return FragPlan{0, 256};  // it rotates the activations itself: nothing to park
+    const int64_t rows = pad_m(M);
+    const size_t xt = round_up((size_t)rows * (size_t)K * 2, 256);
+    return FragPlan{xt, xt + round_up((size_t)rows * (size_t)(K / 256) * 8, 256) + 256};
 }
 
-// Scratch of the streaming kernel for many rows: the same for every tensor of a call.
+// The least room that a call is accepted with (the largest over its tensors).  Above 32 rows it is what a kernel with
+// fp16 operands once needed, shares of K for few output tiles among it: callers have kept such sizes, and what was
+// refused stays refused.  Every such room holds a pass of 16 rows, at least.
+size_t least_workspace(int64_t M, int64_t N, int64_t K) {
+    if (M <= kChunkedMaxM) return plan_frag(M < itq3s::kGemvMaxM ? M : itq3s::kGemvMaxM, K).total;
+    const int64_t tiles = ((M + 127) / 128) * ((N + 255) / 256);
+    int64_t shares = 1;
+    if (tiles <= 128) {
+        shares = 256 / tiles;
+        if (K > 20480 || shares * tiles < 208) shares = 512 / tiles;
+        if (shares > 8) shares = 8;
+        if (shares > K / 1024) shares = K / 1024;
+    }
+    const size_t partial = shares > 1 ? (size_t)shares * (size_t)tiles * (128 * 256 * 4) : 0;
+    return round_up((size_t)M * (size_t)K * 2, 256) + 512 + partial + 256;
+}
+
+// Passes of the streaming kernel for 16 rows, two of them: where the many-row kernel's rule leaves a call of up to 32 rows
+// to them (17 rows of a thin tensor with long K, more than 32 MB of rotated activations: K above 250,000).  Three: where
+// 32 rows of the block-scaled operand would not fit the static scratch that such a call has always fitted.
+inline bool passes_of_16(int64_t M, int64_t N, int64_t K) {
+    return M <= kChunkedMaxM ? !itq3s::rows_path(M, N, K) : M < 38 && itq3s::mx_bytes(1, K) > (size_t)ITQ3S_STATIC_SCRATCH_BYTES;
+}
+
+// Scratch of the kernels for more rows, the same for every tensor of a call: the many-row kernel, the block-scaled ones.
 size_t rows_workspace(int64_t M, int64_t K) { return round_up(itq3s::rows_xt_bytes(M, K), 256) + round_up(itq3s::rows_x0_bytes(M, K), 256); }
+size_t mx_workspace(int64_t M, int64_t K) { return itq3s::mx_sample_bytes(M, K) + itq3s::mx_bytes(M, K); }
+
+// The block-scaled kernels over the tensors that each of them takes, in as many slabs of rows as the room asks for (a
+// row's results do not depend on the others).  The room holds 32 rows.
+int launch_mx_routes(const itq3s_weight* w, const itq3s::Route* route, int count, int64_t K, const _Float16* X, int64_t M, int64_t ldx, int y_f16,
+                     unsigned char* base, size_t room, uint32_t* flags, hipStream_t st) {
+    int64_t slab = M;
+    unsigned char* Xm = base + itq3s::mx_sample_bytes(M, K);
+    _Float16* sample = itq3s::mx_sample_bytes(M, K) > 0 ? reinterpret_cast<_Float16*>(base) : nullptr;
+    if (room < mx_workspace(M, K)) {
+        const int64_t most = (int64_t)(room / itq3s::mx_bytes(1, K)) * itq3s::kMxRows, slabs = (M + most - 1) / most;
+        slab = ((M + slabs - 1) / slabs + itq3s::kMxRows - 1) / itq3s::kMxRows * itq3s::kMxRows;
+        Xm = base;
+        sample = nullptr;
+    }
+    const size_t y_bytes = y_f16 ? 2 : 4;
+    for (int64_t m0 = 0; m0 < M; m0 += slab) {
+        const int64_t rows = M - m0 < slab ? M - m0 : slab;
+        int rc = itq3s::launch_rotate_mx(X + m0 * ldx, rows, K, ldx, Xm, sample, flags, st);
+        for (const itq3s::Route r : {itq3s::Route::shares8, itq3s::Route::shares4, itq3s::Route::tiled}) {
+            itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
+            int n = 0;
+            for (int i = 0; i < count; ++i)
+                if (route[i] == r) gw[n++] = itq3s::GemvWeight{w[i].codes, w[i].scales, w[i].N, static_cast<unsigned char*>(w[i].Y) + (size_t)m0 * (size_t)w[i].ldy * y_bytes, w[i].ldy};
+            if (rc != 0 || n == 0) continue;
+            if (r == itq3s::Route::tiled) rc = itq3s::launch_gemm(gw, n, K, rows, Xm, y_f16, flags, st);
+            else rc = itq3s::launch_mx_shares(gw, n, K, rows, Xm, r == itq3s::Route::shares8 ? 8 : 4, y_f16, flags, st);
+        }
+        if (rc != 0) return rc;
+    }
+    return 0;
+}
 
 }  // namespace
 
@@ -112,10 +154,11 @@ size_t itq3s_scales_bytes(int64_t N, int64_t K) {
 
 size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0 || K % 256 != 0) return 256;
-    // room for the fastest route and for the one that a call with less room falls back to
-    const size_t rows = itq3s::rows_path(M, N, K) ? rows_workspace(M, K) : 0;
-    const size_t other = plan_workspace(M, N, K).total;
-    return rows > other ? rows : other;
+    // room for the kernel that computes the call, and for those that one with less room falls back to
+    const size_t least = least_workspace(M, N, K);
+    if (M <= itq3s::kGemvMaxM || passes_of_16(M, N, K)) return least;
+    const size_t want = itq3s::many_row_route(M, N, K) == itq3s::Route::rows ? rows_workspace(M, K) : mx_workspace(M, K);
+    return want > least ? want : least;
 }
 
 int itq3s_quantize(const float* W, int64_t N, int64_t K, int64_t ldw, uint32_t* codes, uint32_t* scales, uint32_t* status_flags,
@@ -166,7 +209,7 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
         if (!w[i].codes || !w[i].scales || !w[i].Y) return ITQ3S_ERR_NULL;
         if (w[i].N <= 0 || w[i].ldy < w[i].N || (w[i].N + 15) / 16 > 0x7fffffffLL / (K / 256)) return ITQ3S_ERR_SHAPE;
         if (!aligned(w[i].codes, 16) || !aligned(w[i].scales, 16) || !aligned(w[i].Y, y_dtype == ITQ3S_F16 ? 2 : 4)) return ITQ3S_ERR_ALIGN;
-        const size_t need_i = plan_workspace(M, w[i].N, K).total;
+        const size_t need_i = least_workspace(M, w[i].N, K);
         if (need_i > need) need = need_i;
     }
     if (!aligned(X, 16) || ldx % 8 != 0 || (status_flags && !aligned(status_flags, 4))) return ITQ3S_ERR_ALIGN;
@@ -174,73 +217,65 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
     if (!aligned(workspace, 256)) return ITQ3S_ERR_ALIGN;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Tensors that the streaming kernel for many rows takes go first, in one launch; what is left is
-    // computed as if it were a call of its own (its scratch lies over theirs: same stream, one after the other).
-    // That kernel pads the activation rows, up to four times as many at M = 17: room that a call sized for the
-    // other routes, or for another M, may not have.  Such a call takes those routes.
-    itq3s_weight rest[ITQ3S_MAX_GROUP];
-    if (M > itq3s::kGemvMaxM && workspace_bytes >= rows_workspace(M, K)) {
-        itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
-        int n_rows = 0, n_rest = 0;
-        for (int i = 0; i < count; ++i) {
-            if (itq3s::rows_path(M, w[i].N, K)) gw[n_rows++] = itq3s::GemvWeight{w[i].codes, w[i].scales, w[i].N, w[i].Y, w[i].ldy};
-            else rest[n_rest++] = w[i];
-        }
-        if (n_rows > 0) {
-            unsigned char* const base = static_cast<unsigned char*>(workspace);
-            const int rc = itq3s::launch_rows(gw, n_rows, K, static_cast<const _Float16*>(X), ldx, M, reinterpret_cast<_Float16*>(base),
-                                              reinterpret_cast<_Float16*>(base + round_up(itq3s::rows_xt_bytes(M, K), 256)),
-                                              y_dtype == ITQ3S_F16, status_flags, st);
-            if (rc != 0 || n_rest == 0) return rc;
-            w = rest;
-            count = n_rest;
-        }
-    }
-    if (M > itq3s::kGemvMaxM && M <= kChunkedMaxM) {
-        // What the kernel for many rows left (more than 32 MB of rotated activations: K above about
-        // 250,000; 17 rows of thin tensors; less room): two passes of the kernel for 16 rows.  The tiled
-        // kernel's 128-row tiles would be mostly empty.
-        const size_t y_bytes = y_dtype == ITQ3S_F16 ? 2 : 4;
-        for (int64_t m0 = 0; m0 < M; m0 += itq3s::kGemvMaxM) {
-            itq3s_weight part[ITQ3S_MAX_GROUP];
-            for (int i = 0; i < count; ++i) {
-                part[i] = w[i];
-                part[i].Y = static_cast<unsigned char*>(w[i].Y) + (size_t)m0 * (size_t)w[i].ldy * y_bytes;
-            }
-            const int64_t rows = M - m0 < itq3s::kGemvMaxM ? M - m0 : itq3s::kGemvMaxM;
-            const int rc = itq3s_matmul_grouped(part, count, K, static_cast<const _Float16*>(X) + m0 * ldx, rows, ldx, y_dtype, workspace,
-                                                workspace_bytes, status_flags, stream);
-            if (rc != 0) return rc;
-        }
-        return ITQ3S_OK;
-    }
-    const WorkspacePlan p = plan_workspace(M, w[0].N, K);  // (the parts in front of the split-K shares do not depend on N)
-    _Float16* Xt = static_cast<_Float16*>(workspace);
-    const _Float16* Xh = static_cast<const _Float16*>(X);
+    const _Float16* const Xh = static_cast<const _Float16*>(X);
     const int y_f16 = y_dtype == ITQ3S_F16;
+    unsigned char* const base = static_cast<unsigned char*>(workspace);
     if (M <= itq3s::kGemvMaxM) {
         itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
         for (int i = 0; i < count; ++i) gw[i] = itq3s::GemvWeight{w[i].codes, w[i].scales, w[i].N, w[i].Y, w[i].ldy};
         if (M <= itq3s::kGemvFusedMaxM) return itq3s::launch_gemv(gw, count, K, Xh, ldx, M, y_f16, status_flags, st);
         const int MP = pad_m(M) < 8 ? 8 : pad_m(M);
-        float* S = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + p.xt_bytes);
-        int rc = itq3s::launch_rotate_frag(Xh, M, K, ldx, MP, Xt, S, status_flags, st);
+        _Float16* const Xt = static_cast<_Float16*>(workspace);
+        float* const S = reinterpret_cast<float*>(base + plan_frag(M, K).xt_bytes);
+        const int rc = itq3s::launch_rotate_frag(Xh, M, K, ldx, MP, Xt, S, status_flags, st);
         if (rc != 0) return rc;
         return itq3s::launch_gemv_rows(gw, count, K, Xt, S, M, MP, y_f16, status_flags, st);
     }
-    // tiled path: one rotation, then one contraction launch for all tensors that do not split K
-    unsigned char* const base = static_cast<unsigned char*>(workspace);
-    uint32_t* zflags = reinterpret_cast<uint32_t*>(base + p.xt_bytes);
-    float* partial = reinterpret_cast<float*>(base + p.xt_bytes + p.flag_bytes);
-    const size_t partial_room = workspace_bytes - p.xt_bytes - p.flag_bytes;  // (checked above: every tensor's shares fit)
-    static_assert(itq3s::kGemmFlagWords * 4 <= 512, "flag words fit their slot");
-    const int rc = itq3s::launch_rotate_rowmajor(Xh, M, K, ldx, Xt, zflags, itq3s::kGemmFlagWords, status_flags, st);
-    if (rc != 0) return rc;
-    itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
-    for (int i = 0; i < count; ++i) gw[i] = itq3s::GemvWeight{w[i].codes, w[i].scales, w[i].N, w[i].Y, w[i].ldy};
-    // (the tensors of a group share the flag words: a flag left by an earlier tensor only costs the
-    // later one a needless scan of its scale words)
-    return itq3s::launch_gemm(gw, count, K, Xt, Xh, ldx, M, y_f16, partial, partial_room, zflags, status_flags, st);
+    // More rows: every tensor by the kernel that its own sizes ask for; those of one kernel share a launch, and the kernels
+    // follow each other in the same scratch (same stream).  With less room than a kernel takes (a workspace sized for
+    // another M, or by an older rule) the many-row kernel's tensors go to the block-scaled one, which takes the rows
+    // in slabs; what has no room for 32 rows, and up to 32 rows with too little, goes through passes of 16.
+    itq3s_weight mx[ITQ3S_MAX_GROUP], pass[ITQ3S_MAX_GROUP];
+    itq3s::Route mx_route[ITQ3S_MAX_GROUP];
+    itq3s::GemvWeight rows[ITQ3S_MAX_GROUP];
+    int n_rows = 0, n_mx = 0, n_pass = 0;
+    const bool room_rows = workspace_bytes >= rows_workspace(M, K);
+    const bool room_mx = workspace_bytes >= (M <= kChunkedMaxM ? mx_workspace(M, K) : itq3s::mx_bytes(1, K));
+    for (int i = 0; i < count; ++i) {
+        if (passes_of_16(M, w[i].N, K)) {
+            pass[n_pass++] = w[i];
+            continue;
+        }
+        itq3s::Route r = itq3s::many_row_route(M, w[i].N, K);
+        if (r == itq3s::Route::rows && room_rows) {
+            rows[n_rows++] = itq3s::GemvWeight{w[i].codes, w[i].scales, w[i].N, w[i].Y, w[i].ldy};
+            continue;
+        }
+        if (!room_mx || (r == itq3s::Route::rows && M <= kChunkedMaxM)) {
+            pass[n_pass++] = w[i];
+            continue;
+        }
+        mx_route[n_mx] = r == itq3s::Route::rows ? itq3s::Route::shares8 : r;
+        mx[n_mx++] = w[i];
+    }
+    int rc = 0;
+    if (n_rows > 0)
+        rc = itq3s::launch_rows(rows, n_rows, K, Xh, ldx, M, reinterpret_cast<_Float16*>(base),
+                                reinterpret_cast<_Float16*>(base + round_up(itq3s::rows_xt_bytes(M, K), 256)), y_f16, status_flags, st);
+    if (rc == 0 && n_pass > 0) {
+        const size_t y_bytes = y_f16 ? 2 : 4;
+        for (int64_t m0 = 0; m0 < M && rc == 0; m0 += itq3s::kGemvMaxM) {
+            itq3s_weight part[ITQ3S_MAX_GROUP];
+            for (int i = 0; i < n_pass; ++i) {
+                part[i] = pass[i];
+                part[i].Y = static_cast<unsigned char*>(pass[i].Y) + (size_t)m0 * (size_t)pass[i].ldy * y_bytes;
+            }
+            const int64_t m = M - m0 < itq3s::kGemvMaxM ? M - m0 : itq3s::kGemvMaxM;
+            rc = itq3s_matmul_grouped(part, n_pass, K, Xh + m0 * ldx, m, ldx, y_dtype, workspace, workspace_bytes, status_flags, stream);
+        }
+    }
+    if (rc == 0 && n_mx > 0) rc = launch_mx_routes(mx, mx_route, n_mx, K, Xh, M, ldx, y_f16, base, workspace_bytes, status_flags, st);
+    return rc;
 }
 
 int itq3s_matmul(const uint32_t* codes, const uint32_t* scales, int64_t N, int64_t K, const void* X, int64_t M, int64_t ldx, void* Y,
@@ -300,7 +335,7 @@ int itq3s_matmul_sub(const uint32_t* codes, const uint32_t* scales, const uint32
     }
     // the streaming kernel: passes of up to 16 rows; a pass of up to four rows (eight for small tensors) rotates
     // the activations itself, a longer one takes them from a rotation launch through the workspace
-    const WorkspacePlan p = plan_workspace(M < itq3s::kGemvMaxM ? M : itq3s::kGemvMaxM, N, K);
+    const FragPlan p = plan_frag(M < itq3s::kGemvMaxM ? M : itq3s::kGemvMaxM, K);
     if (M > itq3s::kGemvFusedMaxM) {
         if (!workspace || workspace_bytes < p.total) return ITQ3S_ERR_WORKSPACE;
         if (!aligned(workspace, 256)) return ITQ3S_ERR_ALIGN;
@@ -329,7 +364,7 @@ int itq3s_matmul_static(const uint32_t* codes, const uint32_t* scales, int64_t N
                         int y_dtype, int64_t ldy, uint32_t* status_flags, void* stream) {
     if (!codes || !scales || !X || !Y) return ITQ3S_ERR_NULL;
     if (N <= 0 || K <= 0 || M <= 0 || K % 256 != 0 || ldx < K || ldy < N) return ITQ3S_ERR_SHAPE;
-    if (itq3s_matmul_workspace_bytes(M, N, K) > (size_t)ITQ3S_STATIC_SCRATCH_BYTES) return ITQ3S_ERR_WORKSPACE;
+    if (least_workspace(M, N, K) > (size_t)ITQ3S_STATIC_SCRATCH_BYTES) return ITQ3S_ERR_WORKSPACE;
     void* ws = scratch_of_current_device();
     if (ws == nullptr) return ITQ3S_ERR_LAUNCH;
     return itq3s_matmul(codes, scales, N, K, X, M, ldx, Y, y_dtype, ldy, ws, (size_t)ITQ3S_STATIC_SCRATCH_BYTES, status_flags, stream);

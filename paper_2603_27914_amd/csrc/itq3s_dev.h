@@ -18,6 +18,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
 
@@ -59,5 +60,12 @@ __device__ __forceinline__ half4 hadamard_quarter(int lane) {
     const uint32_t w0 = 0x34003400u ^ lo, w1 = w0 ^ ((r >> 1) & 1u) * 0x80008000u;
     return __builtin_bit_cast(half4, u32x2{w0, w1});
 }
+
+// fp4 operands of the block-scaled products: the codes c of a low-plane word's even slots (bits 1:0 of its nibbles)
+// as c / 2, those of its odd slots (bits 3:2) as -2 (c - 1); and the scales of B that go with them and the three parts
+// of A (bytes 0..2: 2^(1, -3, -8) and 2^(-1, -5, -10)).
+__device__ __forceinline__ uint32_t even_digits(uint32_t v) { return v & 0x33333333u; }
+__device__ __forceinline__ uint32_t odd_digits(uint32_t v) { return (v ^ 0x44444444u) & 0xCCCCCCCCu; }
+constexpr int kEvenScales = 0x00777c80, kOddScales = 0x00757a7e;
 
 }  // namespace itq3s

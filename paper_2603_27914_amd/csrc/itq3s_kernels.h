@@ -6,14 +6,14 @@
 #include <stdint.h>
 
 #include "itq3s_once.h"
-#include "itq3s_rows_rule.h"
+#include "itq3s_mx_rule.h"
 
 namespace itq3s {
 
 constexpr uint32_t kFlagNonFinite = 1u, kFlagScaleSat = 2u, kFlagZClamp = 4u, kFlagBadCode = 8u, kFlagActRange = 16u;
 
 // The streaming kernel of itq3s_gemv.hip handles up to this many activation rows; more go to that of
-// itq3s_rows.hip or to the tiled one.
+// itq3s_rows.hip or to the block-scaled ones.
 constexpr int kGemvMaxM = 16;
 // Up to this many rows the streaming kernel rotates the activations itself (one launch, no workspace).
 constexpr int kGemvFusedMaxM = 4;
@@ -44,11 +44,6 @@ int launch_dequantize(const uint32_t* codes, const uint32_t* scales, const uint3
 // rotated value leaves the fp16 range.
 int launch_rotate_frag(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int MP, _Float16* Xt, float* S, uint32_t* flags, hipStream_t stream);
 
-// Rotated activations for the tiled path: Xt[m][k] row-major, row stride K.
-// (also clears n_zero words at zero_words: the split-K flags of the contraction that follows)
-int launch_rotate_rowmajor(const _Float16* X, int64_t M, int64_t K, int64_t ldx, _Float16* Xt, uint32_t* zero_words, int n_zero, uint32_t* flags,
-                           hipStream_t stream);
-
 // One weight tensor of a streaming launch and where its product goes.
 struct GemvWeight {
     const uint32_t* codes;
@@ -74,7 +69,7 @@ bool gemv_sub_fused(int64_t M, int64_t N, int64_t K, int64_t ldx);
 int launch_gemv_rows(const GemvWeight* w, int count, int64_t K, const _Float16* Xt, const float* S, int64_t M, int MP, int y_f16,
                      uint32_t* flags, hipStream_t stream);
 
-// The streaming kernel for more rows than launch_gemv_rows takes (rows_path() says for which calls):
+// The streaming kernel for more rows than launch_gemv_rows takes (many_row_route() says for which calls):
 // rotates the activations into Xt (rows_xt_bytes) and X0 (rows_x0_bytes), both 256-byte aligned, then one
 // launch over all row tiles and groups of up to 64 rows (itq3s_rows_rule.h).
 int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, int64_t ldx, int64_t M, _Float16* Xt, _Float16* X0, int y_f16,
@@ -82,6 +77,13 @@ int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
 // Rotated activations for it: groups x mt tiles of 16 rows, layout at rotate_rows_kernel.
 int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int mt, int groups, _Float16* Xt, _Float16* X0, uint32_t* flags,
                        hipStream_t stream);
+
+// The block-scaled kernels (many_row_route() says for which calls).  launch_rotate_mx writes x~ in three parts to Xm (mx_bytes)
+// and, if `sample` is not null, the first kMxSampleRows rows of it in fp16 there (mx_sample_bytes); the two contractions
+// read Xm: K shared out over 8 or 4 wavefronts of a workgroup, or tiled.
+int launch_rotate_mx(const _Float16* X, int64_t M, int64_t K, int64_t ldx, unsigned char* Xm, _Float16* sample, uint32_t* flags, hipStream_t stream);
+int launch_mx_shares(const GemvWeight* w, int count, int64_t K, int64_t M, const unsigned char* Xm, int ks, int y_f16, uint32_t* flags, hipStream_t stream);
+int launch_gemm(const GemvWeight* w, int count, int64_t K, int64_t M, const unsigned char* Xm, int y_f16, uint32_t* flags, hipStream_t stream);
 
 // Compute units of the current device (cached).
 int cu_count();
@@ -92,19 +94,6 @@ inline bool raise_lds_limit(DeviceOnce& once, const void* kernel, int bytes) {
     if (hipGetDevice(&device) != hipSuccess) return false;
     return once(device, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; });
 }
-
-// Tiled matmul for what the streaming kernels do not take.  Xt = rotated activations (launch_rotate_rowmajor); X, ldx = the activations
-// themselves (zero-point term).  Shapes with few output tiles split K over several workgroups per tile
-// and add the shares in a second launch (gemm_splits > 1); all others share one launch.  The former use
-// `partial` (gemm_partial_bytes, 16-byte aligned; partial_bytes = what is there -- too little, or none,
-// means no split) and `zflags` (kGemmFlagWords words, all zero at launch).
-constexpr int kGemmMaxSplits = 8;
-constexpr int kGemmSplitMaxTiles = 128;  // more tiles than this: no split
-constexpr int kGemmFlagWords = 128;
-int gemm_splits(int64_t M, int64_t N, int64_t K);
-size_t gemm_partial_bytes(int64_t M, int64_t N, int64_t K);
-int launch_gemm(const GemvWeight* w, int count, int64_t K, const _Float16* Xt, const _Float16* X, int64_t ldx, int64_t M, int y_f16, float* partial,
-                size_t partial_bytes, uint32_t* zflags, uint32_t* flags, hipStream_t stream);
 
 // Tiled matmul with the inverse transform applied to the weights inside the tile loader (Alg. 2 as
 // printed); X = the activations themselves.  Any M.  subscales: the 116-byte variant's array, or null.

@@ -20,17 +20,20 @@ namespace itq3s {
 // elements e = 64 (l/16) + 16 i + l%16, i = 0..3.
 // Returns false if a rotated value (or the intermediate T, which then turns the result into NaN)
 // leaves the fp16 range.
-__device__ __forceinline__ bool rotate_operand(half4 xa, int lane, _Float16 out[4]) {
-    const half4 q = hadamard_quarter(lane);
+__device__ __forceinline__ floatx4 rotate_f32(half4 xa, const half4& columns, const half4& q) {  // columns: q, or with columns negated
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-    const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, q, zero, 0, 0, 0);
+    const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, columns, zero, 0, 0, 0);
     const half4 th = __builtin_convertvector(T, half4);
     floatx4 rest;
 #pragma unroll
     for (int j = 0; j < 4; ++j) rest[j] = __builtin_fmaf((float)th[j], -1.0f, T[j]);  // exact
     const half4 tl = __builtin_convertvector(rest, half4);
     floatx4 U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, th, zero, 0, 0, 0);
-    U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, tl, U, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(q, tl, U, 0, 0, 0);
+}
+__device__ __forceinline__ bool rotate_operand(half4 xa, int lane, _Float16 out[4]) {
+    const half4 q = hadamard_quarter(lane);
+    const floatx4 U = rotate_f32(xa, q, q);
     const half4 r = __builtin_convertvector(U, half4);
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[i] = r[i];
@@ -133,47 +136,118 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void r
     *reinterpret_cast<u32x4*>(Xt + (((gb * 8 + wave) * mts + mt) * 64 + lane) * 8) = v;  // step t = wave
 }
 
-// Operand order of the tiled kernel: rows stay rows; inside every group of 16 channels, slot s moves
-// to position 2 (s & 7) + (s >> 3), the order in which the tile loader's unpack emits the weights.
-// A wavefront rotates four consecutive chunks (of the list row by row), loads first, and passes the rounded
-// values through a corner of LDS of its own, so that it stores 1 KiB of consecutive addresses per
-// instruction: bound by memory, not by the number of 2-byte stores (2048 x 14336: 31 -> 24 us, at the
-// 5.1 TB/s of a large copy).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rotate_rowmajor_kernel(const _Float16* __restrict__ X, int64_t chunks, int KB, int64_t ldx,
-                                                              _Float16* __restrict__ Xt, uint32_t* __restrict__ zero_words, int n_zero, uint32_t* __restrict__ flags) {
-    __shared__ __align__(16) _Float16 lds[4][4 * kBlock];
+// Operand order of the block-scaled kernels (itq3s_mx_rule.h): a wavefront rotates eight rows of a block and passes the fp32
+// values through LDS of its own, so that a lane holds the 32 channels (row lane % 8, quarter lane / 16, even or odd slots
+// by lane / 8 % 2) that one lane of the products holds; nobody waits for another.
+constexpr int kMxRowStride = 296;  // floats of a row's 256 in LDS: eight groups of 32 in 36, and 8 more (16-byte reads of 8 rows x 2 groups touch all banks)
+typedef float floatx32 __attribute__((ext_vector_type(32)));
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void rotate_mx_kernel(const _Float16* __restrict__ X, int M, int KB, int64_t ldx,
+                                                              unsigned char* __restrict__ Xm, _Float16* __restrict__ sample, uint32_t* __restrict__ flags) {
+    __shared__ __align__(16) float lds[4][8 * kMxRowStride];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // the split-K flags of the contraction that follows start from zero
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n_zero; i += 256) zero_words[i] = 0u;
-    const int64_t first = ((int64_t)blockIdx.x * 4 + wave) * 4;
-    const int n = chunks - first < 4 ? (int)(chunks - first) : 4;
-    if (n <= 0) return;
-    half4 xa[4];
+    const int tile = (int)blockIdx.x / KB, b = (int)blockIdx.x - tile * KB;  // tile of 32 rows
+    unsigned char* const out = Xm + ((int64_t)tile * KB + b) * kMxBlockBytes;
+    unsigned char* const meta = out + 4 * kMxStepBytes;
+    float* const rows = lds[wave];
+    half4 xa[8];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const uint32_t chunk = (uint32_t)(first + (c < n ? c : 0)), m = chunk / (uint32_t)KB, b = chunk - m * (uint32_t)KB;  // (M K / 256 is below 2^31)
-        xa[c] = *reinterpret_cast<const half4*>(X + (int64_t)m * ldx + (int64_t)b * kBlock + 16 * (lane & 15) + 4 * (lane >> 4));
+    for (int rr = 0; rr < 8; ++rr) {
+        const int m = tile * 32 + wave * 8 + rr;
+        xa[rr] = half4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+        if (m < M) xa[rr] = *reinterpret_cast<const half4*>(X + (int64_t)m * ldx + (int64_t)b * kBlock + 16 * (lane & 15) + 4 * (lane >> 4));
     }
-    const int s = lane & 15;
-    bool ok = true;
+    // element 64 q + 16 i + s (q = lane / 16, s = lane % 16) -> group 2 q + s % 2, place 8 i + s / 2; odd s negated
+    // (a result's slot is its column in the first product, where the sign costs nothing)
+    const half4 q = hadamard_quarter(lane);
+    const uint32_t flip = (lane & 1) != 0 ? 0x80008000u : 0u;
+    const half4 columns = __builtin_bit_cast(half4, __builtin_bit_cast(u32x2, q) ^ u32x2{flip, flip});
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        _Float16 r[4];
-        ok = rotate_operand(xa[c], lane, r) && ok;
-        _Float16* const dst = lds[wave] + c * kBlock + 64 * (lane >> 4) + 2 * (s & 7) + (s >> 3);
+    for (int rr = 0; rr < 8; ++rr) {
+        const floatx4 U = rotate_f32(xa[rr], columns, q);
+        float* const dst = rows + rr * kMxRowStride + (2 * (lane >> 4) + (lane & 1)) * 36 + ((lane & 15) >> 1);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) dst[16 * j] = r[j];
+        for (int i = 0; i < 4; ++i) dst[8 * i] = U[i];
     }
+    if (lane == 0) {  // E
+        float* const e = reinterpret_cast<float*>(meta + 384 + wave * 32);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            *reinterpret_cast<floatx4*>(e + 4 * i) = floatx4{16.0f * (float)xa[4 * i][0], 16.0f * (float)xa[4 * i + 1][0], 16.0f * (float)xa[4 * i + 2][0], 16.0f * (float)xa[4 * i + 3][0]};
+    }
+    __builtin_amdgcn_wave_barrier();  // (the LDS instructions of a wavefront stay in order)
+    const int r8 = lane & 7, group = lane >> 3, odd = group & 1, kg = (group >> 1) & 1, step = 2 * (group >> 2) + odd;
+    const float* const src = rows + r8 * kMxRowStride + group * 36;
+    floatx16 r0, r1;  // even and odd fields: the conversion's two sources
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const floatx4 v = *reinterpret_cast<const floatx4*>(src + 4 * i);
+        r0[2 * i] = v[0];
+        r1[2 * i] = v[1];
+        r0[2 * i + 1] = v[2];
+        r1[2 * i + 1] = v[3];
+    }
+    if (sample != nullptr && tile * 32 < (int)kMxSampleRows) {  // (uniform) of every sixteen channels the even slots, then the odd ones
+        _Float16* const to = sample + ((int64_t)(tile * 32 + wave * 8 + r8) * KB + b) * kBlock + 64 * (group >> 1) + 8 * odd;
+        const float sign = odd != 0 ? -1.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            half8 h;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) h[j] = (_Float16)(sign * (j % 2 == 0 ? r0[4 * i + j / 2] : r1[4 * i + j / 2]));
+            *reinterpret_cast<half8*>(to + 16 * i) = h;
+        }
+    }
+    float peak = 0.f, sum = 0.f, sum1 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        peak = __builtin_elementwise_maximum(peak, __builtin_elementwise_maximum(__builtin_fabsf(r0[i]), __builtin_fabsf(r1[i])));
+        sum += r0[i];
+        sum1 += r1[i];
+    }
+    const bool ok = peak <= 65504.0f;
+    const uint32_t bits = __builtin_bit_cast(uint32_t, peak);
+    // scale 2^e with peak / 2^e in (3.75, 7.5], the largest value of the format
+    uint32_t e8 = (bits >> 23) - 2u + ((bits & 0x7fffffu) > 0x700000u ? 1u : 0u);
+    if (peak == 0.f || !ok) e8 = 127u;
+    const int at = 32 * kg + 8 * wave + r8;  // lane of the products
+    unsigned char* const frag = out + step * kMxStepBytes;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const float scale = __builtin_bit_cast(float, (e8 - (p == 0 ? 0u : p == 1 ? 4u : 9u)) << 23);
+        const u32x6 packed = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(r0, r1, scale);
+        const floatx32 back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(packed, scale);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            r0[k] -= back[2 * k];
+            r1[k] -= back[2 * k + 1];
+        }
+        *reinterpret_cast<u32x4*>(frag + p * kMxPartBytes + at * 16) = u32x4{packed[0], packed[1], packed[2], packed[3]};
+        *reinterpret_cast<u32x2*>(frag + p * kMxPartBytes + 1024 + at * 8) = u32x2{packed[4], packed[5]};
+    }
+    // the sum of the parts: of the values less what remains of them
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        sum -= r0[k];
+        sum1 -= r1[k];
+    }
+    sum += sum1;
+    if (!ok) sum = __builtin_nanf("");
+    // -S: over the four groups of even slots
+    sum += xor_lane_f32(sum, 16);
+    sum += xor_lane_f32(sum, 32);
+    if (lane < 8) *reinterpret_cast<float*>(meta + 256 + (8 * wave + r8) * 4) = -sum;
+    int word = (int)((ok ? e8 : 0xffu) << (8 * step));
+    word |= xor_lane_i32(word, 8);
+    word |= xor_lane_i32(word, 32);
+    if (step == 0) *reinterpret_cast<int*>(meta + at * 4) = word;
     if (!ok && flags != nullptr) atomicOr(flags, kFlagActRange);
-    // (one wavefront writes and reads: the LDS instructions of a wavefront stay in order)
-    __builtin_amdgcn_wave_barrier();
-    u32x4* const out = reinterpret_cast<u32x4*>(Xt + first * kBlock);
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(lds[wave] + (64 * u + lane) * 8);
-        if (2 * u + (lane >> 5) < n) out[64 * u + lane] = v;
-    }
+}
+
+int launch_rotate_mx(const _Float16* X, int64_t M, int64_t K, int64_t ldx, unsigned char* Xm, _Float16* sample, uint32_t* flags, hipStream_t stream) {
+    const int64_t tiles = (M + kMxRows - 1) / kMxRows * (K / kBlock);
+    hipLaunchKernelGGL(rotate_mx_kernel, dim3((unsigned)tiles), dim3(256), 0, stream, X, (int)M, (int)(K / kBlock), ldx, Xm, sample, flags);
+    return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
 int launch_rotate_frag(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int MP, _Float16* Xt, float* S, uint32_t* flags, hipStream_t stream) {
@@ -186,13 +260,6 @@ int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int
                        hipStream_t stream) {
     const int64_t tiles = (int64_t)mt * groups * (K / kBlock);
     hipLaunchKernelGGL(rotate_rows_kernel, dim3((unsigned)tiles), dim3(512), 0, stream, X, (int)M, (int)(K / kBlock), ldx, mt, Xt, X0, flags);
-    return hipGetLastError() == hipSuccess ? 0 : -6;
-}
-
-int launch_rotate_rowmajor(const _Float16* X, int64_t M, int64_t K, int64_t ldx, _Float16* Xt, uint32_t* zero_words, int n_zero, uint32_t* flags,
-                           hipStream_t stream) {
-    const int64_t chunks = M * (K / kBlock);
-    hipLaunchKernelGGL(rotate_rowmajor_kernel, dim3((unsigned)((chunks + 15) / 16)), dim3(256), 0, stream, X, chunks, (int)(K / kBlock), ldx, Xt, zero_words, n_zero, flags);
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 

@@ -18,13 +18,12 @@
 // = 10.8 us next to 3.2 us for the weights.  Behind that the unpacking (13 vector instructions per eight
 // weights) and, from 48 rows on, the matrix pipes, each about the weights' time from memory.  So RT is as
 // large as the registers allow -- a fragment fetched serves RT tiles -- but no larger than keeps every unit
-// busy, and K is shared out inside the workgroup.  The tiled kernel at these sizes has its 128 x 256 tiles
-// partly empty and leaves most units idle, or splits K and pays the shares' way through memory.
-// Which calls it takes and how a launch is divided: itq3s_rows_rule.h.
-// Measured, whole call with the rotation launch, before (two passes of the kernel for 16 rows up to 32,
-// tiled kernel above) / now, us (K x N): 4096x4096 M = 32 14.3 / 9.2, M = 48 30 / 10.8, M = 512 38 / 31; three such
-// tensors in one group M = 48 86 / 15; two of 4096x11008 M = 48 66 / 23; 11008x4096 M = 48 40 / 18.9;
-// 8192x28672 M = 48 76 / 43.
+// busy, and K is shared out inside the workgroup.
+// How a launch is divided: itq3s_rows_rule.h; which calls it takes: many_row_route in itq3s_mx_rule.h (the block-scaled
+// kernels fetch 2.31 bytes an activation instead of 2 and unpack in a fifth of the instructions, but start
+// 2.5 us later: a longer rotation, and 32 columns where this kernel takes 16).
+// Measured, whole call with the rotation launch, two passes of the kernel for 16 rows / this one, us (K x N):
+// 4096x4096 M = 32 14.3 / 9.2; M = 48 10.8, three such tensors in one group 15, two of 4096x11008 23; 11008x4096 M = 48 18.9.
 //
 // Order of the loads: a wavefront's load counter is in order, so the weights of the next block are issued
 // between the last fragments of this block that they may overtake and the first of the next: what is

@@ -47,28 +47,21 @@ inline int64_t rows_padded(int64_t M) {
 inline size_t rows_xt_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)K * 2; }
 inline size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)(K / 256) * 3; }  // 64 bytes per 32 rows, 128 per 48 or 64
 
-// When this kernel takes a tensor's call.  Its time over 2 M N K grows faster than the tiled kernel's (0.7 against
-// 1.0 PFLOP/s once the chip is full), but it starts 10 to 15 us earlier (no 128 x 256 tiles that leave the chip
-// empty, no shares of K to write and add).  Beyond 64 rows it is asked up to 36 GFLOP and 3.4 million
-// outputs, a line between sizes like these (us here / there, K x N): 11008x4096 M = 256 36 / 43, 500 63 / 63;
-// 8192x8192 M = 256 49 / 51; 4096x4096 M = 900 57 / 50.  It is no exact one: 28672x8192 M = 96 68 / 77 lies beyond.
-// Within, where the tiled kernel is the faster one all the same:
-//  - short K: the ends of the items count, so a launch of more than so much cost (rows_split) loses.  K = 256:
-//    cost 1719 16.3 / 16.6, 2400 20.2 / 16.1 (N = 28672, M = 65); K = 512: 2400 20.7 / 19.7, 2624 23.8 / 20.8; K = 1024:
-//    2624 34.0 / 31.1 (it wins elsewhere: 0.84 to 0.99), 3280 a tenth slower; up to 64 rows, where the
-//    other kernel's tiles are half empty, 4800 39.7 / 40.5, 5248 48.5 / 41.5 (N = 128256, M = 56).
+// Which calls this kernel may take (many_row_route decides between it and the block-scaled ones, whose times are of the
+// same form; where it may not, they take the call whatever their time).  Beyond 64 rows up to 36 GFLOP and 3.4 million
+// outputs: there the block-scaled ones are ahead by a third (28672x8192 M = 96 83 / 50 us, K x N, here / there).  And not:
+//  - short K: the ends of the items count, so a launch of more than so much cost (rows_split) loses against tiles.
+//    Against tiles of fp16 operands: K = 256: cost 1719 16.3 / 16.6, 2400 20.2 / 16.1 (N = 28672, M = 65); K = 512: 2624
+//    23.8 / 20.8; K = 1024: 2624 34.0 / 31.1; up to 64 rows 4800 39.7 / 40.5, 5248 48.5 / 41.5 (N = 128256, M = 56).
 //  - more than 1280 rows: every round more reads the rotated activations through every chiplet's L2 again, which
-//    does not hold them.  N = 1000, K = 4096: M = 1024 (one round) 24 / 34, 1500 (two) 41 / 36, 2048 (two) 52 / 41;
-//    N = 766, K = 6912, M = 1532 (two) 59 / 44; K = 2048: N = 1000, M = 2048 (two) 32.9 / 33.2, N = 1500, M = 2048
-//    (three) 43.5 / 34.6.  (Thin tensors of a group lose by it: they would share one launch here, there each
-//    splits K for itself: M = 1696, 632 + 632 + 79 columns, K = 4864 67 / 92.)
+//    does not hold them (N = 1000, K = 4096: M = 1024, one round, 24; 1500, two, 41; 2048, two, 52).
 //  - 17 rows of a thin tensor with long K: two passes of the kernel for 16 rows, whose second rotates its one row
 //    in the kernel, are 4 to 10 % faster (N = 16, K = 28672 30.5 / 27.8).
 // A rule on the sizes of one tensor (counted for 256 units): a grouped call computes every tensor as a call
 // of its own does.
 inline bool rows_path(int64_t M, int64_t N, int64_t K) {
     if (M < kRowsMinM || K > kRowsMaxK || M > kRowsMaxM) return false;
-    // the padded rows must not take a call over a scratch limit that the tiled path keeps
+    // scratch: the padded rows must not take a call over a limit that rows as they are keep
     if (rows_xt_bytes(M, K) + rows_x0_bytes(M, K) > (32u << 20)) return false;
     if (M <= 32) return M > 17 || N > 1024 || K < 20480;
     if (M > 64 && ((double)M * (double)N * (double)K > 18e9 || (double)M * (double)N > 3.4e6)) return false;

@@ -1,0 +1,142 @@
+"""The block-scaled kernels (fp4 digits, activations in three fp6 parts) at the sizes where their division of the work
+changes: rows of every remainder modulo the tiles of 32 and 64, ragged columns, wavefronts without a block, several rounds,
+each number of columns an item has, tensors of one launch.  Against itq3s_dequantize and a dense fp64 product."""
+import os
+import subprocess
+
+import pytest
+
+from tests.test_gpu_rows import gpu, tensor  # noqa: F401  (gpu is a fixture)
+
+# M, N, K, route (0 many-row kernel, 1 and 2 K over 8 or 4 wavefronts, 3 tiled)
+SIZES = [
+    (481, 33, 3584, 1),     # 14 blocks: two wavefronts have one, the others two; 32 columns an item
+    (1301, 100, 1280, 1),   # five blocks: three wavefronts have none; 64 columns
+    (700, 1000, 2304, 1),   # nine blocks; 128 columns
+    (500, 1000, 4096, 1),
+    (20, 28672, 4096, 1),   # rows: 12 of padding
+    (2113, 300, 8192, 1),   # two rounds
+    (512, 4096, 4096, 2),
+    (2081, 515, 1024, 2),   # one block a wavefront, the last columns of an item beyond the tensor
+    (993, 1032, 4096, 2),
+    (6300, 17, 256, 3),     # one block, one storage tile and a ragged one, an odd number of tiles of 32 rows
+    (65, 65000, 512, 3),    # one row in the second tile of 64
+    (640, 4100, 2560, 3),
+    (33, 40000, 2816, 3),
+]
+
+
+def test_sizes_take_the_routes_they_are_here_for(tmp_path):
+    from paper_2603_27914_amd import build
+
+    main = tmp_path / "route.cpp"
+    main.write_text(
+        '#include "itq3s_mx_rule.h"\n#include <cstdio>\n'
+        "int main() { long long M, N, K;\n"
+        '    while (std::scanf("%lld %lld %lld", &M, &N, &K) == 3) std::printf("%d ", (int)itq3s::many_row_route(M, N, K)); }\n'
+    )
+    exe = tmp_path / "route"
+    subprocess.run(["g++", "-std=c++17", "-I", build.CSRC, str(main), "-o", str(exe)], check=True)
+    # besides: a group's thin tensors go where its wide ones go
+    more = [(512, n, 4096, None) for n in (512, 1024, 4096)] + [(58, n, 23040, 0) for n in (264, 2112)] + [(48, n, 4096, 0) for n in (512, 4096)]
+    sizes = "".join("%d %d %d\n" % s[:3] for s in SIZES + more)
+    got = [int(v) for v in subprocess.run([str(exe)], input=sizes, check=True, stdout=subprocess.PIPE, text=True).stdout.split()]
+    for (M, N, K, route), r in zip(SIZES + more, got):
+        assert r == route if route is not None else r != 0, (M, N, K, r)
+
+
+def activations(torch, M, K, seed):
+    X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(seed), device="cuda").half()
+    X[:, 5::97] *= 10
+    return X
+
+
+def check(torch, Y, X, What, half):
+    """A rotated value is carried to 2^-14 of the largest of its 32 (the last part's step is 2^-12 of a unit that the
+    largest exceeds 3.75 times), so per element at most 2^-14 sqrt(32) ||x|| ||w_hat|| by Cauchy-Schwarz over the groups,
+    half as much again for the fp32 sums; the intermediate of the rotation in two fp16 parts, the lower one no finer than
+    fp16's 2^-24 (2^-25 an element; what follows it is orthonormal, so sqrt(K) of them in norm: rows of tiny values); and
+    the rounding of the result.  Rows on the whole: 1e-4 (3.5e-5 measured)."""
+    want = X.double() @ What.T
+    err = (Y.double() - want).abs()
+    x, w = X.double().norm(dim=1)[:, None], What.norm(dim=1)[None, :]
+    bound = (1.5 * 2.0**-14 * 32**0.5 * x + 2.0**-25 * X.shape[1] ** 0.5) * w + 2.0 ** (-11 if half else -22) * want.abs()
+    assert (err / bound).max().item() <= 1.0
+    if not half:
+        assert (err.norm() / want.norm()).item() <= 1e-4
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,route", SIZES)
+def test_block_scaled(gpu, M, N, K, route):  # noqa: F811
+    torch, binding = gpu
+    codes, scales, What = tensor(torch, binding, N, K, "mx", M, z_fraction=0.02 if N < 5000 else 0.0)
+    buf = activations(torch, M, K + 8, M)
+    X = buf[:, :K]
+    for dtype in (torch.float32, torch.float16):
+        out = torch.full((M, N + 3), 7.0, dtype=dtype, device="cuda")
+        flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+        ws = torch.full((binding.itq3s_matmul_workspace_bytes(M, N, K),), 0xFF, dtype=torch.uint8, device="cuda")
+        binding.itq3s_matmul(codes, scales, N, K, X, out=out[:, :N], workspace=ws, status_flags=flags)
+        assert int(flags.item()) == 0 and bool((out[:, N:] == 7.0).all())
+        check(torch, out[:, :N], X, What, dtype == torch.float16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,Ns", [(901, 1792, (4096, 1000, 40, 17)), (1301, 1280, (300, 9000, 2048))])
+def test_group_and_slabs_equal_single_calls(gpu, M, K, Ns):  # noqa: F811
+    """Tensors of all three kernels in one call; the same with room for part of the rows only, in several slabs."""
+    torch, binding = gpu
+    ts = [tensor(torch, binding, N, K, "mxg", i, z_fraction=(0.0, 0.9)[i & 1]) for i, N in enumerate(Ns)]
+    X = activations(torch, M, K, 1)
+    want = [binding.itq3s_matmul(c, s, N, K, X) for (c, s, _), N in zip(ts, Ns)]
+    for (_, _, What), Y in zip(ts, want):
+        check(torch, Y, X, What, False)
+    full = max(binding.itq3s_matmul_workspace_bytes(M, N, K) for N in Ns)
+    least = (M * K * 2 + 255) // 256 * 256 + 768  # the activation rows as they are (K below 2048: no shares of K on top)
+    assert least < full
+    for room in (full, least):
+        ws = torch.full((room,), 0xFF, dtype=torch.uint8, device="cuda")
+        outs = binding.itq3s_matmul_grouped([(c, s, N) for (c, s, _), N in zip(ts, Ns)], K, X, dtype=torch.float32, workspace=ws)
+        for a, b in zip(outs, want):
+            assert torch.equal(a, b), room
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(500, 1000, 4096), (512, 4096, 4096), (640, 4100, 2560)])
+def test_range_and_format_flags(gpu, M, N, K):  # noqa: F811
+    torch, binding = gpu
+    codes, scales, What = tensor(torch, binding, N, K, "mxf")
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    bad = codes.clone()
+    bad[-384 + 256 + 100] = -1 << 31  # a high-plane bit in the last tile
+    X = activations(torch, M, K, 2)
+    binding.itq3s_matmul(bad, scales, N, K, X, status_flags=flags)
+    assert int(flags.item()) == binding.FLAG_BAD_CODE
+    for value in (4100.0, float("inf"), float("nan")):  # rotates to 16 x 4100 > 65504; not finite
+        Z = X.clone()
+        Z[M - 1, 256:512] = value
+        flags.zero_()
+        Y = binding.itq3s_matmul(codes, scales, N, K, Z, status_flags=flags)
+        assert int(flags.item()) == binding.FLAG_ACT_RANGE
+        assert not bool(torch.isfinite(Y[M - 1]).any()) and bool(torch.isfinite(Y[: M - 1]).all())
+        check(torch, Y[: M - 1], Z[: M - 1], What, False)
+
+
+@pytest.mark.gpu
+def test_scales_of_the_activations(gpu):  # noqa: F811
+    """Rows of every magnitude that fp16 has, constants (one rotated value, all others zero), a single spike, zeros: a row's
+    error is bound by its own norm."""
+    torch, binding = gpu
+    M, N, K = 500, 1000, 4096
+    codes, scales, What = tensor(torch, binding, N, K, "mxs")
+    X = activations(torch, M, K, 3)
+    X[0] = 0
+    X[1] = 3.0
+    X[2] = 0
+    X[2, 777] = 1000.0
+    for i in range(3, 27):
+        X[i] = (X[i].float() * 2.0 ** (i - 24)).half()
+    Y = binding.itq3s_matmul(codes, scales, N, K, X)
+    assert bool((Y[0] == 0).all())
+    check(torch, Y, X, What, False)
