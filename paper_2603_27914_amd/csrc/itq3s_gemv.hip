@@ -16,8 +16,12 @@
 // Contraction: v_mfma_f32_16x16x32_f16 with the activations as the A operand (rows = m) and 16
 // weight rows of a tile as the B operand (columns = n), so that every accumulator of a lane belongs
 // to the lane's own weight row and needs only that row's scale.  A code c in {0,1,2} placed in bits
-// 11:10 of a half is the number c * 2^-14, so two codes that sit 16 bits apart in a low-plane word
-// become a half2 with one shift and one mask; the factor 2^14 is applied together with d.
+// 11:10 of a half is the number c * 2^-14, in bits 9:8 c * 2^-16 (fp16's subnormal numbers take part in the products
+// unchanged), so a shift of a low-plane word by a multiple of four gives two half2 operands with one mask each; the factors
+// are applied together with d.  Four-row decode is bound by this arithmetic (two of 4096x11008, M = 4: 5.5 us of
+// vector instructions in a launch of 11): the two positions took a sixth off a tile's share, and the rows
+// are rotated together, two by two, instead of one after another.  us, before / now (K x N): 11008x4096 M = 1 7.0 / 6.6, M = 4 9.5 / 8.6;
+// 28672x8192 M = 1 18.8 / 17.9, M = 4 25.0 / 22.5; 8192x57344 M = 4 39.5 / 36.5; 5120x5120 M = 4 7.4 / 6.8.
 //
 // Work split: workgroup g (8 wavefronts) owns RT or RT-1 consecutive 16-row tiles of the launch and
 // all of K; wavefront w takes blocks w, w+8, ...  A step of a wavefront is one block against the
@@ -77,40 +81,61 @@ struct TileRegs {
 // b', four rows a per lane) is exactly the B-operand layout of the second, so nothing moves between
 // lanes.  A lane holds x[16 (l%16) + 4 (l/16) + 0..3] on entry and element e = 64 (l/16) + 16 r + l%16,
 // r = 0..3, of the result.
-// x~ = H x for one 256-chunk, rounded to fp16, scattered into operand order at `dst` (256*MP halves:
-// index ((t*4 + g)*MP + m)*8 + i).  `peak` collects the largest magnitude of a rotated value; a value (or the
+// x~ = H x for one 256-chunk of each row, rounded to fp16, in operand order: half i of step t of quarter g of row m at
+// half m kXsRow + g kXsQuarter + 8 t + i.  `peak` collects the largest magnitude of a rotated value; a value (or the
 // intermediate T, which then turns the result into NaN) outside the fp16 range leaves it above 65504 or NaN.
 // Every workgroup rotates all of X for itself, so with two to four rows this arithmetic is a good part
 // of the launch: both products take the quarter of H (their factors make up the 1/16 exactly), conversions
-// go in pairs, the residue of T is one mixed-precision multiply-add, and the range is one NaN-propagating
-// three-way maximum per two values -- 12 vector instructions a chunk instead of 26.
-template <int MP>
-__device__ __forceinline__ void rotate_to_lds(u32x2 raw, const half4& q, int lane, int m, _Float16* dst, float& peak) {
-    const half4 xa = __builtin_bit_cast(half4, raw);
-    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-    const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, q, zero, 0, 0, 0);
-    const half4 th = __builtin_convertvector(T, half4);
-    floatx4 rest;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) rest[j] = __builtin_fmaf((float)th[j], -1.0f, T[j]);  // exact
-    const half4 tl = __builtin_convertvector(rest, half4);
-    floatx4 U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, th, zero, 0, 0, 0);
-    U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, tl, U, 0, 0, 0);
-    const half4 r = __builtin_convertvector(U, half4);
-    peak = __builtin_elementwise_maximum(peak, __builtin_elementwise_maximum(__builtin_fabsf(U[0]), __builtin_fabsf(U[1])));
-    peak = __builtin_elementwise_maximum(peak, __builtin_elementwise_maximum(__builtin_fabsf(U[2]), __builtin_fabsf(U[3])));
-    // element e = 64g + 16w + slot (w = r, slot = l%16): quarter g, low-plane word w, code slot `slot`;
-    // MFMA step t = 2w + ((slot&7)>>2), position i = 2(slot&3) + (slot>>3)
+// go in pairs, the residue of T is one mixed-precision multiply-add, the range is one NaN-propagating
+// three-way maximum per two values, and the rows go through each stage together (a row alone waits for three products
+// one after another).  Element e = 64 g + 16 w + slot is half 2 w + slot / 8 of step slot % 8: lanes whose slots are 8 apart
+// hold the two halves of the same words, so each gives the other half of its words and both write eight bytes.
+constexpr int kXsQuarter = 72, kXsRow = 4 * kXsQuarter;  // halves; 64 and 8 more: the reads of 4 rows x 4 quarters touch all banks
+struct XsLane {  // what a lane needs to write its part, computed once
+    _Float16* dst;
+    uint32_t sel0;  // the halves of its first word; of the second: two bytes on
+};
+__device__ __forceinline__ XsLane xs_lane(_Float16* xs, int lane) {
     const int g = lane >> 4, slot = lane & 15;
-    const int tb = (slot & 7) >> 2, i0 = 2 * (slot & 3) + (slot >> 3);
+    return XsLane{xs + g * kXsQuarter + (slot & 7) * 8 + ((slot & 8) >> 1), (slot & 8) != 0 ? 0x05040100u : 0x01000504u};
+}
+template <int M0, int MN, int MP>
+__device__ __forceinline__ void rotate_to_lds(const u32x2 (&raw)[MP], const half4& q, const XsLane& at, float& peak) {
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    float minus_one = -1.0f;
+    asm("" : "+s"(minus_one));  // (with the constant in sight the multiply-add becomes a conversion and a subtraction)
+    floatx4 T[MN], U[MN];
+    half4 th[MN], tl[MN];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) dst[(((2 * w + tb) * 4 + g) * MP + m) * 8 + i0] = r[w];
+    for (int m = 0; m < MN; ++m) T[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(half4, raw[M0 + m]), q, zero, 0, 0, 0);
+#pragma unroll
+    for (int m = 0; m < MN; ++m) th[m] = __builtin_convertvector(T[m], half4);
+#pragma unroll
+    for (int m = 0; m < MN; ++m) {
+        U[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(q, th[m], zero, 0, 0, 0);
+        floatx4 rest;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rest[j] = __builtin_fmaf((float)th[m][j], minus_one, T[m][j]);  // exact
+        tl[m] = __builtin_convertvector(rest, half4);
+    }
+#pragma unroll
+    for (int m = 0; m < MN; ++m) U[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(q, tl[m], U[m], 0, 0, 0);
+#pragma unroll
+    for (int m = 0; m < MN; ++m) {
+        const u32x2 h = __builtin_bit_cast(u32x2, __builtin_convertvector(U[m], half4));
+        const bool upper = (at.sel0 & 0x04000000u) != 0;
+        const uint32_t keep = upper ? h.y : h.x, send = upper ? h.x : h.y;
+        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x128, 0xf, 0xf, true);  // row_ror:8
+        *reinterpret_cast<half4*>(at.dst + (M0 + m) * kXsRow) = __builtin_bit_cast(half4, u32x2{__builtin_amdgcn_perm(keep, got, at.sel0), __builtin_amdgcn_perm(keep, got, at.sel0 + 0x02020202u)});
+        peak = __builtin_elementwise_maximum(peak, __builtin_elementwise_maximum(__builtin_fabsf(U[m][0]), __builtin_fabsf(U[m][1])));
+        peak = __builtin_elementwise_maximum(peak, __builtin_elementwise_maximum(__builtin_fabsf(U[m][2]), __builtin_fabsf(U[m][3])));
+    }
 }
 
 // kGrouped: the launch serves several tensors (a single-tensor launch skips the lookup and the
 // fetch of the unused descriptors, which are on the way to the first load).
-// NBC > 0: every wavefront has exactly NBC blocks (K = 2048 NBC): the pipeline is straight-line code,
-// which the compiler fits into 57..92 registers instead of 86..126 -- a third workgroup per compute unit.
+// NBC > 0: every wavefront has exactly NBC blocks (K = 2048 NBC): the pipeline is straight-line code, for one and two
+// tiles (60 to 126 registers; three tiles would take up to 156, and the second workgroup per compute unit).
 // kSub: the sub-block-scale variant of the format (Sec. 4.1: 116 bytes per block), one tensor per launch:
 //   Y[m][n] = sum_b d ( sum_j s[n,b,j/32] (c-1)[n,b,j] x~[m,b,j]  -  z E[m,b] ).
 // A lane's 64 codes belong to two sub-blocks (low-plane words 0,1 and 2,3), whose scales are the two
@@ -130,8 +155,8 @@ __device__ __forceinline__ void rotate_to_lds(u32x2 raw, const half4& q, int lan
 template <int MP, int RT, bool kGrouped, int NBC, bool kSub = false, bool kRotated = false, int NSG = 1>
 // (launch bounds: the second figure is a lower bound on wavefronts per SIMD: 4 = two workgroups per
 // compute unit = at most 128 registers, which every instantiation of the general pipeline meets
-// without scratch; the straight-line kernels use 57..92 registers on their own; eight rows rotated here
-// run with one workgroup per compute unit)
+// without scratch (four rows against three tiles only just: what is said to cost registers below); eight rows rotated
+// here run with one workgroup per compute unit)
 __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotated) ? 2 : 4) void gemv_kernel(const GemvArgs a) {
     static_assert(!kRotated || (NBC == 0 && MP >= 8), "rotated activations: general pipeline");
     static_assert(kRotated || MP <= 8, "in-kernel rotation: at most eight rows");
@@ -153,8 +178,8 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
         int64_t rows;  // rows of that tensor from n0 on that exist (<= 0: slot unused)
     };
     // LDS: per wavefront MP*512 bytes of x~ (in-kernel rotation only) | red: W*RTW*MP*16 floats | slot_out[RTW]
-    constexpr size_t kXsBytes = kRotated ? 0 : (size_t)W * MP * 512;
-    _Float16* const xs = reinterpret_cast<_Float16*>(smem) + (size_t)wave * MP * 256;
+    constexpr size_t kXsBytes = kRotated ? 0 : (size_t)W * MP * kXsRow * 2;
+    _Float16* const xs = reinterpret_cast<_Float16*>(smem) + (size_t)wave * MP * kXsRow;
     float* const red = reinterpret_cast<float*>(smem + kXsBytes);
     SlotOut* const slot_out = reinterpret_cast<SlotOut*>(smem + kXsBytes + (size_t)W * RTW * MP * 16 * 4);
 
@@ -197,20 +222,20 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
         so_n0[rt] = local * 16;
         so_rows[rt] = have ? t_n - local * 16 : 0;
     }
-    // activations: rows beyond M read as zeros (offset outside the descriptor's range)
-    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<_Float16*>(a.X), 0, kRotated ? KB * MP * 512 : (int)(((int64_t)(a.M - 1) * a.ldx + (int64_t)KB * 256) * 2), kRawBuffer);
+    // activations; rows beyond M have an empty descriptor and read as zeros
+    __amdgpu_buffer_rsrc_t xrs[kRotated ? 1 : MP];
+#pragma unroll
+    for (int m = 0; m < (kRotated ? 1 : MP); ++m)
+        xrs[m] = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<_Float16*>(a.X), 0, kRotated ? KB * MP * 512 : m < a.M ? (int)(((int64_t)(a.M - 1) * a.ldx + (int64_t)KB * 256) * 2) : 0, kRawBuffer);
     const __amdgpu_buffer_rsrc_t sumrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.S), 0, kRotated ? 2 * KB * MP * 4 : 0, kRawBuffer);
     const int nb = KB > wave ? (KB - wave + W - 1) / W : 0;  // blocks of this wavefront: b = wave + j*W
 
     constexpr uint32_t kOutside = 0x80000000u;  // an offset no descriptor here covers
     const uint32_t none = nb > 0 ? 0u : kOutside;  // a wavefront without blocks (K < 2048) loads nothing
     const uint32_t off_lo = lane * 16 + none, off_hi = lane * 8 + 1024 + none, off_sc = r16 * 4 + none, off_ss = lane * 4 + none;
-    uint32_t off_x[kRotated ? 1 : MP];
-    if constexpr (!kRotated) {
-#pragma unroll
-        for (int m = 0; m < MP; ++m) off_x[m] = m < a.M ? ((uint32_t)(m * a.ldx * 2) + (16 * r16 + 4 * g) * 2) | none : kOutside;
-    }
+    // (a row's place is in the scalar offset, which costs no register)
+    const uint32_t off_x = (uint32_t)((16 * r16 + 4 * g) * 2) | none;
     // rotated activations: fragment t of the block for lane (row mm, quarter g) at ((t*4 + g)*MP + mm)*16 bytes
     const uint32_t off_xf = (uint32_t)((g * MP + mm) * 16) + none, off_sum = (uint32_t)(((4 * g) & (MP - 1)) * 4) + none;
     half8 xf[kRotated ? 8 : 1];
@@ -219,7 +244,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
         const int b = nb > 0 ? wave + j * W : 0;
 #pragma unroll
         for (int t = 0; t < 8; ++t)
-            xf[t] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(xrs, off_xf + (uint32_t)(t * 4 * MP * 16), b * (MP * 512), 0));
+            xf[t] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(xrs[0], off_xf + (uint32_t)(t * 4 * MP * 16), b * (MP * 512), 0));
         sv_r = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(sumrs, off_sum, b * (MP * 4), 0));
         ev_r = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(sumrs, off_sum, (KB + b) * (MP * 4), 0));
     };
@@ -243,7 +268,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
         const int b = nb > 0 ? wave + j * W : 0;
         if constexpr (!kRotated) {
 #pragma unroll
-            for (int m = 0; m < MP; ++m) s.xr[m] = __builtin_amdgcn_raw_buffer_load_b64(xrs, off_x[m], b * 512, 0);
+            for (int m = 0; m < MP; ++m) s.xr[m] = __builtin_amdgcn_raw_buffer_load_b64(xrs[m], off_x, b * 512 + (int)(m * a.ldx * 2), 0);
         }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
@@ -256,67 +281,119 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
     auto issue = [&](Slot& s, int j) { issue_sg(s, j, std::integral_constant<int, 0>{}); };
 
     [[maybe_unused]] const half4 hq = hadamard_quarter(lane);
-    const half8 ones = as_half8(0x04000400u, 0x04000400u, 0x04000400u, 0x04000400u);  // 2^-14 each
+    [[maybe_unused]] const XsLane xs_at = xs_lane(xs, lane);
+    [[maybe_unused]] const _Float16* const xs_src = xs + mm * kXsRow + g * kXsQuarter;
 
     auto compute_sg = [&](const Slot& s, auto sgc) {
         constexpr int SG = decltype(sgc)::value;
-        float ev[4];
-        if constexpr (kRotated) {
+        [[maybe_unused]] uint32_t first[kRotated ? 1 : MP];  // lane 0 holds x[0..3] of the chunk
+        float ev[4];  // E = 16 x_0 (rows m = 4g + i of the accumulators are row m & (MP-1))
+        auto sums_e = [&] {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ev[i] = ev_r[i];
-        } else {
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (kRotated) {
+                    ev[i] = ev_r[i];
+                } else {
+                    ev[i] = 16.0f * f16_bits_to_f32(first[i & (MP - 1)] & 0xffffu);
+                    if constexpr (MP == 8) ev[i] = (g & 1) != 0 ? 16.0f * f16_bits_to_f32(first[4 + i] & 0xffffu) : ev[i];
+                }
+            }
+        };
+        if constexpr (!kRotated) {
+            if constexpr (MP > 2) {  // (E behind the products, from scalar registers)
 #pragma unroll
-            for (int m = 0; m < MP; ++m) rotate_to_lds<MP>(s.xr[m], hq, lane, m, xs, peak);
+            for (int m = 0; m < MP; ++m) first[m] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.xr[m].x);
+            }
+            if constexpr (MP <= 2) {
+                rotate_to_lds<0, MP>(s.xr, hq, xs_at, peak);
+            } else {
+                rotate_to_lds<0, 2>(s.xr, hq, xs_at, peak);
+                __builtin_amdgcn_sched_barrier(0);
+                rotate_to_lds<2, 2>(s.xr, hq, xs_at, peak);
+                if constexpr (MP > 4) {
+                    rotate_to_lds<4, 2>(s.xr, hq, xs_at, peak);
+                    rotate_to_lds<6, 2>(s.xr, hq, xs_at, peak);
+                }
+            }
+            if constexpr (MP <= 2) {
+#pragma unroll
+            for (int m = 0; m < MP; ++m) first[m] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.xr[m].x);
+                sums_e();
+            }
             // (116-byte variant, one row: without the line here the scheduler spreads the rotation over the
             // unpacking and three row tiles take 128 registers and scratch: 8192x11008 11.3 us instead of 10.7)
             if constexpr (kSub && MP == 1) __builtin_amdgcn_sched_barrier(0);
-            // lane 0 holds x[0..3] of the chunk: E = 16 x_0 (rows m = 4g + i of the accumulators are row m & (MP-1))
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.xr[i & (MP - 1)].x);
-                ev[i] = 16.0f * f16_bits_to_f32(w0 & 0xffffu);
-                if constexpr (MP == 8) {
-                    const uint32_t w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.xr[4 + i].x);
-                    ev[i] = (g & 1) != 0 ? 16.0f * f16_bits_to_f32(w1 & 0xffffu) : ev[i];
-                }
-            }
         }
         // the block sums S come from the matrix cores as well: the same fragments against an operand of ones
+        uint32_t one = 0x04000400u;
+        if constexpr (!kRotated && MP > 2 && RT == 3) asm("" : "+v"(one));  // (made anew for each block: registers)
+        [[maybe_unused]] const half8 ones = as_half8(one, one, one, one);  // 2^-14 each
         floatx4 sacc = {0.f, 0.f, 0.f, 0.f};
         floatx4 c[RT];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) c[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
-        half8 sub_mul[kSub ? RT : 1][2], sub_add[kSub ? RT : 1][2];  // (sub-block variant) 16 s and -s 2^-10 of the lane's two sub-blocks
+        half8 sub_mul[kSub ? RT : 1], sub_add[kSub ? RT : 1];  // (sub-block variant) 16 s and -s 2^-10 of the lane's two sub-blocks
         if constexpr (kSub) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 const half2v s2 = __builtin_bit_cast(half2v, s.t[rt].ss);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const _Float16 m = s2[h] * (_Float16)16.0f, n = s2[h] * (_Float16)(-0.0009765625f);
-                    sub_mul[rt][h] = half8{m, m, m, m, m, m, m, m};
-                    sub_add[rt][h] = half8{n, n, n, n, n, n, n, n};
-                }
+                const half2v m = s2 * half2v{(_Float16)16.0f, (_Float16)16.0f}, n = s2 * half2v{(_Float16)(-0.0009765625f), (_Float16)(-0.0009765625f)};
+                sub_mul[rt] = half8{m.x, m.x, m.x, m.x, m.y, m.y, m.y, m.y};  // words 0,1 | 2,3
+                sub_add[rt] = half8{n.x, n.x, n.x, n.x, n.y, n.y, n.y, n.y};
             }
         }
+        // Slots s and s + 8 of a low-plane word are 16 bits apart.  Shifted by a multiple of four the word has one pair at bits
+        // 11:10 (odd s: the halves c 2^-14) and one at 9:8 (even s: c 2^-16, in a sum of its own that counts four times):
+        // eleven instructions a word instead of fifteen with a shift for each pair.  (The sub-scaled operands, whose
+        // range ends at fp16's, all come from bits 11:10.)
+        auto fragment = [&](int t) -> half8 {
+            if constexpr (kRotated) return xf[t];
+            else return *reinterpret_cast<const half8*>(xs_src + 8 * t);
+        };
         constexpr uint32_t kMask = 0x0C000C00u;
+        auto shifted = [](uint32_t v, int by) -> uint32_t { return by >= 0 ? v << by : v >> -by; };
+        if constexpr (kSub) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            half8 Xf;
-            if constexpr (kRotated) Xf = xf[t];
-            else Xf = *reinterpret_cast<const half8*>(xs + ((t * 4 + g) * MP + mm) * 8);
-            if constexpr (!kSub && !kRotated) sacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xf, ones, sacc, 0, 0, 0);
+            for (int t = 0; t < 8; ++t) {
+                const half8 Xf = fragment(t);
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const uint32_t wds[4] = {s.t[rt].lo.x, s.t[rt].lo.y, s.t[rt].lo.z, s.t[rt].lo.w};
-                const uint32_t v = wds[t >> 1];
-                // slots j and j+8 of the word -> bits 11:10 and 27:26
-                half8 op = (t & 1) == 0 ? as_half8((v << 10) & kMask, (v << 8) & kMask, (v << 6) & kMask, (v << 4) & kMask)
-                                        : as_half8((v << 2) & kMask, v & kMask, (v >> 2) & kMask, (v >> 4) & kMask);
-                if constexpr (kSub) op = __builtin_elementwise_fma(op, sub_mul[rt][t >> 2], sub_add[rt][t >> 2]);  // words 0,1 | 2,3
-                c[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xf, op, c[rt], 0, 0, 0);
+                for (int rt = 0; rt < RT; ++rt) {
+                    const u32x4 v = s.t[rt].lo;
+                    half8 op = as_half8(shifted(v.x, 10 - 2 * t) & kMask, shifted(v.y, 10 - 2 * t) & kMask, shifted(v.z, 10 - 2 * t) & kMask, shifted(v.w, 10 - 2 * t) & kMask);
+                    op = __builtin_elementwise_fma(op, sub_mul[rt], sub_add[rt]);
+                    c[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xf, op, c[rt], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
+        } else {
+            floatx4 ce[RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) ce[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {  // slots 2p + 1 and 2p
+                const half8 Xo = fragment(2 * p + 1), Xe = fragment(2 * p);
+                if constexpr (!kRotated) {
+                    sacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xo, ones, sacc, 0, 0, 0);
+                    sacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xe, ones, sacc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const u32x4 lo = s.t[rt].lo;
+                    const uint32_t v[4] = {shifted(lo.x, 8 - 4 * p), shifted(lo.y, 8 - 4 * p), shifted(lo.z, 8 - 4 * p), shifted(lo.w, 8 - 4 * p)};
+                    c[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xo, as_half8(v[0] & kMask, v[1] & kMask, v[2] & kMask, v[3] & kMask), c[rt], 0, 0, 0);
+                    ce[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xe, as_half8(v[0] & (kMask >> 2), v[1] & (kMask >> 2), v[2] & (kMask >> 2), v[3] & (kMask >> 2)), ce[rt], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[rt][i] = __builtin_fmaf(ce[rt][i], 4.0f, c[rt][i]);
         }
+        if constexpr (kRotated || MP > 2) sums_e();
+        float sv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sv[i] = kRotated ? sv_r[i] : 16384.0f * sacc[i];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             bad |= s.t[rt].hi.x | s.t[rt].hi.y;
@@ -325,8 +402,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 acc[SG * RT + rt][i] = kSub       ? __builtin_fmaf(d, __builtin_fmaf(c[rt][i], 1024.0f, -z * ev[i]), acc[SG * RT + rt][i])
-                                       : kRotated ? __builtin_fmaf(d, __builtin_fmaf(c[rt][i], 16384.0f, -__builtin_fmaf(z, ev[i], sv_r[i])), acc[SG * RT + rt][i])
-                                                  : __builtin_fmaf(d, __builtin_fmaf(c[rt][i] - sacc[i], 16384.0f, -z * ev[i]), acc[SG * RT + rt][i]);
+                                                  : __builtin_fmaf(d, __builtin_fmaf(c[rt][i], 16384.0f, -__builtin_fmaf(z, ev[i], sv[i])), acc[SG * RT + rt][i]);
         }
     };
     auto compute = [&](const Slot& s) { compute_sg(s, std::integral_constant<int, 0>{}); };
@@ -400,14 +476,15 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
     }
 
     // ---- add the W partial sums of every output, store Y.  red[wave][rt][m][r]; slot_out says where
-    // the 16 outputs of a slot go.
+    // the 16 outputs of a slot go.  (The lane's number is counted anew: held through the pipeline it costs registers.)
+    const int lane_end = MP > 2 && RT == 3 ? (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane, g_end = lane_end >> 4;
 #pragma unroll
     for (int rt = 0; rt < RTW; ++rt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (4 * g + i < MP) red[((wave * RTW + rt) * MP + 4 * g + i) * 16 + r16] = acc[rt][i];
+            if (4 * g_end + i < MP) red[((wave * RTW + rt) * MP + 4 * g_end + i) * 16 + (lane_end & 15)] = acc[rt][i];
     __syncthreads();
-    for (int o = threadIdx.x; o < RTW * 16 * MP; o += W * 64) {
+    for (int o = wave * 64 + lane_end; o < RTW * 16 * MP; o += W * 64) {
         const int rr = o % (RTW * 16), m = o / (RTW * 16);  // rr = rt*16 + r: consecutive threads, consecutive n
         const int rt = rr >> 4, r = rr & 15;
         const SlotOut so = slot_out[rt];
@@ -429,7 +506,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
 template <int MP, int RT, bool kGrouped, int NBC, bool kSub = false, bool kRotated = false, int NSG = 1>
 static int launch_kernel(const GemvArgs& a, int grid, hipStream_t stream) {
     auto kern = gemv_kernel<MP, RT, kGrouped, NBC, kSub, kRotated, NSG>;
-    const size_t lds = (kRotated ? 0 : (size_t)kGemvWaves * MP * 512) + (size_t)kGemvWaves * RT * NSG * MP * 16 * 4 + (size_t)RT * NSG * 32;
+    const size_t lds = (kRotated ? 0 : (size_t)kGemvWaves * MP * kXsRow * 2) + (size_t)kGemvWaves * RT * NSG * MP * 16 * 4 + (size_t)RT * NSG * 32;
     const LaunchTiming tm = take_launch_timing();
     if (tm.start != nullptr) hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kGemvWaves * 64), lds, stream, tm.start, tm.stop, 0, a);
     else hipLaunchKernelGGL(kern, dim3(grid), dim3(kGemvWaves * 64), lds, stream, a);
@@ -447,7 +524,7 @@ static int launch_shape(const GemvArgs& a, int grid, int rt, hipStream_t stream)
     switch (rt) {
         case 1: return launch_one<MP, 1, NBC>(a, grid, stream);
         case 2: return launch_one<MP, 2, NBC>(a, grid, stream);
-        case 3: return launch_one<MP, 3, NBC>(a, grid, stream);
+        case 3: return launch_one<MP, 3, 0>(a, grid, stream);  // (straight-line code for three tiles takes more than 128 registers)
     }
     return -2;
 }
@@ -487,25 +564,15 @@ int launch_gemv(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
     const int64_t nt_total = fill_tensors(a.t, w, count);
     if (nt_total < 0) return -2;
     // Row tiles per workgroup (every workgroup rotates all of X for itself, so more tiles per workgroup
-    // mean less of that; fewer mean more workgroups in flight).  Measured on the 7B and 70B shapes:
-    //  - K = 2048 or 4096 (a wavefront walks one or two blocks; three or four workgroups fit a compute
-    //    unit): the fewest tiles per workgroup that keep the grid within three workgroups per unit;
-    //  - otherwise: as many tiles as keep one workgroup per compute unit busy, at most three.
+    // mean less of that; fewer mean more workgroups in flight): as many as keep one workgroup per compute unit busy, at
+    // most three; two where three would leave units with twice the tiles of others and two do not (between three
+    // and four tiles a unit).  us with one / two / three tiles: three 4096x4096 M = 1 6.2 / 6.6 / 6.2, M = 4 9.2 / 8.0 / 7.0;
+    // two of 4096x11008 M = 1 10.2 / 9.1 / 8.4, M = 4 14.3 / 11.3 / 10.6; 2048x16384 (four tiles a unit) M = 1 5.0 / 4.6 / 5.2, M = 4 6.9 / 5.7 / 6.3.
     const int cus = cu_count();
-    int64_t grid64;
-    if ((a.KB == 8 || a.KB == 16) && a.t[0].subscales == nullptr) {
-        int64_t want = (nt_total + 3 * cus - 1) / (3 * cus);
-        // two to four rows: what a workgroup spends on rotating them counts, so one workgroup per unit where
-        // that covers the launch (three 4096x4096, M = 4: 8.4 us in 768 workgroups of one tile, 7.3 in 256 of three)
-        if (M > 1 && (nt_total + cus - 1) / cus <= kGemvMaxRT) want = (nt_total + cus - 1) / cus;
-        if (want > kGemvMaxRT) want = kGemvMaxRT;
-        grid64 = (nt_total + want - 1) / want;
-    } else {
-        int64_t want = (nt_total + cus - 1) / cus;
-        if (want > kGemvMaxRT) want = kGemvMaxRT;
-        grid64 = (nt_total + want - 1) / want;
-        if (grid64 < cus && nt_total >= cus) grid64 = cus;  // (workgroups then own `want` or `want - 1` tiles)
-    }
+    int64_t want = (nt_total + cus - 1) / cus;
+    if (want > kGemvMaxRT) want = nt_total <= 4 * (int64_t)cus ? 2 : kGemvMaxRT;
+    int64_t grid64 = (nt_total + want - 1) / want;
+    if (grid64 < cus && nt_total >= cus) grid64 = cus;  // (workgroups then own `want` or `want - 1` tiles)
     if (grid64 > 0x7fffffff) return -2;
     const int grid = (int)grid64;
     const int rt = (int)((nt_total + grid - 1) / grid);

@@ -24,9 +24,11 @@ __device__ __forceinline__ floatx4 rotate_f32(half4 xa, const half4& columns, co
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
     const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, columns, zero, 0, 0, 0);
     const half4 th = __builtin_convertvector(T, half4);
+    float minus_one = -1.0f;
+    asm("" : "+s"(minus_one));  // (with the constant in sight the multiply-add becomes a conversion and a subtraction)
     floatx4 rest;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) rest[j] = __builtin_fmaf((float)th[j], -1.0f, T[j]);  // exact
+    for (int j = 0; j < 4; ++j) rest[j] = __builtin_fmaf((float)th[j], minus_one, T[j]);  // exact
     const half4 tl = __builtin_convertvector(rest, half4);
     floatx4 U = __builtin_amdgcn_mfma_f32_16x16x16f16(q, th, zero, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x16f16(q, tl, U, 0, 0, 0);
@@ -52,9 +54,9 @@ __device__ __forceinline__ bool rotate_chunk(const _Float16* __restrict__ src, i
 
 // Operand order of the streaming kernel.  The 16x16x32 MFMA of step t (0..7) takes from lane
 // (column m, k-group g) eight halves; position i of those eight is element
-//     e = 64 g + 16 (t>>1) + 4 (t&1) + (i>>1) + 8 (i&1)
+//     e = 64 g + 16 (i>>1) + t + 8 (i&1)
 // of the chunk, which is where the weight kernel's shift-and-mask unpack puts the code of the same
-// element.  Xt index = (((b*8 + t)*4 + g)*MP + m)*8 + i.   S[b*MP + m] = sum_e x~_e (rounded values),
+// element (a step is one slot of the lane's four low-plane words and the slot eight further).  Xt index = (((b*8 + t)*4 + g)*MP + m)*8 + i.   S[b*MP + m] = sum_e x~_e (rounded values),
 // S[KB*MP + b*MP + m] = 16 x_0 (the same sum before rounding, exact).
 // (at least two wavefronts per SIMD: with a register budget of 256 the matrix instructions write ordinary
 // vector registers; with the full 512 the compiler parks their results in accumulator registers and copies
@@ -85,19 +87,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
         // exact sum of the unrounded chunk: H 1 = 16 e_0 (lane 0 holds x[0] from its operand load)
         S[KB * MP + b * MP + m] = 16.0f * (float)x0;
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int e = 64 * (lane >> 4) + 16 * j + (lane & 15);
-        const int g = e >> 6, w = (e >> 4) & 3, slot = e & 15;
-        const int t = 2 * w + ((slot & 7) >> 2);
-        const int i = 2 * (slot & 3) + (slot >> 3);
-        Xt[(((((int64_t)b * 8 + t) * 4 + g) * MP + m) * 8) + i] = r[j];
-    }
+    // lanes whose slots are 8 apart hold the two halves of the same words: each gives the other half of its words
+    const int slot = lane & 15;
+    const bool upper = (slot & 8) != 0;
+    const u32x2 h = __builtin_bit_cast(u32x2, half4{r[0], r[1], r[2], r[3]});
+    const uint32_t keep = upper ? h.y : h.x, got = (uint32_t)row_xor_i32<8>((int)(upper ? h.x : h.y));
+    *reinterpret_cast<u32x2*>(Xt + ((((int64_t)b * 8 + (slot & 7)) * 4 + (lane >> 4)) * MP + m) * 8 + (upper ? 4 : 0)) =
+        u32x2{__builtin_amdgcn_perm(keep, got, upper ? 0x05040100u : 0x01000504u), __builtin_amdgcn_perm(keep, got, upper ? 0x07060302u : 0x03020706u)};
 }
 
 // Operand order of the streaming kernel for 17 and more rows (itq3s_rows.hip): rows in groups of 16 mt, a
 // group's fragments (t, mt) of a block one after another, 1 KiB each -- lane l = 16 g + r of the MFMA
-// operand finds its eight halves, the same elements as above, at 16 l.
+// operand finds its eight halves, e = 64 g + 16 (t>>1) + 4 (t&1) + (i>>1) + 8 (i&1), at 16 l.
 //   Xt index = ((((group*KB + b)*8 + t)*mts + mt)*64 + l)*8 + i,   row m = (group*mts + mt)*16 + r
 //   X0 index = ((group*KB + b)*4 + q)*stride + 4 mt + i = x[(group*mts + mt)*16 + 4 q + i][256 b], stride 8 for
 //              mts <= 2, else 16
