@@ -359,6 +359,7 @@ int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
     const int rc = launch_rotate_rows(X, M, K, ldx, mt, groups, Xt, X0, flags, stream);
     if (rc != 0) return rc;
     switch (mt) {
+        case 1: return launch_rows_mt<1>(a, rt, stream);
         case 2: return launch_rows_mt<2>(a, rt, stream);
         case 3: return launch_rows_mt<3>(a, rt, stream);
         case 4: return launch_rows_mt<4>(a, rt, stream);

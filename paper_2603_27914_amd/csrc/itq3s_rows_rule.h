@@ -10,6 +10,7 @@ constexpr int64_t kRowsMinM = 17;  // fewer rows: the streaming kernel of itq3s_
 constexpr int64_t kRowsMaxM = 1 << 16;
 constexpr int64_t kRowsMaxK = 1 << 18;
 constexpr int kRowsWaves = 8;  // wavefronts per workgroup
+constexpr int64_t kRowsMaxM1 = 96;  // groups of 16 rows up to here (beyond, their first elements could take more than rows_x0_bytes)
 constexpr int kRowsMaxRT = 4;  // row tiles per item, at most (256 registers with 64 rows)
 
 // Rows per group (16 mt) and row tiles per item (rt): the pair that takes the least time in rounds of one
@@ -24,7 +25,10 @@ struct RowsSplit {
 inline RowsSplit rows_split(int64_t row_tiles, int64_t M, int64_t K, int units) {
     const int64_t steps = (K / 256 + kRowsWaves - 1) / kRowsWaves;
     RowsSplit best{2, 1, 0, 0, INT64_MAX};
-    for (int m = 2; m <= 4; ++m) {
+    // Groups of 16 rows: thin tensors, which leave units idle otherwise (with all rows to a unit, all of the activations go through
+    // each of the few units at 53 bytes a clock).  us without / with: 4096x1024 M = 48 8.6 / 7.1, 11008x512 M = 64 13.8 / 10.9,
+    // 28672x1024 M = 24 33.3 / 22.5.  Not beyond what a chiplet's L2 holds (4 MB): 28672x1024 M = 64 33.8 / 24.3, M = 80 34.4 / 35.7.
+    for (int m = M <= kRowsMaxM1 && M * K <= 2000000 ? 1 : 2; m <= 4; ++m) {
         const int64_t groups = (M + 16 * m - 1) / (16 * m);
         for (int r = 1; r <= kRowsMaxRT; ++r) {
             const int64_t items = (row_tiles + r - 1) / r * groups, rounds = (items + units - 1) / units;
@@ -35,7 +39,7 @@ inline RowsSplit rows_split(int64_t row_tiles, int64_t M, int64_t K, int units) 
     return best;
 }
 
-// Activation rows padded to whole groups of 32, 48 or 64: the most of the three.
+// Activation rows padded to whole groups of 32, 48 or 64: the most of the three (groups of 16 take no more).
 inline int64_t rows_padded(int64_t M) {
     int64_t most = 0;
     for (int mt = 2; mt <= 4; ++mt) {
@@ -45,7 +49,7 @@ inline int64_t rows_padded(int64_t M) {
     return most;
 }
 inline size_t rows_xt_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)K * 2; }
-inline size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)(K / 256) * 3; }  // 64 bytes per 32 rows, 128 per 48 or 64
+inline size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M) * (size_t)(K / 256) * 3; }  // 64 bytes per 16 or 32 rows, 128 per 48 or 64
 
 // Which calls this kernel may take (many_row_route decides between it and the block-scaled ones, whose times are of the
 // same form; where it may not, they take the call whatever their time).  Beyond 64 rows up to 36 GFLOP and 3.4 million
@@ -56,7 +60,7 @@ inline size_t rows_x0_bytes(int64_t M, int64_t K) { return (size_t)rows_padded(M
 //  - more than 1280 rows: every round more reads the rotated activations through every chiplet's L2 again, which
 //    does not hold them (N = 1000, K = 4096: M = 1024, one round, 24; 1500, two, 41; 2048, two, 52).
 //  - 17 rows of a thin tensor with long K: two passes of the kernel for 16 rows, whose second rotates its one row
-//    in the kernel, are 4 to 10 % faster (N = 16, K = 28672 30.5 / 27.8).
+//    in the kernel, were 4 to 10 % faster than groups of 32 rows (N = 16, K = 28672 27.8 / 30.5).
 // A rule on the sizes of one tensor (counted for 256 units): a grouped call computes every tensor as a call
 // of its own does.
 inline bool rows_path(int64_t M, int64_t N, int64_t K) {

@@ -105,6 +105,21 @@ def test_many_rows_flags(gpu):
     assert int(flags.item()) == binding.FLAG_ACT_RANGE
 
 
+# one, two, three and four row tiles to an item of 16 rows; wavefronts without a block; the last group with one row
+@pytest.mark.parametrize("M,N,K", [(17, 200, 512), (33, 100, 2304), (24, 4100, 4096), (32, 8200, 2560), (48, 16500, 1792), (81, 520, 11008), (96, 33, 20480), (17, 1040, 1024)])
+def test_groups_of_sixteen_rows(gpu, M, N, K):
+    """A thin tensor alone goes in groups of 16 rows, beside a wide one in larger ones: the same bits."""
+    torch, binding = gpu
+    codes, scales, What = tensor(torch, binding, N, K, "sixteen", M)
+    wide = tensor(torch, binding, 4096, K, "sixteen-wide", M)
+    X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
+    Y = binding.itq3s_matmul(codes, scales, N, K, X)
+    check(Y, X, What, False)
+    a, b = binding.itq3s_matmul_grouped([(codes, scales, N), (*wide[:2], 4096)], K, X, dtype=torch.float32)
+    assert torch.equal(a, Y)
+    check(b, X, wide[2], False)
+
+
 @pytest.mark.parametrize("M,N,K,less", [(17, 1000, 4096, "pass"), (32, 100, 11008, "pass"), (64, 33000, 256, "tiled")])
 def test_room_for_the_other_routes_is_still_enough(gpu, M, N, K, less):
     """A call whose workspace has room for the passes of 16 rows or for the tiled kernel (no padded rows: sized
