@@ -60,7 +60,7 @@ extern "C" {
 #define ITQ3S_FLAG_Z_CLAMP 4u   /* quantize: |z| exceeded 2048 and was clamped                     */
 #define ITQ3S_FLAG_BAD_CODE 8u  /* decode: a code outside {0,1,2} was met (dequantize checks both
                                    planes; matmul checks the high plane only and treats a low-plane
-                                   3 as digit +2)                                                  */
+                                   3 as digit +2; itq3s_matmul_sub up to 64 rows: as +3)           */
 #define ITQ3S_FLAG_ACT_RANGE 16u /* matmul: a rotated activation left the fp16 range (see itq3s_matmul);
                                    the outputs that depend on that 256-channel chunk are Inf or NaN */
 

@@ -15,10 +15,11 @@
 //
 // Contraction: v_mfma_f32_16x16x32_f16 with the activations as the A operand (rows = m) and 16
 // weight rows of a tile as the B operand (columns = n), so that every accumulator of a lane belongs
-// to the lane's own weight row and needs only that row's scale.  A code c in {0,1,2} placed in bits
-// 11:10 of a half is the number c * 2^-14, in bits 9:8 c * 2^-16 (fp16's subnormal numbers take part in the products
-// unchanged), so a shift of a low-plane word by a multiple of four gives two half2 operands with one mask each; the factors
-// are applied together with d.  Four-row decode is bound by this arithmetic (two of 4096x11008, M = 4: 5.5 us of
+// to the lane's own weight row and needs only that row's scale.  A code c placed in bits
+// 10:9 of a half is the number c * 2^-15, in bits 8:7 c * 2^-17 (fp16's subnormal numbers take part in the products
+// unchanged, but the products are added up with the bits that stand in front of them missing, so not further down;
+// further up, at bits 11:10, a stored 3 would count as 4), so a shift of a low-plane word by a
+// multiple of four gives two half2 operands with one mask each; the factors are applied together with d.  Four-row decode is bound by this arithmetic (two of 4096x11008, M = 4: 5.5 us of
 // vector instructions in a launch of 11): the two positions took a sixth off a tile's share, and the rows
 // are rotated together, two by two, instead of one after another.  us, before / now (K x N): 11008x4096 M = 1 7.0 / 6.6, M = 4 9.5 / 8.6;
 // 28672x8192 M = 1 18.8 / 17.9, M = 4 25.0 / 22.5; 8192x57344 M = 4 39.5 / 36.5; 5120x5120 M = 4 7.4 / 6.8.
@@ -343,14 +344,14 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
             }
         }
         // Slots s and s + 8 of a low-plane word are 16 bits apart.  Shifted by a multiple of four the word has one pair at bits
-        // 11:10 (odd s: the halves c 2^-14) and one at 9:8 (even s: c 2^-16, in a sum of its own that counts four times):
-        // eleven instructions a word instead of fifteen with a shift for each pair.  (The sub-scaled operands, whose
+        // 10:9 (odd s: the halves c 2^-15) and one at 8:7 (even s: c 2^-17, in a sum of its own that counts four times):
+        // twelve instructions a word instead of sixteen with a shift for each pair.  (The sub-scaled operands, whose
         // range ends at fp16's, all come from bits 11:10.)
         auto fragment = [&](int t) -> half8 {
             if constexpr (kRotated) return xf[t];
             else return *reinterpret_cast<const half8*>(xs_src + 8 * t);
         };
-        constexpr uint32_t kMask = 0x0C000C00u;
+        constexpr uint32_t kSubMask = 0x0C000C00u, kOddMask = 0x06000600u, kEvenMask = 0x01800180u;
         auto shifted = [](uint32_t v, int by) -> uint32_t { return by >= 0 ? v << by : v >> -by; };
         if constexpr (kSub) {
 #pragma unroll
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     const u32x4 v = s.t[rt].lo;
-                    half8 op = as_half8(shifted(v.x, 10 - 2 * t) & kMask, shifted(v.y, 10 - 2 * t) & kMask, shifted(v.z, 10 - 2 * t) & kMask, shifted(v.w, 10 - 2 * t) & kMask);
+                    half8 op = as_half8(shifted(v.x, 10 - 2 * t) & kSubMask, shifted(v.y, 10 - 2 * t) & kSubMask, shifted(v.z, 10 - 2 * t) & kSubMask, shifted(v.w, 10 - 2 * t) & kSubMask);
                     op = __builtin_elementwise_fma(op, sub_mul[rt], sub_add[rt]);
                     c[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xf, op, c[rt], 0, 0, 0);
                 }
@@ -379,9 +380,9 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     const u32x4 lo = s.t[rt].lo;
-                    const uint32_t v[4] = {shifted(lo.x, 8 - 4 * p), shifted(lo.y, 8 - 4 * p), shifted(lo.z, 8 - 4 * p), shifted(lo.w, 8 - 4 * p)};
-                    c[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xo, as_half8(v[0] & kMask, v[1] & kMask, v[2] & kMask, v[3] & kMask), c[rt], 0, 0, 0);
-                    ce[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xe, as_half8(v[0] & (kMask >> 2), v[1] & (kMask >> 2), v[2] & (kMask >> 2), v[3] & (kMask >> 2)), ce[rt], 0, 0, 0);
+                    const uint32_t v[4] = {shifted(lo.x, 7 - 4 * p), shifted(lo.y, 7 - 4 * p), shifted(lo.z, 7 - 4 * p), shifted(lo.w, 7 - 4 * p)};
+                    c[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xo, as_half8(v[0] & kOddMask, v[1] & kOddMask, v[2] & kOddMask, v[3] & kOddMask), c[rt], 0, 0, 0);
+                    ce[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Xe, as_half8(v[0] & kEvenMask, v[1] & kEvenMask, v[2] & kEvenMask, v[3] & kEvenMask), ce[rt], 0, 0, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(kGemvWaves * 64, NBC > 0 ? 3 : (MP == 8 && !kRotate
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 acc[SG * RT + rt][i] = kSub       ? __builtin_fmaf(d, __builtin_fmaf(c[rt][i], 1024.0f, -z * ev[i]), acc[SG * RT + rt][i])
-                                                  : __builtin_fmaf(d, __builtin_fmaf(c[rt][i], 16384.0f, -__builtin_fmaf(z, ev[i], sv[i])), acc[SG * RT + rt][i]);
+                                                  : __builtin_fmaf(d, __builtin_fmaf(c[rt][i], 32768.0f, -__builtin_fmaf(z, ev[i], sv[i])), acc[SG * RT + rt][i]);
         }
     };
     auto compute = [&](const Slot& s) { compute_sg(s, std::integral_constant<int, 0>{}); };

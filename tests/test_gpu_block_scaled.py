@@ -140,3 +140,23 @@ def test_scales_of_the_activations(gpu):  # noqa: F811
     Y = binding.itq3s_matmul(codes, scales, N, K, X)
     assert bool((Y[0] == 0).all())
     check(torch, Y, X, What, False)
+
+
+# M <= 4 (straight-line code and not), 5 to 16, the many-row kernel
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(1, 200, 4096), (4, 200, 2816), (16, 200, 1024), (48, 500, 4096)])
+def test_code_three_counts_as_two(gpu, M, N, K):  # noqa: F811
+    """A low-plane 3 is the digit +2 in every slot of a word (the header's promise), as in itq3s_dequantize."""
+    torch, binding = gpu
+    codes, scales, _ = tensor(torch, binding, N, K, "three", M)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    words = codes.view(-1, 384)[:, :256]
+    shape = tuple(words.shape) + (16,)
+    hit = (torch.rand(shape, generator=gen, device="cuda") < 0.03) << (2 * torch.arange(16, device="cuda"))
+    hit = hit.sum(dim=-1)
+    words |= (hit | hit << 1).to(torch.int32)
+    What = binding.itq3s_dequantize(codes, scales, N, K).double()
+    X = torch.randn((M, K), generator=gen, device="cuda").half()
+    Y = binding.itq3s_matmul(codes, scales, N, K, X).double()
+    want = X.double() @ What.T
+    assert ((Y - want).norm() / want.norm()).item() <= 4e-4  # (2^-11 / sqrt(3) where x~ is rounded to fp16)
