@@ -61,11 +61,12 @@ __device__ __forceinline__ half4 hadamard_quarter(int lane) {
     return __builtin_bit_cast(half4, u32x2{w0, w1});
 }
 
-// fp4 operands of the block-scaled products: the codes c of a low-plane word's even slots (bits 1:0 of its nibbles)
-// as c / 2, those of its odd slots (bits 3:2) as -2 (c - 1); and the scales of B that go with them and the three parts
-// of A (bytes 0..2: 2^(1, -3, -8) and 2^(-1, -5, -10)).
+// fp4 operands of the block-scaled products: the codes c of a low-plane word's even slots (bits 1:0 of its nibbles) and
+// of its odd slots (bits 3:2), as c / 2 (0, 0.5, 1, and 1.5 for a 3: the format's one linear run of codes, so the odd ones
+// take a shift more than they would as 2, 0, -2); and the scales of B that go with them and the three parts of A (bytes
+// 0..2: 2^(1, -3, -8)).
 __device__ __forceinline__ uint32_t even_digits(uint32_t v) { return v & 0x33333333u; }
-__device__ __forceinline__ uint32_t odd_digits(uint32_t v) { return (v ^ 0x44444444u) & 0xCCCCCCCCu; }
-constexpr int kEvenScales = 0x00777c80, kOddScales = 0x00757a7e;
+__device__ __forceinline__ uint32_t odd_digits(uint32_t v) { return (v >> 2) & 0x33333333u; }
+constexpr int kDigitScales = 0x00777c80;
 
 }  // namespace itq3s

@@ -1,5 +1,5 @@
 // Tiled matmul for the calls with more activation rows or larger products than the streaming kernels take (the prefill
-// path).  Operands and arithmetic are those of itq3s_mx.hip: digits in fp4 as they are stored, rotated activations in three
+// path).  Operands and arithmetic are those of itq3s_mx.hip: codes in fp4 as they are stored, rotated activations in three
 // parts of fp6 with a power of two per 32 channels, a block's sum apart because its scale belongs to a column and a block.
 //
 //   Y[m][n] = sum_b d ( sum_j q[n,b,j] x~[m,b,j]  -  z E[m,b] ),   q = c - 1,  E[m,b] = 16 x[m][256 b]
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int v = 0; v < 16; ++v) acc[n][v] = 0.f;
     int scale_a = 0;
     float d[NT];
-    const int scale_even = kEvenScales, scale_odd = kOddScales;
+    const int scale_w = kDigitScales;
     constexpr std::integral_constant<int, 0> c0{};
     constexpr std::integral_constant<int, 1> c1{};
     constexpr std::integral_constant<int, 2> c2{};
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     auto product = [&](const u32x4 (&fa)[3], const u32x2 (&ft)[3], auto qc, auto pc, int n) {
         constexpr int q = decltype(qc)::value, p = decltype(pc)::value;
         const i32x8 a = {(int)fa[p].x, (int)fa[p].y, (int)fa[p].z, (int)fa[p].w, (int)ft[p].x, (int)ft[p].y, 0, 0};
-        blk[n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, op[n], q == 0 && p == 0 ? neg_s : blk[n], 2, 4, q, scale_a, p, q % 2 == 0 ? scale_even : scale_odd);
+        blk[n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, op[n], q == 0 && p == 0 ? neg_s : blk[n], 2, 4, q, scale_a, p, scale_w);
     };
     // a step's products; behind the last one of a column its digits for the next step
     auto all = [&](const u32x4 (&fa)[3], const u32x2 (&ft)[3], auto qc, auto next_step) {
@@ -196,8 +196,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             unpack(n, next_step);
         }
     };
-    auto order = [&](auto reads, auto head) {
-        constexpr int kReads = decltype(reads)::value, kHead = decltype(head)::value;
+    auto order = [&](auto reads, auto head, auto next_step) {
+        constexpr int kReads = decltype(reads)::value, kHead = decltype(head)::value, kUnpack = decltype(next_step)::value == 0 ? 4 : 8;
         __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, kUnpack, 0);
         }
     };
     constexpr std::integral_constant<int, NT + 6> first_reads{};
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
             for (int n = 0; n < NT; ++n) unpack(n, c0);
         }
-        order(first_reads, c0);
+        order(first_reads, c0, c0);
         ITQ3S_FENCE;
         copy_half(b, c1);
         float dl[NT];
@@ -286,20 +286,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 for (int v = 0; v < 16; ++v) acc[n][v] = __builtin_fmaf(dl[n], blk[n][v], acc[n][v]);
         }
         all(a0, t0, c0, c1);
-        order(second_reads, sixteen);
+        order(second_reads, sixteen, c1);
         ITQ3S_FENCE;
         // second half
         sync();
         load_w(1);
         load_a(a0, t0, 1, 0);
         all(a1, t1, c1, c0);
-        order(first_reads, c0);
+        order(first_reads, c0, c0);
         ITQ3S_FENCE;
         copy_half(b + 1, c0);
         ITQ3S_FENCE;
         load_a(a1, t1, 1, 1);
         all(a0, t0, c2, c1);
-        order(second_reads, c0);
+        order(second_reads, c0, c1);
         ITQ3S_FENCE;
     }
     if (have_z) zero_points(KB - 1);

@@ -3,16 +3,16 @@
 //
 //   Y[m][n] = sum_b d ( sum_j q[n,b,j] x~[m,b,j]  -  z E[m,b] ),   q = c - 1,  E[m,b] = 16 x[m][256 b]
 //
-// The digits are fp4 as they are stored: the codes of a low-plane word's even slots, masked (one instruction for eight
-// codes), are 0, 0.5 and 1; those of its odd slots, masked and with one bit flipped (one instruction), 2, 0 and -2.  So
-// no digit is ever built, where the fp16 operands took 13 instructions for eight weights.  The rotated activations x~ come
+// The codes are fp4 as they are stored: those of a low-plane word's even slots, masked (one instruction for eight
+// codes), are 0, 0.5 and 1; those of its odd slots after a shift.  So no digit is ever built, where the fp16 operands
+// took 13 instructions for eight weights.  The rotated activations x~ come
 // in three parts of fp6 (four significant bits each) with one power of two per 32 channels of a row: x~ = 2^e (p0 + p1 / 16
 // + p2 / 512), the remainder at most 2^-13 of the group's largest value, 4.4e-5 of the values' deviation on normal
 // ones (fp16, before: 2e-4; errors of whole products, fp32 results, 3.5e-5 against 2.2e-4).  v_mfma_scale_f32_32x32x64_f8f6f4
-// runs fp6 x fp4 at four times the fp16 rate, so three products take 0.75 of one in fp16.  Odd slots are stored negated;
-// the even ones' offset (code 1 = digit 0) is taken back by starting a block's sum at -S, S the sum of the even slots'
-// parts.  A block's sum is a sum of its own (32 x 32 outputs in 16 registers) because its scale d belongs to a
-// column and a block: one fused multiply-add per output and block.
+// runs fp6 x fp4 at four times the fp16 rate, so three products take 0.75 of one in fp16.  The codes'
+// offset (code 1 = digit 0) is taken back by starting a block's sum at -S, S the sum of its activations' parts.  A
+// block's sum is a sum of its own (32 x 32 outputs in 16 registers) because its scale d belongs to a column and a
+// block: one fused multiply-add per output and block.
 //
 // Work split: a workgroup of eight wavefronts owns 32 rows and 32 NT (KS = 8) or 64 NT (KS = 4) columns; wavefront w takes blocks
 // w / (8 / KS), + KS, ... of all of K and keeps 32 x 32 NT sums; one sum over the KS wavefronts through LDS at the end, no
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void mx_kernel(const MxArgs args)
         for (int v = 0; v < 16; ++v) acc[n][v] = 0.f;
     int scale_a = 0;
     float d[NT];
-    const int scale_even = kEvenScales, scale_odd = kOddScales;
+    const int scale_w = kDigitScales;
     constexpr std::integral_constant<int, 0> c0{};
     constexpr std::integral_constant<int, 1> c1{};
     constexpr std::integral_constant<int, 2> c2{};
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void mx_kernel(const MxArgs args)
             auto part = [&](auto pc) {
                 constexpr int p = decltype(pc)::value;
                 const i32x8 a = {(int)fa[p].x, (int)fa[p].y, (int)fa[p].z, (int)fa[p].w, (int)ft[p].x, (int)ft[p].y, 0, 0};
-                blk[n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, op, q == 0 && p == 0 ? neg_s : blk[n], 2, 4, q, scale_a, p, q % 2 == 0 ? scale_even : scale_odd);
+                blk[n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, op, q == 0 && p == 0 ? neg_s : blk[n], 2, 4, q, scale_a, p, scale_w);
             };
             part(c0);
             part(c1);
@@ -250,10 +250,10 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void mx_kernel(const MxArgs args)
 
 #define ITQ3S_FENCE __builtin_amdgcn_sched_barrier(0)
     // the loads between the products: issued in a row they fill the address unit's queue, and the wavefront stands
-    auto spread = [&]() {
+    auto spread = [&](auto qc) {
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, decltype(qc)::value % 2 == 0 ? 4 : 8, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -280,21 +280,21 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void mx_kernel(const MxArgs args)
         issue_a(a1, t1, cur, b, 1);
         issue_w(w1, cur, b, 1);
         multiply(a0, t0, w0, c0);
-        spread();
+        spread(c0);
         ITQ3S_FENCE;
         issue_a(a0, t0, cur, b, 2);
         multiply(a1, t1, w0, c1);
-        spread();
+        spread(c1);
         ITQ3S_FENCE;
         issue_a(a1, t1, cur, b, 3);
         issue_w(w0, nxt, bn, 0);
         issue_m(nxt, bn);
         multiply(a0, t0, w1, c2);
-        spread();
+        spread(c2);
         ITQ3S_FENCE;
         issue_a(a0, t0, nxt, bn, 0);
         multiply(a1, t1, w1, c3);
-        spread();
+        spread(c3);
         ITQ3S_FENCE;
         end_block();
         ITQ3S_FENCE;

@@ -20,9 +20,9 @@ namespace itq3s {
 // elements e = 64 (l/16) + 16 i + l%16, i = 0..3.
 // Returns false if a rotated value (or the intermediate T, which then turns the result into NaN)
 // leaves the fp16 range.
-__device__ __forceinline__ floatx4 rotate_f32(half4 xa, const half4& columns, const half4& q) {  // columns: q, or with columns negated
+__device__ __forceinline__ floatx4 rotate_f32(half4 xa, const half4& q) {
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-    const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, columns, zero, 0, 0, 0);
+    const floatx4 T = __builtin_amdgcn_mfma_f32_16x16x16f16(xa, q, zero, 0, 0, 0);
     const half4 th = __builtin_convertvector(T, half4);
     float minus_one = -1.0f;
     asm("" : "+s"(minus_one));  // (with the constant in sight the multiply-add becomes a conversion and a subtraction)
@@ -35,7 +35,7 @@ __device__ __forceinline__ floatx4 rotate_f32(half4 xa, const half4& columns, co
 }
 __device__ __forceinline__ bool rotate_operand(half4 xa, int lane, _Float16 out[4]) {
     const half4 q = hadamard_quarter(lane);
-    const floatx4 U = rotate_f32(xa, q, q);
+    const floatx4 U = rotate_f32(xa, q);
     const half4 r = __builtin_convertvector(U, half4);
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[i] = r[i];
@@ -158,14 +158,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         xa[rr] = half4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
         if (m < M) xa[rr] = *reinterpret_cast<const half4*>(X + (int64_t)m * ldx + (int64_t)b * kBlock + 16 * (lane & 15) + 4 * (lane >> 4));
     }
-    // element 64 q + 16 i + s (q = lane / 16, s = lane % 16) -> group 2 q + s % 2, place 8 i + s / 2; odd s negated
-    // (a result's slot is its column in the first product, where the sign costs nothing)
+    // element 64 q + 16 i + s (q = lane / 16, s = lane % 16) -> group 2 q + s % 2, place 8 i + s / 2
     const half4 q = hadamard_quarter(lane);
-    const uint32_t flip = (lane & 1) != 0 ? 0x80008000u : 0u;
-    const half4 columns = __builtin_bit_cast(half4, __builtin_bit_cast(u32x2, q) ^ u32x2{flip, flip});
 #pragma unroll
     for (int rr = 0; rr < 8; ++rr) {
-        const floatx4 U = rotate_f32(xa[rr], columns, q);
+        const floatx4 U = rotate_f32(xa[rr], q);
         float* const dst = rows + rr * kMxRowStride + (2 * (lane >> 4) + (lane & 1)) * 36 + ((lane & 15) >> 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) dst[8 * i] = U[i];
@@ -190,12 +187,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     }
     if (sample != nullptr && tile * 32 < (int)kMxSampleRows) {  // (uniform) of every sixteen channels the even slots, then the odd ones
         _Float16* const to = sample + ((int64_t)(tile * 32 + wave * 8 + r8) * KB + b) * kBlock + 64 * (group >> 1) + 8 * odd;
-        const float sign = odd != 0 ? -1.0f : 1.0f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             half8 h;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) h[j] = (_Float16)(sign * (j % 2 == 0 ? r0[4 * i + j / 2] : r1[4 * i + j / 2]));
+            for (int j = 0; j < 8; ++j) h[j] = (_Float16)(j % 2 == 0 ? r0[4 * i + j / 2] : r1[4 * i + j / 2]);
             *reinterpret_cast<half8*>(to + 16 * i) = h;
         }
     }
@@ -234,7 +230,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     }
     sum += sum1;
     if (!ok) sum = __builtin_nanf("");
-    // -S: over the four groups of even slots
+    // -S: over the eight groups
+    sum += xor_lane_f32(sum, 8);
     sum += xor_lane_f32(sum, 16);
     sum += xor_lane_f32(sum, 32);
     if (lane < 8) *reinterpret_cast<float*>(meta + 256 + (8 * wave + r8) * 4) = -sum;

@@ -142,11 +142,11 @@ def test_scales_of_the_activations(gpu):  # noqa: F811
     check(torch, Y, X, What, False)
 
 
-# M <= 4 (straight-line code and not), 5 to 16, the many-row kernel
+# M <= 4 (straight-line code and not), 5 to 16, the many-row kernel, K over 8 and over 4 wavefronts, tiles
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", [(1, 200, 4096), (4, 200, 2816), (16, 200, 1024), (48, 500, 4096)])
+@pytest.mark.parametrize("M,N,K", [(1, 200, 4096), (4, 200, 2816), (16, 200, 1024), (48, 500, 4096), (500, 1000, 4096), (512, 4096, 4096), (640, 4100, 2560)])
 def test_code_three_counts_as_two(gpu, M, N, K):  # noqa: F811
-    """A low-plane 3 is the digit +2 in every slot of a word (the header's promise), as in itq3s_dequantize."""
+    """A low-plane 3 is the digit +2 in every slot of a word, on every path (the header's promise), as in itq3s_dequantize."""
     torch, binding = gpu
     codes, scales, _ = tensor(torch, binding, N, K, "three", M)
     gen = torch.Generator(device="cuda").manual_seed(M)
