@@ -85,7 +85,7 @@ size_t rows_workspace(int64_t M, int64_t K) { return round_up(itq3s::rows_xt_byt
 size_t mx_workspace(int64_t M, int64_t K) { return itq3s::mx_sample_bytes(M, K) + itq3s::mx_bytes(M, K); }
 
 // The block-scaled kernels over the tensors that each of them takes, in as many slabs of rows as the room asks for (a
-// row's results do not depend on the others).  The room holds 32 rows.
+// row's results do not depend on those beyond its tile of 32).  The room holds 32 rows.
 int launch_mx_routes(const itq3s_weight* w, const itq3s::Route* route, int count, int64_t K, const _Float16* X, int64_t M, int64_t ldx, int y_f16,
                      unsigned char* base, size_t room, uint32_t* flags, hipStream_t st) {
     int64_t slab = M;

@@ -30,6 +30,8 @@
 
 #include "itq3s_dev.h"
 #include "itq3s_kernels.h"
+#include "itq3s_mx_wide.h"
+#include "itq3s_stream.h"
 
 namespace itq3s {
 
@@ -196,6 +198,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             unpack(n, next_step);
         }
     };
+    uint32_t any_wide = 0;
     auto order = [&](auto reads, auto head, auto next_step) {
         constexpr int kReads = decltype(reads)::value, kHead = decltype(head)::value, kUnpack = decltype(next_step)::value == 0 ? 4 : 8;
         __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
@@ -220,6 +223,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     auto begin_block = [&](int b) -> bool {
         const char* const meta = lds + kMeta + (b & 1) * 1024 + wm * kMxMetaBytes;
         scale_a = *reinterpret_cast<const int*>(meta + lane * 4);
+        any_wide |= wide_steps((uint32_t)__builtin_amdgcn_readfirstlane(scale_a));
         uint32_t any = 0;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
@@ -308,6 +312,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int n = 0; n < NT; ++n)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[n][v] = __builtin_fmaf(d[n], blk[n][v], acc[n][v]);
+    if (any_wide != 0 && wm < x_tiles) {  // (no second tile of 32 rows: its scales are read as 0 too)
+        const int64_t tile0 = nt0 + wn * (2 * NT);
+        const int rows = tensor_tiles - tile0 < 2 * NT ? (tensor_tiles > tile0 ? (int)(tensor_tiles - tile0) : 0) : 2 * NT;
+        const int64_t from = rows > 0 ? tile0 * KB : 0;
+        add_wide_steps<NT>(
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(args.Xm + (int64_t)(2 * tm + wm) * KB * kMxBlockBytes), 0, wm < x_tiles ? KB * kMxBlockBytes : 0, kRawBuffer),
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(codes + from * kTileWords), 0, rows * KB * (kTileWords * 4), kRawBuffer),
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(scales + from * kTileRows), 0, rows * KB * (kTileRows * 4), kRawBuffer), 0, 1, KB,
+            (l32 >> 4) * KB * (kTileWords * 4) + kg * 256 + (l32 & 15) * 16, 2 * KB * (kTileWords * 4), (l32 >> 4) * KB * (kTileRows * 4) + (l32 & 15) * 4,
+            2 * KB * (kTileRows * 4), acc);
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the copies beyond the last block are into this workgroup's LDS too)
 #undef ITQ3S_FENCE
 

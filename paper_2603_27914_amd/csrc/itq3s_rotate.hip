@@ -146,6 +146,7 @@ typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void rotate_mx_kernel(const _Float16* __restrict__ X, int M, int KB, int64_t ldx,
                                                               unsigned char* __restrict__ Xm, _Float16* __restrict__ sample, uint32_t* __restrict__ flags) {
     __shared__ __align__(16) float lds[4][8 * kMxRowStride];
+    __shared__ uint32_t votes[4];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int tile = (int)blockIdx.x / KB, b = (int)blockIdx.x - tile * KB;  // tile of 32 rows
     unsigned char* const out = Xm + ((int64_t)tile * KB + b) * kMxBlockBytes;
@@ -207,35 +208,78 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     // scale 2^e with peak / 2^e in (3.75, 7.5], the largest value of the format
     uint32_t e8 = (bits >> 23) - 2u + ((bits & 0x7fffffu) > 0x700000u ? 1u : 0u);
     if (peak == 0.f || !ok) e8 = 127u;
+    // Three parts leave the small values of a group an error of 1.3e-5 of its largest one (root mean square), fp16 2.1e-4 of
+    // themselves: the same where the largest is 16 times the others' deviation, 24 times their median.  Where the most
+    // are far below it (17 of the 32 below 2^-5 of it), the step's 64 channels of all 32 rows are fp16: activations with
+    // an offset, say, rotate to one large value in a block, and the outputs whose digit there is 0 are made of
+    // the others.  Such outputs, offset 0 / 1 / 4 / 30 deviations: 3.4e-5, 1.1e-4, 1.1e-4, 7e-5 (x~ in fp16 alone 2.1e-4, 2.1e-4, 2.1e-4,
+    // 1.5e-4; without fp16 steps 3.4e-5, 1e-4, 4e-4, 2.5e-3).  Normal activations have no such step in 10^5.
+    int small = 0;
+    const float few = peak * 0.03125f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        small += __builtin_fabsf(r0[k]) < few ? 1 : 0;
+        small += __builtin_fabsf(r1[k]) < few ? 1 : 0;
+    }
+    const uint64_t vote = __builtin_amdgcn_ballot_w64(ok && small > 16);
+    if (lane == 0) {  // (a byte a group; step s has groups s + s / 2 * 2 and two further)
+        uint32_t v = 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) v |= (vote & (0x00ff00ffull << (8 * (s + s / 2 * 2)))) != 0 ? 1u << s : 0u;
+        votes[wave] = v;
+    }
+    __syncthreads();
+    const bool wide = (((votes[0] | votes[1] | votes[2] | votes[3]) >> step) & 1u) != 0;
     const int at = 32 * kg + 8 * wave + r8;  // lane of the products
     unsigned char* const frag = out + step * kMxStepBytes;
+    if (wide) {  // eight halves for each nibble of the lane's four words, in the place of the parts' bytes
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        const float scale = __builtin_bit_cast(float, (e8 - (p == 0 ? 0u : p == 1 ? 4u : 9u)) << 23);
-        const u32x6 packed = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(r0, r1, scale);
-        const floatx32 back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(packed, scale);
+        for (int p = 0; p < 4; ++p) {
+            half8 h;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            r0[k] -= back[2 * k];
-            r1[k] -= back[2 * k + 1];
+            for (int j = 0; j < 8; ++j) {  // place 8 (j / 2) + p + 4 (j % 2)
+                const int k = 4 * (j / 2) + p / 2 + 2 * (j % 2);
+                h[j] = (_Float16)(p % 2 == 0 ? r0[k] : r1[k]);
+            }
+            const u32x4 w = __builtin_bit_cast(u32x4, h);
+            if (p < 3) {
+                *reinterpret_cast<u32x4*>(frag + p * kMxPartBytes + at * 16) = w;
+            } else {
+                *reinterpret_cast<u32x2*>(frag + 1024 + at * 8) = u32x2{w.x, w.y};
+                *reinterpret_cast<u32x2*>(frag + kMxPartBytes + 1024 + at * 8) = u32x2{w.z, w.w};
+                *reinterpret_cast<u32x2*>(frag + 2 * kMxPartBytes + 1024 + at * 8) = u32x2{0u, 0u};
+            }
         }
-        *reinterpret_cast<u32x4*>(frag + p * kMxPartBytes + at * 16) = u32x4{packed[0], packed[1], packed[2], packed[3]};
-        *reinterpret_cast<u32x2*>(frag + p * kMxPartBytes + 1024 + at * 8) = u32x2{packed[4], packed[5]};
+    } else {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const float scale = __builtin_bit_cast(float, (e8 - (p == 0 ? 0u : p == 1 ? 4u : 9u)) << 23);
+            const u32x6 packed = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(r0, r1, scale);
+            const floatx32 back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(packed, scale);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                r0[k] -= back[2 * k];
+                r1[k] -= back[2 * k + 1];
+            }
+            *reinterpret_cast<u32x4*>(frag + p * kMxPartBytes + at * 16) = u32x4{packed[0], packed[1], packed[2], packed[3]};
+            *reinterpret_cast<u32x2*>(frag + p * kMxPartBytes + 1024 + at * 8) = u32x2{packed[4], packed[5]};
+        }
     }
-    // the sum of the parts: of the values less what remains of them
+    // the sum of the parts: of the values less what remains of them (fp16 steps are multiplied with digits, not with codes)
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         sum -= r0[k];
         sum1 -= r1[k];
     }
     sum += sum1;
+    if (wide) sum = 0.f;
     if (!ok) sum = __builtin_nanf("");
     // -S: over the eight groups
     sum += xor_lane_f32(sum, 8);
     sum += xor_lane_f32(sum, 16);
     sum += xor_lane_f32(sum, 32);
     if (lane < 8) *reinterpret_cast<float*>(meta + 256 + (8 * wave + r8) * 4) = -sum;
-    int word = (int)((ok ? e8 : 0xffu) << (8 * step));
+    int word = (int)((wide ? 0u : ok ? e8 : 0xffu) << (8 * step));
     word |= xor_lane_i32(word, 8);
     word |= xor_lane_i32(word, 32);
     if (step == 0) *reinterpret_cast<int*>(meta + at * 4) = word;

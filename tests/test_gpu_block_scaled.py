@@ -52,11 +52,11 @@ def activations(torch, M, K, seed):
 
 
 def check(torch, Y, X, What, half):
-    """A rotated value is carried to 2^-14 of the largest of its 32 (the last part's step is 2^-12 of a unit that the
-    largest exceeds 3.75 times), so per element at most 2^-14 sqrt(32) ||x|| ||w_hat|| by Cauchy-Schwarz over the groups,
-    half as much again for the fp32 sums; the intermediate of the rotation in two fp16 parts, the lower one no finer than
-    fp16's 2^-24 (2^-25 an element; what follows it is orthonormal, so sqrt(K) of them in norm: rows of tiny values); and
-    the rounding of the result.  Rows on the whole: 1e-4 (3.5e-5 measured)."""
+    """A rotated value is carried to 2^-12 / 3.75 of the largest of its 32 (half the last part's step is 2^-12 of a unit that the
+    largest exceeds 3.75 times), so per element at most 1.07 * 2^-14 sqrt(32) ||x|| ||w_hat|| by Cauchy-Schwarz over the
+    groups (in fp16, 2^-11 of itself, less), the rest up to 1.5 for the fp32 sums; the intermediate of the rotation in two
+    fp16 parts, the lower one no finer than fp16's 2^-24 (2^-25 an element; what follows it is orthonormal, so sqrt(K) of
+    them in norm: rows of tiny values); and the rounding of the result.  Rows on the whole: 1e-4 (3.5e-5 measured)."""
     want = X.double() @ What.T
     err = (Y.double() - want).abs()
     x, w = X.double().norm(dim=1)[:, None], What.norm(dim=1)[None, :]
@@ -160,3 +160,49 @@ def test_code_three_counts_as_two(gpu, M, N, K):  # noqa: F811
     Y = binding.itq3s_matmul(codes, scales, N, K, X).double()
     want = X.double() @ What.T
     assert ((Y - want).norm() / want.norm()).item() <= 4e-4  # (2^-11 / sqrt(3) where x~ is rounded to fp16)
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(500, 1000, 4096), (512, 4096, 4096), (640, 4100, 2560)])
+@pytest.mark.parametrize("half", [False, True])
+def test_outputs_beside_a_spike(gpu, M, N, K, half):  # noqa: F811
+    """Activations with an offset rotate to a spike at a block's channel 0 (with one of their own for every 64 channels: at 0, 64,
+    128, 192).  Outputs whose digits there are 0 are as good as with x~ in fp16: 2^-11 / sqrt(3) in norm, of
+    the rounding of x~ and, for fp16 results, of theirs.  In tiles of 32 rows with an offset, some with, and without."""
+    torch, binding = gpu
+    codes, scales, _ = tensor(torch, binding, N, K, "spike", M, z_fraction=0.0)
+    # digit 0 (code 1) at channels 0, 64, 128, 192 of the even columns: word 4 (16 g + r), bits 1:0, r even
+    lanes = codes.view(-1, 384)[:, :256].view(-1, 4, 16, 4)
+    lanes[:, :, ::2, 0] = (lanes[:, :, ::2, 0] & ~3) | 1
+    What = binding.itq3s_dequantize(codes, scales, N, K).double()
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    noise = torch.randn((M, K), generator=gen, device="cuda")
+    sign = torch.randint(0, 2, (M, K // 64), generator=gen, device="cuda").repeat_interleave(64, dim=1) * 2.0 - 1.0
+    classes = (0.0, 0.5, 1.5, 4.0, 30.0, 300.0)
+    for rows in (torch.arange(M, device="cuda") % 6, torch.arange(M, device="cuda") // 32 % 6):
+        offset = torch.tensor(classes, device="cuda")[rows][:, None]
+        for X in ((noise + offset).half(), (noise + offset * sign).half()):
+            Y = binding.itq3s_matmul(codes, scales, N, K, X, dtype=torch.float16 if half else torch.float32).double()
+            want = X.double() @ What.T
+            for i, c in enumerate(classes):
+                for cols in (slice(0, N, 2), slice(1, N, 2)):
+                    y, w = Y[rows == i][:, cols], want[rows == i][:, cols]
+                    err = ((y - w).norm() / w.norm()).item()
+                    assert err <= (2.0**0.5 if half else 1.0) * 2.0**-11 / 3**0.5, (c, cols.start, err)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,rows", [(64, 40, 140032, 64), (2048, 4096, 16640, 33), (700, 1000, 2304, 1), (6300, 17, 256, 6300)])
+def test_fp16_steps_of_many_blocks(gpu, M, N, K, rows):  # noqa: F811
+    """More blocks with fp16 steps than a wavefront looks at in one go (64), every other block with some and without; in some
+    tiles of rows only, in all; one block."""
+    torch, binding = gpu
+    codes, scales, What = tensor(torch, binding, N, K, "steps", M, z_fraction=0.02 if N < 5000 else 0.0)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    X = torch.randn((M, K), generator=gen, device="cuda")
+    at = torch.arange(K, device="cuda")
+    X[M - rows :, (at // 256) % 2 == 0] += 40.0
+    X[M - rows :, (at // 256) % 5 == 3] += 25.0 * (1 - 2 * (at[(at // 256) % 5 == 3] // 64 % 2))
+    X = X.half()
+    Y = binding.itq3s_matmul(codes, scales, N, K, X).double()
+    want = X.double() @ What.T
+    assert ((Y - want).norm(dim=1) / want.norm(dim=1)).max().item() <= 2.0**-11 / 3**0.5 * 1.5  # (a row at a time: 17 outputs at the least)
