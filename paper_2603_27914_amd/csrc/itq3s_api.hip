@@ -82,25 +82,20 @@ inline bool passes_of_16(int64_t M, int64_t N, int64_t K) {
 
 // Scratch of the kernels for more rows, the same for every tensor of a call: the many-row kernel, the block-scaled ones.
 size_t rows_workspace(int64_t M, int64_t K) { return round_up(itq3s::rows_xt_bytes(M, K), 256) + round_up(itq3s::rows_x0_bytes(M, K), 256); }
-size_t mx_workspace(int64_t M, int64_t K) { return itq3s::mx_sample_bytes(M, K) + itq3s::mx_bytes(M, K); }
 
 // The block-scaled kernels over the tensors that each of them takes, in as many slabs of rows as the room asks for (a
 // row's results do not depend on those beyond its tile of 32).  The room holds 32 rows.
 int launch_mx_routes(const itq3s_weight* w, const itq3s::Route* route, int count, int64_t K, const _Float16* X, int64_t M, int64_t ldx, int y_f16,
-                     unsigned char* base, size_t room, uint32_t* flags, hipStream_t st) {
+                     unsigned char* Xm, size_t room, uint32_t* flags, hipStream_t st) {
     int64_t slab = M;
-    unsigned char* Xm = base + itq3s::mx_sample_bytes(M, K);
-    _Float16* sample = itq3s::mx_sample_bytes(M, K) > 0 ? reinterpret_cast<_Float16*>(base) : nullptr;
-    if (room < mx_workspace(M, K)) {
+    if (room < itq3s::mx_bytes(M, K)) {
         const int64_t most = (int64_t)(room / itq3s::mx_bytes(1, K)) * itq3s::kMxRows, slabs = (M + most - 1) / most;
         slab = ((M + slabs - 1) / slabs + itq3s::kMxRows - 1) / itq3s::kMxRows * itq3s::kMxRows;
-        Xm = base;
-        sample = nullptr;
     }
     const size_t y_bytes = y_f16 ? 2 : 4;
     for (int64_t m0 = 0; m0 < M; m0 += slab) {
         const int64_t rows = M - m0 < slab ? M - m0 : slab;
-        int rc = itq3s::launch_rotate_mx(X + m0 * ldx, rows, K, ldx, Xm, sample, flags, st);
+        int rc = itq3s::launch_rotate_mx(X + m0 * ldx, rows, K, ldx, Xm, flags, st);
         for (const itq3s::Route r : {itq3s::Route::shares8, itq3s::Route::shares4, itq3s::Route::tiled}) {
             itq3s::GemvWeight gw[ITQ3S_MAX_GROUP];
             int n = 0;
@@ -157,7 +152,7 @@ size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     // room for the kernel that computes the call, and for those that one with less room falls back to
     const size_t least = least_workspace(M, N, K);
     if (M <= itq3s::kGemvMaxM || passes_of_16(M, N, K)) return least;
-    const size_t want = itq3s::many_row_route(M, N, K) == itq3s::Route::rows ? rows_workspace(M, K) : mx_workspace(M, K);
+    const size_t want = itq3s::many_row_route(M, N, K) == itq3s::Route::rows ? rows_workspace(M, K) : itq3s::mx_bytes(M, K);
     return want > least ? want : least;
 }
 
@@ -240,7 +235,7 @@ int itq3s_matmul_grouped(const itq3s_weight* w, int count, int64_t K, const void
     itq3s::GemvWeight rows[ITQ3S_MAX_GROUP];
     int n_rows = 0, n_mx = 0, n_pass = 0;
     const bool room_rows = workspace_bytes >= rows_workspace(M, K);
-    const bool room_mx = workspace_bytes >= (M <= kChunkedMaxM ? mx_workspace(M, K) : itq3s::mx_bytes(1, K));
+    const bool room_mx = workspace_bytes >= itq3s::mx_bytes(1, K);
     for (int i = 0; i < count; ++i) {
         if (passes_of_16(M, w[i].N, K)) {
             pass[n_pass++] = w[i];

@@ -78,10 +78,9 @@ int launch_rows(const GemvWeight* w, int count, int64_t K, const _Float16* X, in
 int launch_rotate_rows(const _Float16* X, int64_t M, int64_t K, int64_t ldx, int mt, int groups, _Float16* Xt, _Float16* X0, uint32_t* flags,
                        hipStream_t stream);
 
-// The block-scaled kernels (many_row_route() says for which calls).  launch_rotate_mx writes x~ in three parts to Xm (mx_bytes)
-// and, if `sample` is not null, the first kMxSampleRows rows of it in fp16 there (mx_sample_bytes); the two contractions
-// read Xm: K shared out over 8 or 4 wavefronts of a workgroup, or tiled.
-int launch_rotate_mx(const _Float16* X, int64_t M, int64_t K, int64_t ldx, unsigned char* Xm, _Float16* sample, uint32_t* flags, hipStream_t stream);
+// The block-scaled kernels (many_row_route() says for which calls).  launch_rotate_mx writes their operand to Xm (mx_bytes), both
+// contractions read it: K shared out over 8 or 4 wavefronts of a workgroup, or tiled.
+int launch_rotate_mx(const _Float16* X, int64_t M, int64_t K, int64_t ldx, unsigned char* Xm, uint32_t* flags, hipStream_t stream);
 int launch_mx_shares(const GemvWeight* w, int count, int64_t K, int64_t M, const unsigned char* Xm, int ks, int y_f16, uint32_t* flags, hipStream_t stream);
 int launch_gemm(const GemvWeight* w, int count, int64_t K, int64_t M, const unsigned char* Xm, int y_f16, uint32_t* flags, hipStream_t stream);
 

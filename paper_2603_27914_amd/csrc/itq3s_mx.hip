@@ -353,16 +353,9 @@ int launch_mx_shares(const GemvWeight* w, int count, int64_t K, int64_t M, const
     a.Xm = Xm; a.flags = flags; a.M = (int)M; a.KB = (int)(K / kBlock); a.y_f16 = y_f16;
     a.tiles_m = (int)((M + kMxRows - 1) / kMxRows);
     if (ks == 4) return launch_mx_kernel<4, 4>(a, w, count, stream);
-    // columns of an item: what takes the fewest rounds' time for the launch as a whole (the sums do not depend on it)
-    int best_nt = 1;
-    double best = 1e300;
-    for (int nt = 1; nt <= 4; nt *= 2) {
-        int64_t cols = 0;
-        for (int i = 0; i < count; ++i) cols += (w[i].N + 32 * nt - 1) / (32 * nt);
-        const double t = shares8_time(cols, nt, M, K, cu_count());
-        if (t < best) { best = t; best_nt = nt; }
-    }
-    switch (best_nt) {
+    int64_t N[kGemvMaxGroup];
+    for (int i = 0; i < count; ++i) N[i] = w[i].N;
+    switch (shares8_columns(N, count, M, K, cu_count())) {
         case 1: return launch_mx_kernel<8, 1>(a, w, count, stream);
         case 2: return launch_mx_kernel<8, 2>(a, w, count, stream);
         default: return launch_mx_kernel<8, 4>(a, w, count, stream);

@@ -17,11 +17,6 @@ constexpr int kMxMetaBytes = 64 * 4 + 32 * 4 + 32 * 4;     // 512
 constexpr int kMxBlockBytes = 4 * kMxStepBytes + kMxMetaBytes;  // 18944
 inline size_t mx_bytes(int64_t M, int64_t K) { return (size_t)((M + kMxRows - 1) / kMxRows) * (size_t)(K / 256) * kMxBlockBytes; }
 
-// The rotated activations of the first 64 rows in fp16, row by row (channels moved inside groups of sixteen), stand in
-// front of the operand of calls with more rows: what tells from outside that a call was computed this way.
-constexpr int64_t kMxSampleRows = 64;
-inline size_t mx_sample_bytes(int64_t M, int64_t K) { return M > kMxSampleRows ? (size_t)kMxSampleRows * (size_t)K * 2 : 0; }
-
 constexpr int kMxWaves = 8;  // wavefronts of a workgroup of mx_kernel
 enum class Route { rows, shares8, shares4, tiled };
 
@@ -36,6 +31,19 @@ inline double shares_time(const double (&c)[6], int64_t items, int64_t steps, in
 inline double shares8_time(int64_t col_tiles, int nt, int64_t M, int64_t K, int units) {
     constexpr double c[3][6] = {{7.81, -0.51, 1.11, 1.84, 0.0, 1.47}, {7.89, -0.23, 1.07, 2.02, 0.11, 1.21}, {8.7, 0.03, 1.24, 2.51, 0.5, 1.02}};
     return shares_time(c[nt == 1 ? 0 : nt == 2 ? 1 : 2], (M + kMxRows - 1) / kMxRows * col_tiles, (K / 256 + 7) / 8, M, K, units);
+}
+// Columns of an item over 32 for a launch of these tensors: what takes the fewest rounds' time for the launch as a whole (a
+// column's sums do not depend on it).
+inline int shares8_columns(const int64_t* N, int count, int64_t M, int64_t K, int units) {
+    int best_nt = 1;
+    double best = 1e300;
+    for (int nt = 1; nt <= 4; nt *= 2) {
+        int64_t cols = 0;
+        for (int i = 0; i < count; ++i) cols += (N[i] + 32 * nt - 1) / (32 * nt);
+        const double t = shares8_time(cols, nt, M, K, units);
+        if (t < best) { best = t; best_nt = nt; }
+    }
+    return best_nt;
 }
 inline double shares4_time(int64_t M, int64_t N, int64_t K, int units) {
     constexpr double c[6] = {9.13, 1.1, 1.74, 2.22, 0.51, 0.86};

@@ -144,7 +144,7 @@ constexpr int kMxRowStride = 296;  // floats of a row's 256 in LDS: eight groups
 typedef float floatx32 __attribute__((ext_vector_type(32)));
 typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void rotate_mx_kernel(const _Float16* __restrict__ X, int M, int KB, int64_t ldx,
-                                                              unsigned char* __restrict__ Xm, _Float16* __restrict__ sample, uint32_t* __restrict__ flags) {
+                                                              unsigned char* __restrict__ Xm, uint32_t* __restrict__ flags) {
     __shared__ __align__(16) float lds[4][8 * kMxRowStride];
     __shared__ uint32_t votes[4];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -185,16 +185,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         r1[2 * i] = v[1];
         r0[2 * i + 1] = v[2];
         r1[2 * i + 1] = v[3];
-    }
-    if (sample != nullptr && tile * 32 < (int)kMxSampleRows) {  // (uniform) of every sixteen channels the even slots, then the odd ones
-        _Float16* const to = sample + ((int64_t)(tile * 32 + wave * 8 + r8) * KB + b) * kBlock + 64 * (group >> 1) + 8 * odd;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            half8 h;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) h[j] = (_Float16)(j % 2 == 0 ? r0[4 * i + j / 2] : r1[4 * i + j / 2]);
-            *reinterpret_cast<half8*>(to + 16 * i) = h;
-        }
     }
     float peak = 0.f, sum = 0.f, sum1 = 0.f;
 #pragma unroll
@@ -286,9 +276,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     if (!ok && flags != nullptr) atomicOr(flags, kFlagActRange);
 }
 
-int launch_rotate_mx(const _Float16* X, int64_t M, int64_t K, int64_t ldx, unsigned char* Xm, _Float16* sample, uint32_t* flags, hipStream_t stream) {
+int launch_rotate_mx(const _Float16* X, int64_t M, int64_t K, int64_t ldx, unsigned char* Xm, uint32_t* flags, hipStream_t stream) {
     const int64_t tiles = (M + kMxRows - 1) / kMxRows * (K / kBlock);
-    hipLaunchKernelGGL(rotate_mx_kernel, dim3((unsigned)tiles), dim3(256), 0, stream, X, (int)M, (int)(K / kBlock), ldx, Xm, sample, flags);
+    hipLaunchKernelGGL(rotate_mx_kernel, dim3((unsigned)tiles), dim3(256), 0, stream, X, (int)M, (int)(K / kBlock), ldx, Xm, flags);
     return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 

@@ -194,7 +194,7 @@ def test_settings_kept_per_device_are_made_on_every_device(tmp_path):
             assert "hipFuncSetAttribute" not in open(os.path.join(build.CSRC, name)).read(), name
 
 
-@pytest.mark.parametrize("source", ["gemv", "rows", "rotate", "gemm", "gemm_ws", "dequantize", "quantize"])
+@pytest.mark.parametrize("source", ["gemv", "rows", "rotate", "gemm", "mx", "gemm_ws", "dequantize", "quantize"])
 def test_kernels_keep_their_registers(source):
     """No kernel of the path parks registers in scratch memory (a spill in one of the many instantiations of a
     kernel costs time and nothing else, so no other test sees it)."""

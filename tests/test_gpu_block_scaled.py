@@ -1,48 +1,35 @@
 """The block-scaled kernels (fp4 digits, activations in three fp6 parts) at the sizes where their division of the work
 changes: rows of every remainder modulo the tiles of 32 and 64, ragged columns, wavefronts without a block, several rounds,
 each number of columns an item has, tensors of one launch.  Against itq3s_dequantize and a dense fp64 product."""
-import os
-import subprocess
-
 import pytest
 
+from tests.block_scaled import ROWS, SHARES4, SHARES8, TILED, route
 from tests.test_gpu_rows import gpu, tensor  # noqa: F401  (gpu is a fixture)
 
-# M, N, K, route (0 many-row kernel, 1 and 2 K over 8 or 4 wavefronts, 3 tiled)
+# M, N, K, the kernel that takes it
 SIZES = [
-    (481, 33, 3584, 1),     # 14 blocks: two wavefronts have one, the others two; 32 columns an item
-    (1301, 100, 1280, 1),   # five blocks: three wavefronts have none; 64 columns
-    (700, 1000, 2304, 1),   # nine blocks; 128 columns
-    (500, 1000, 4096, 1),
-    (20, 28672, 4096, 1),   # rows: 12 of padding
-    (2113, 300, 8192, 1),   # two rounds
-    (512, 4096, 4096, 2),
-    (2081, 515, 1024, 2),   # one block a wavefront, the last columns of an item beyond the tensor
-    (993, 1032, 4096, 2),
-    (6300, 17, 256, 3),     # one block, one storage tile and a ragged one, an odd number of tiles of 32 rows
-    (65, 65000, 512, 3),    # one row in the second tile of 64
-    (640, 4100, 2560, 3),
-    (33, 40000, 2816, 3),
+    (481, 33, 3584, SHARES8),     # 14 blocks: two wavefronts have one, the others two; 32 columns an item
+    (1301, 100, 1280, SHARES8),   # five blocks: three wavefronts have none; 64 columns
+    (700, 1000, 2304, SHARES8),   # nine blocks; 128 columns
+    (500, 1000, 4096, SHARES8),
+    (20, 28672, 4096, SHARES8),   # rows: 12 of padding
+    (2113, 300, 8192, SHARES8),   # two rounds
+    (512, 4096, 4096, SHARES4),
+    (2081, 515, 1024, SHARES4),   # one block a wavefront, the last columns of an item beyond the tensor
+    (993, 1032, 4096, SHARES4),
+    (6300, 17, 256, TILED),     # one block, one storage tile and a ragged one, an odd number of tiles of 32 rows
+    (65, 65000, 512, TILED),    # one row in the second tile of 64
+    (640, 4100, 2560, TILED),
+    (33, 40000, 2816, TILED),
 ]
 
 
-def test_sizes_take_the_routes_they_are_here_for(tmp_path):
-    from paper_2603_27914_amd import build
-
-    main = tmp_path / "route.cpp"
-    main.write_text(
-        '#include "itq3s_mx_rule.h"\n#include <cstdio>\n'
-        "int main() { long long M, N, K;\n"
-        '    while (std::scanf("%lld %lld %lld", &M, &N, &K) == 3) std::printf("%d ", (int)itq3s::many_row_route(M, N, K)); }\n'
-    )
-    exe = tmp_path / "route"
-    subprocess.run(["g++", "-std=c++17", "-I", build.CSRC, str(main), "-o", str(exe)], check=True)
+def test_sizes_take_the_routes_they_are_here_for():
+    for M, N, K, kernel in SIZES:
+        assert route(M, N, K) == kernel, (M, N, K)
     # besides: a group's thin tensors go where its wide ones go
-    more = [(512, n, 4096, None) for n in (512, 1024, 4096)] + [(58, n, 23040, 0) for n in (264, 2112)] + [(48, n, 4096, 0) for n in (512, 4096)]
-    sizes = "".join("%d %d %d\n" % s[:3] for s in SIZES + more)
-    got = [int(v) for v in subprocess.run([str(exe)], input=sizes, check=True, stdout=subprocess.PIPE, text=True).stdout.split()]
-    for (M, N, K, route), r in zip(SIZES + more, got):
-        assert r == route if route is not None else r != 0, (M, N, K, r)
+    for M, K, Ns, many in ((512, 4096, (512, 1024, 4096), False), (58, 23040, (264, 2112), True), (48, 4096, (512, 4096), True)):
+        assert [route(M, N, K) == ROWS for N in Ns] == [many] * len(Ns), (M, K, Ns)
 
 
 def activations(torch, M, K, seed):

@@ -1,10 +1,11 @@
 """The streaming kernel for 17 and more activation rows at the sizes where its division of the work
 changes (padding of rows and row tiles, wavefronts without a block, several rounds of items, tensors
-that share an item), and the tiled kernel at ragged sizes large enough to reach it.  Checked on the
+that share an item), and sizes just beyond it.  Every size says which kernel takes it, and that is asserted.  Checked on the
 device against itq3s_dequantize (held to the oracle within 1e-6 elsewhere) and a dense fp64 product."""
 import numpy as np
 import pytest
 
+from tests.block_scaled import ROWS, SHARES4, SHARES8, TILED, route, route_and_items
 from tests.packed_inputs import random_packed
 
 pytestmark = pytest.mark.gpu
@@ -39,26 +40,34 @@ def check(Y, X, What, half):
 
 
 SIZES = [
+    # the many-row kernel
     (17, 16, 256),      # one row tile, one block: seven of eight wavefronts have nothing
     (33, 1000, 2304),   # nine blocks: one wavefront has two; a ragged last row tile
     (48, 257, 4096),
     (49, 4100, 512),    # 64 rows, 15 of them padding
     (64, 9000, 768),    # 563 row tiles: three per workgroup, the last item one short
     (65, 300, 2048),    # two groups of 48 rows
-    (97, 17000, 256),   # two rounds of items of four row tiles
+    (97, 13000, 512),   # two rounds of items of four row tiles
     (130, 1032, 1280),  # three groups
     (160, 4096, 1024),
     (257, 333, 11008),
     (1024, 2048, 512),
-    (64, 40, 165376),   # nearly the longest K at 64 rows (rotated activations of 32 MB)
-    (20, 24, 250112),   # ... and at 20
-    (64, 40, 196608),   # beyond: the tiled kernel
-    (20, 24, 262400),   # beyond: two passes of the kernel for up to 16 rows
+    (64, 16, 28928),    # the longest K at 64 rows
+    (20, 16, 79872),    # ... and at 20
+    # beyond
+    (97, 17000, 256, TILED),
+    (64, 40, 165376, SHARES8),  # many blocks a wavefront
+    (20, 24, 250112, SHARES8),
+    (64, 40, 196608, SHARES8),
+    (20, 24, 262400, None),     # two passes of the kernel for up to 16 rows
 ]
 
 
-@pytest.mark.parametrize("M,N,K", SIZES)
-def test_many_rows(gpu, M, N, K):
+@pytest.mark.parametrize("size", SIZES)
+def test_many_rows(gpu, size):
+    M, N, K, kernel = size if len(size) == 4 else (*size, ROWS)
+    assert kernel is None or route(M, N, K) == kernel
+    assert (M, N, K) != (97, 13000, 512) or route_and_items(M, N, K)[1] > 256  # (an item to a unit)
     torch, binding = gpu
     codes, scales, What = tensor(torch, binding, N, K, "rows", M)
     gen = torch.Generator(device="cuda").manual_seed(M + N)
@@ -75,12 +84,13 @@ def test_many_rows(gpu, M, N, K):
 @pytest.mark.parametrize("M", [24, 40, 64, 100])
 def test_many_rows_grouped_equals_single_calls(gpu, M):
     """Items that span tensors (16 + 1000 + 17 + 300 rows, and 256-tile tensors with three tiles per item),
-    and a group in which one tensor is large enough for the tiled kernel."""
+    and a group in which one tensor is large enough for a block-scaled kernel."""
     torch, binding = gpu
     groups = [(512, [16, 1000, 17, 300]), (1024, [4096, 4096, 4096])]
     if M == 100:
         groups.append((8192, [24576, 500]))
     for K, Ns in groups:
+        assert [route(M, N, K) for N in Ns] == [SHARES8 if N == 24576 else ROWS for N in Ns]
         ts = [tensor(torch, binding, N, K, "rowsg", i) for i, N in enumerate(Ns)]
         X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
         outs = binding.itq3s_matmul_grouped([(c, s, N) for (c, s, _), N in zip(ts, Ns)], K, X, dtype=torch.float16)
@@ -120,18 +130,18 @@ def test_groups_of_sixteen_rows(gpu, M, N, K):
     check(b, X, wide[2], False)
 
 
-@pytest.mark.parametrize("M,N,K,less", [(17, 1000, 4096, "pass"), (32, 100, 11008, "pass"), (64, 33000, 256, "tiled")])
+@pytest.mark.parametrize("M,N,K,less", [(17, 1000, 4096, "pass"), (32, 100, 11008, "pass"), (64, 33000, 256, "slabs")])
 def test_room_for_the_other_routes_is_still_enough(gpu, M, N, K, less):
-    """A call whose workspace has room for the passes of 16 rows or for the tiled kernel (no padded rows: sized
-    for those routes, or for another M) is computed by them: alone, in a group, twice on one workspace of
-    garbage.  One byte less is refused."""
+    """A call whose workspace has room for the passes of 16 rows or for the activation rows as they are (sized for
+    another M, or when the tiled kernel had fp16 operands) is computed in passes, or in slabs of rows: alone, in a
+    group, twice on one workspace of garbage.  One byte less is refused."""
     torch, binding = gpu
     codes, scales, What = tensor(torch, binding, N, K, "room", M)
     X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
     if less == "pass":
         room = binding.itq3s_matmul_workspace_bytes(16, N, K)
         want = torch.cat([binding.itq3s_matmul(codes, scales, N, K, X[m : m + 16]) for m in range(0, M, 16)])
-    else:  # 129 tiles do not split K: the activation rows, 512 bytes of flags, 256 bytes
+    else:  # (129 tiles of 128 x 256: the activation rows and 768 bytes)
         room = (M * K * 2 + 255) // 256 * 256 + 768
         want = None
     assert room < binding.itq3s_matmul_workspace_bytes(M, N, K)
@@ -147,9 +157,11 @@ def test_room_for_the_other_routes_is_still_enough(gpu, M, N, K, less):
 
 
 # rotated activations of more than 32 MB, or a product too large for the streaming kernel
-@pytest.mark.parametrize("M,N,K,z", [(8200, 100, 2048, 0.02), (2100, 300, 8192, 0.6), (4200, 700, 4096, 0.0), (66000, 17, 256, 0.02), (517, 9300, 4096, 0.02)])
-def test_tiled_kernel_ragged(gpu, M, N, K, z):
+@pytest.mark.parametrize("M,N,K,z,kernel", [(8200, 100, 2048, 0.02, SHARES8), (2100, 300, 8192, 0.6, SHARES8), (517, 9300, 4096, 0.02, SHARES8), (517, 3000, 4096, 0.3, SHARES4),
+                                            (4200, 700, 4096, 0.0, TILED), (4201, 700, 4096, 0.6, TILED), (66000, 17, 256, 0.02, TILED)])
+def test_larger_calls_ragged(gpu, M, N, K, z, kernel):
     torch, binding = gpu
+    assert route(M, N, K) == kernel
     codes, scales, What = tensor(torch, binding, N, K, "tiled", M, z_fraction=z)
     X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
     for dtype in (torch.float32, torch.float16):
