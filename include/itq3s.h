@@ -109,8 +109,8 @@ int itq3s_dequantize(const uint32_t *codes, const uint32_t *scales, int64_t N, i
  * M > 16 accepts K <= 4194304 only (ITQ3S_ERR_SHAPE beyond), M <= 16 K <= 2^28.  fp32 accumulation in
  * all, the zero-point terms included: an output element is rounded once.
  * Activation range.  Every 256-channel chunk x of a row of X is replaced by x~ = H x, rounded to
- * fp16 or, on the block-scaled path, to 2^-13 of the largest of 32 values (every other one of 64 channels; to fp16 there too, for
- * 64 channels of 32 rows, where one of these rows has most of its values below 2^-5 of the largest), after an intermediate T = X_16x16 H_16 / 4 that is split into fp16 parts.  Both stay
+ * fp16 or, on the block-scaled path, to 2^-13 of the largest of 32 values (every other one of 64 channels; to fp16 there too
+ * where most of the 32 are below 2^-5 of the largest), after an intermediate T = X_16x16 H_16 / 4 that is split into fp16 parts.  Both stay
  * finite whenever  max|x| <= 16376  and  |(H x)_k| <= 65504  over the chunk (the second holds if
  * sum|x| <= 16 * 65504; any chunk with max|x| <= 4094 satisfies both).  Outside that range the
  * products that involve the chunk are Inf/NaN although the exact result is finite, and

@@ -84,7 +84,7 @@ inline bool passes_of_16(int64_t M, int64_t N, int64_t K) {
 size_t rows_workspace(int64_t M, int64_t K) { return round_up(itq3s::rows_xt_bytes(M, K), 256) + round_up(itq3s::rows_x0_bytes(M, K), 256); }
 
 // The block-scaled kernels over the tensors that each of them takes, in as many slabs of rows as the room asks for (a
-// row's results do not depend on those beyond its tile of 32).  The room holds 32 rows.
+// row's results do not depend on the others).  The room holds 32 rows.
 int launch_mx_routes(const itq3s_weight* w, const itq3s::Route* route, int count, int64_t K, const _Float16* X, int64_t M, int64_t ldx, int y_f16,
                      unsigned char* Xm, size_t room, uint32_t* flags, hipStream_t st) {
     int64_t slab = M;

@@ -69,8 +69,8 @@ __device__ __forceinline__ uint32_t even_digits(uint32_t v) { return v & 0x33333
 __device__ __forceinline__ uint32_t odd_digits(uint32_t v) { return (v >> 2) & 0x33333333u; }
 constexpr int kDigitScales = 0x00777c80;
 
-// Steps of 64 channels whose activations are fp16 (rotate_mx_kernel says which and why) have scales of 0, which no group has
-// otherwise and which takes what the step's bytes are as fp6 to below 1e-35.  Bit 8 q + 7 of the result for step q of a block.
+// Groups of 32 activations that are fp16 (rotate_mx_kernel says which and why) have a scale of 0, which none has otherwise
+// and which takes what their bytes are as fp6 to below 1e-35.  Of a lane's four scales: bit 8 q + 7 for step q.
 __device__ __forceinline__ uint32_t wide_steps(uint32_t scales) { return (scales - 0x01010101u) & ~scales & 0x80808080u; }
 
 }  // namespace itq3s

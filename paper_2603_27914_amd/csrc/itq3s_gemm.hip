@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             unpack(n, next_step);
         }
     };
-    uint32_t any_wide = 0;
+    uint64_t any_wide = 0;
     auto order = [&](auto reads, auto head, auto next_step) {
         constexpr int kReads = decltype(reads)::value, kHead = decltype(head)::value, kUnpack = decltype(next_step)::value == 0 ? 4 : 8;
         __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     auto begin_block = [&](int b) -> bool {
         const char* const meta = lds + kMeta + (b & 1) * 1024 + wm * kMxMetaBytes;
         scale_a = *reinterpret_cast<const int*>(meta + lane * 4);
-        any_wide |= wide_steps((uint32_t)__builtin_amdgcn_readfirstlane(scale_a));
+        any_wide |= __builtin_amdgcn_ballot_w64(wide_steps((uint32_t)scale_a) != 0u);
         uint32_t any = 0;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int64_t tile0 = nt0 + wn * (2 * NT);
         const int rows = tensor_tiles - tile0 < 2 * NT ? (tensor_tiles > tile0 ? (int)(tensor_tiles - tile0) : 0) : 2 * NT;
         const int64_t from = rows > 0 ? tile0 * KB : 0;
-        add_wide_steps<NT>(
+        add_wide_steps<NT, NT>(
             __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(args.Xm + (int64_t)(2 * tm + wm) * KB * kMxBlockBytes), 0, wm < x_tiles ? KB * kMxBlockBytes : 0, kRawBuffer),
             __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(codes + from * kTileWords), 0, rows * KB * (kTileWords * 4), kRawBuffer),
             __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(scales + from * kTileRows), 0, rows * KB * (kTileRows * 4), kRawBuffer), 0, 1, KB,

@@ -9,7 +9,7 @@
 // in three parts of fp6 (four significant bits each) with one power of two per 32 channels of a row: x~ = 2^e (p0 + p1 / 16
 // + p2 / 512), the remainder at most 2^-12 / 3.75 (6.5e-5) of the group's largest value, 3.4e-5 of the values' deviation on
 // normal ones (fp16: 2.1e-4, and that is what whole products, fp32 results, are off by).  Where a group's largest value stands
-// alone, the 64 channels are fp16 (rotate_mx_kernel), and products of their own (itq3s_mx_wide.h).  v_mfma_scale_f32_32x32x64_f8f6f4
+// alone, the group is fp16 (rotate_mx_kernel), with products of its own (itq3s_mx_wide.h).  v_mfma_scale_f32_32x32x64_f8f6f4
 // runs fp6 x fp4 at four times the fp16 rate, so three products take 0.75 of one in fp16.  The codes'
 // offset (code 1 = digit 0) is taken back by starting a block's sum at -S, S the sum of its activations' parts.  A
 // block's sum is a sum of its own (32 x 32 outputs in 16 registers) because its scale d belongs to a column and a
@@ -160,11 +160,11 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void mx_kernel(const MxArgs args)
             part(c2);
         }
     };
-    uint32_t any_wide = 0;  // of the item's blocks
+    uint64_t any_wide = 0;  // of the item's blocks
     float* const rowval = reinterpret_cast<float*>(smem) + wave * 64;  // -S and E of the 32 rows, this wavefront's own
     auto begin_block = [&]() {
         scale_a = (int)mt0;
-        any_wide |= wide_steps((uint32_t)__builtin_amdgcn_readfirstlane(scale_a));
+        any_wide |= __builtin_amdgcn_ballot_w64(wide_steps((uint32_t)scale_a) != 0u);
         rowval[lane] = __builtin_bit_cast(float, mt1);
         __builtin_amdgcn_wave_barrier();
         uint32_t any = 0;
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void mx_kernel(const MxArgs args)
         end_block();
         ITQ3S_FENCE;
         if (last) {
-            if (any_wide != 0) add_wide_steps<NT>(cur.x, cur.c, cur.s, ks, KS, nb, off_w, step_w, off_s, step_s, acc);
+            if (any_wide != 0) add_wide_steps<NT, (NT < 4 ? NT : 2)>(cur.x, cur.c, cur.s, ks, KS, nb, off_w, step_w, off_s, step_s, acc);
             any_wide = 0;
             finish(item);
             item += args.wg_per_chiplet;

@@ -146,7 +146,6 @@ typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void rotate_mx_kernel(const _Float16* __restrict__ X, int M, int KB, int64_t ldx,
                                                               unsigned char* __restrict__ Xm, uint32_t* __restrict__ flags) {
     __shared__ __align__(16) float lds[4][8 * kMxRowStride];
-    __shared__ uint32_t votes[4];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int tile = (int)blockIdx.x / KB, b = (int)blockIdx.x - tile * KB;  // tile of 32 rows
     unsigned char* const out = Xm + ((int64_t)tile * KB + b) * kMxBlockBytes;
@@ -200,26 +199,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     if (peak == 0.f || !ok) e8 = 127u;
     // Three parts leave the small values of a group an error of 1.3e-5 of its largest one (root mean square), fp16 2.1e-4 of
     // themselves: the same where the largest is 16 times the others' deviation, 24 times their median.  Where the most
-    // are far below it (17 of the 32 below 2^-5 of it), the step's 64 channels of all 32 rows are fp16: activations with
-    // an offset, say, rotate to one large value in a block, and the outputs whose digit there is 0 are made of
-    // the others.  Such outputs, offset 0 / 1 / 4 / 30 deviations: 3.4e-5, 1.1e-4, 1.1e-4, 7e-5 (x~ in fp16 alone 2.1e-4, 2.1e-4, 2.1e-4,
-    // 1.5e-4; without fp16 steps 3.4e-5, 1e-4, 4e-4, 2.5e-3).  Normal activations have no such step in 10^5.
+    // are far below it (10 of 16 of them below 2^-5 of it), the group is fp16: activations with an offset, say,
+    // rotate to one large value in a block, and the outputs whose digit there is 0 are made of the others.
+    // Such outputs, offset 0 / 1 / 4 / 30 deviations: 3.4e-5, 9.8e-5, 8.2e-5, 5.2e-5 (x~ in fp16 alone 2.1e-4, 2.1e-4, 2.1e-4, 1.5e-4;
+    // no group in fp16 3.4e-5, 9.8e-5, 4e-4, 2.5e-3).  Of groups of normal values one in 10^7 is.
     int small = 0;
     const float few = peak * 0.03125f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < 16; k += 2) {
         small += __builtin_fabsf(r0[k]) < few ? 1 : 0;
         small += __builtin_fabsf(r1[k]) < few ? 1 : 0;
     }
-    const uint64_t vote = __builtin_amdgcn_ballot_w64(ok && small > 16);
-    if (lane == 0) {  // (a byte a group; step s has groups s + s / 2 * 2 and two further)
-        uint32_t v = 0;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) v |= (vote & (0x00ff00ffull << (8 * (s + s / 2 * 2)))) != 0 ? 1u << s : 0u;
-        votes[wave] = v;
-    }
-    __syncthreads();
-    const bool wide = (((votes[0] | votes[1] | votes[2] | votes[3]) >> step) & 1u) != 0;
+    const bool wide = ok && small >= 10;
     const int at = 32 * kg + 8 * wave + r8;  // lane of the products
     unsigned char* const frag = out + step * kMxStepBytes;
     if (wide) {  // eight halves for each nibble of the lane's four words, in the place of the parts' bytes
@@ -255,7 +246,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
             *reinterpret_cast<u32x2*>(frag + p * kMxPartBytes + 1024 + at * 8) = u32x2{packed[4], packed[5]};
         }
     }
-    // the sum of the parts: of the values less what remains of them (fp16 steps are multiplied with digits, not with codes)
+    // the sum of the parts: of the values less what remains of them (fp16 groups are multiplied with digits, not with codes)
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         sum -= r0[k];

@@ -154,7 +154,8 @@ def test_code_three_counts_as_two(gpu, M, N, K):  # noqa: F811
 def test_outputs_beside_a_spike(gpu, M, N, K, half):  # noqa: F811
     """Activations with an offset rotate to a spike at a block's channel 0 (with one of their own for every 64 channels: at 0, 64,
     128, 192).  Outputs whose digits there are 0 are as good as with x~ in fp16: 2^-11 / sqrt(3) in norm, of
-    the rounding of x~ and, for fp16 results, of theirs.  In tiles of 32 rows with an offset, some with, and without."""
+    the rounding of x~ and, for fp16 results, of theirs.  Rows with an offset and without in one tile, and apart; a row's
+    bits do not depend on the others."""
     torch, binding = gpu
     codes, scales, _ = tensor(torch, binding, N, K, "spike", M, z_fraction=0.0)
     # digit 0 (code 1) at channels 0, 64, 128, 192 of the even columns: word 4 (16 g + r), bits 1:0, r even
@@ -168,7 +169,12 @@ def test_outputs_beside_a_spike(gpu, M, N, K, half):  # noqa: F811
     for rows in (torch.arange(M, device="cuda") % 6, torch.arange(M, device="cuda") // 32 % 6):
         offset = torch.tensor(classes, device="cuda")[rows][:, None]
         for X in ((noise + offset).half(), (noise + offset * sign).half()):
-            Y = binding.itq3s_matmul(codes, scales, N, K, X, dtype=torch.float16 if half else torch.float32).double()
+            def call(x):
+                return binding.itq3s_matmul(codes, scales, N, K, x, dtype=torch.float16 if half else torch.float32).double()
+
+            Y = call(X)
+            alone = rows % 2 == 0
+            assert torch.equal(call(torch.where(alone[:, None], X, noise.half()))[alone], Y[alone])
             want = X.double() @ What.T
             for i, c in enumerate(classes):
                 for cols in (slice(0, N, 2), slice(1, N, 2)):
@@ -179,9 +185,9 @@ def test_outputs_beside_a_spike(gpu, M, N, K, half):  # noqa: F811
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,rows", [(64, 40, 140032, 64), (2048, 4096, 16640, 33), (700, 1000, 2304, 1), (6300, 17, 256, 6300)])
-def test_fp16_steps_of_many_blocks(gpu, M, N, K, rows):  # noqa: F811
-    """More blocks with fp16 steps than a wavefront looks at in one go (64), every other block with some and without; in some
-    tiles of rows only, in all; one block."""
+def test_fp16_groups_of_many_blocks(gpu, M, N, K, rows):  # noqa: F811
+    """Blocks with groups of fp16 between blocks without, one step of a block and several; many blocks a wavefront; in some
+    tiles of rows only, in one row, in all; one block."""
     torch, binding = gpu
     codes, scales, What = tensor(torch, binding, N, K, "steps", M, z_fraction=0.02 if N < 5000 else 0.0)
     gen = torch.Generator(device="cuda").manual_seed(M)
