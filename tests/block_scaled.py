@@ -15,14 +15,17 @@ int main() {
     while (std::scanf("%lld %lld %lld", &M, &N, &K) == 3) {
         const itq3s::Route r = itq3s::many_row_route(M, N, K);
         const int64_t n = N;
-        long long items = 0;  // of a call with this tensor alone, for 256 units
-        if (r == itq3s::Route::rows) items = itq3s::rows_split((N + 15) / 16, M, K, 256).items;
-        else if (r == itq3s::Route::tiled) items = (M + 63) / 64 * ((N + 255) / 256);
-        else {
-            const int cols = r == itq3s::Route::shares4 ? 256 : 32 * itq3s::shares8_columns(&n, 1, M, K, 256);
-            items = (M + 31) / 32 * ((N + cols - 1) / cols);
+        // of a call with this tensor alone, for 256 units: items, and the columns of one
+        long long items = 0, cols = 256;
+        if (r == itq3s::Route::rows) {
+            const itq3s::RowsSplit s = itq3s::rows_split((N + 15) / 16, M, K, 256);
+            items = s.items;
+            cols = 16 * s.rt;
+        } else {
+            if (r == itq3s::Route::shares8) cols = 32 * itq3s::shares8_columns(&n, 1, M, K, 256);
+            items = (M + (r == itq3s::Route::tiled ? 63 : 31)) / (r == itq3s::Route::tiled ? 64 : 32) * ((N + cols - 1) / cols);
         }
-        std::printf("%d %lld\n", (int)r, items);
+        std::printf("%d %lld %lld\n", (int)r, items, cols);
     }
 }
 """
@@ -41,13 +44,13 @@ def _rule():
 
 
 @functools.lru_cache(maxsize=None)
-def route_and_items(M, N, K):
+def route_items_columns(M, N, K):
     out = subprocess.run([_rule()], input="%d %d %d\n" % (M, N, K), check=True, stdout=subprocess.PIPE, text=True).stdout.split()
-    return int(out[0]), int(out[1])
+    return tuple(int(v) for v in out)
 
 
 def route(M, N, K):
-    return route_and_items(M, N, K)[0]
+    return route_items_columns(M, N, K)[0]
 
 
 def holds_operand(torch, ws, X):

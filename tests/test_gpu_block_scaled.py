@@ -1,32 +1,40 @@
-"""The block-scaled kernels (fp4 digits, activations in three fp6 parts) at the sizes where their division of the work
+"""The block-scaled kernels (fp4 codes, activations in three fp6 parts) at the sizes where their division of the work
 changes: rows of every remainder modulo the tiles of 32 and 64, ragged columns, wavefronts without a block, several rounds,
 each number of columns an item has, tensors of one launch.  Against itq3s_dequantize and a dense fp64 product."""
 import pytest
 
-from tests.block_scaled import ROWS, SHARES4, SHARES8, TILED, route
+from tests.block_scaled import ROWS, SHARES4, SHARES8, TILED, route, route_items_columns
 from tests.test_gpu_rows import gpu, tensor  # noqa: F401  (gpu is a fixture)
 
-# M, N, K, the kernel that takes it
+# M, N, K, the kernel that takes it, the columns of an item and the rounds of one to a unit (K over wavefronts)
 SIZES = [
-    (481, 33, 3584, SHARES8),     # 14 blocks: two wavefronts have one, the others two; 32 columns an item
-    (1301, 100, 1280, SHARES8),   # five blocks: three wavefronts have none; 64 columns
-    (700, 1000, 2304, SHARES8),   # nine blocks; 128 columns
-    (500, 1000, 4096, SHARES8),
-    (20, 28672, 4096, SHARES8),   # rows: 12 of padding
-    (2113, 300, 8192, SHARES8),   # two rounds
-    (512, 4096, 4096, SHARES4),
-    (2081, 515, 1024, SHARES4),   # one block a wavefront, the last columns of an item beyond the tensor
-    (993, 1032, 4096, SHARES4),
-    (6300, 17, 256, TILED),     # one block, one storage tile and a ragged one, an odd number of tiles of 32 rows
-    (65, 65000, 512, TILED),    # one row in the second tile of 64
-    (640, 4100, 2560, TILED),
-    (33, 40000, 2816, TILED),
+    (481, 33, 3584, SHARES8, 32, 1),      # 14 blocks: two wavefronts have one, the others two
+    (1301, 100, 1280, SHARES8, 64, 1),    # five blocks: three wavefronts have none
+    (9000, 33, 1280, SHARES8, 64, 2),
+    (1338, 822, 1280, SHARES8, 128, 2),
+    (700, 1000, 2304, SHARES8, 128, 1),   # nine blocks
+    (500, 1000, 4096, SHARES8, 64, 1),
+    (20, 28672, 4096, SHARES8, 128, 1),   # rows: 12 of padding
+    (2113, 300, 8192, SHARES8, 128, 1),
+    (1233, 796, 28672, SHARES8, 64, 2),
+    (512, 4096, 4096, SHARES4, 256, 1),
+    (2081, 515, 1024, SHARES4, 256, 1),   # one block a wavefront, the last columns of an item beyond the tensor
+    (993, 1032, 4096, SHARES4, 256, 1),
+    (1067, 2300, 5120, SHARES4, 256, 2),
+    (197, 33013, 3072, SHARES4, 256, 4),
+    (6300, 17, 256, TILED, None, None),   # one block, one storage tile and a ragged one, an odd number of tiles of 32 rows
+    (65, 65000, 512, TILED, None, None),  # one row in the second tile of 64
+    (640, 4100, 2560, TILED, None, None),
+    (33, 40000, 2816, TILED, None, None),
 ]
 
 
 def test_sizes_take_the_routes_they_are_here_for():
-    for M, N, K, kernel in SIZES:
-        assert route(M, N, K) == kernel, (M, N, K)
+    for M, N, K, kernel, columns, rounds in SIZES:
+        got, items, got_columns = route_items_columns(M, N, K)
+        assert got == kernel, (M, N, K)
+        if columns is not None:
+            assert (got_columns, (items + 255) // 256) == (columns, rounds), (M, N, K)
     # besides: a group's thin tensors go where its wide ones go
     for M, K, Ns, many in ((512, 4096, (512, 1024, 4096), False), (58, 23040, (264, 2112), True), (48, 4096, (512, 4096), True)):
         assert [route(M, N, K) == ROWS for N in Ns] == [many] * len(Ns), (M, K, Ns)
@@ -54,8 +62,8 @@ def check(torch, Y, X, What, half):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K,route", SIZES)
-def test_block_scaled(gpu, M, N, K, route):  # noqa: F811
+@pytest.mark.parametrize("M,N,K", [s[:3] for s in SIZES])
+def test_block_scaled(gpu, M, N, K):  # noqa: F811
     torch, binding = gpu
     codes, scales, What = tensor(torch, binding, N, K, "mx", M, z_fraction=0.02 if N < 5000 else 0.0)
     buf = activations(torch, M, K + 8, M)
@@ -184,10 +192,10 @@ def test_outputs_beside_a_spike(gpu, M, N, K, half):  # noqa: F811
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K,rows", [(64, 40, 140032, 64), (2048, 4096, 16640, 33), (700, 1000, 2304, 1), (6300, 17, 256, 6300)])
+@pytest.mark.parametrize("M,N,K,rows", [(64, 40, 140032, 64), (2048, 4096, 16640, 33), (700, 1000, 2304, 1), (6300, 17, 256, 6300), (1338, 822, 1280, 700), (1067, 2300, 5120, 500)])
 def test_fp16_groups_of_many_blocks(gpu, M, N, K, rows):  # noqa: F811
     """Blocks with groups of fp16 between blocks without, one step of a block and several; many blocks a wavefront; in some
-    tiles of rows only, in one row, in all; one block."""
+    tiles of rows only, in one row, in all; one block; items of a second round."""
     torch, binding = gpu
     codes, scales, What = tensor(torch, binding, N, K, "steps", M, z_fraction=0.02 if N < 5000 else 0.0)
     gen = torch.Generator(device="cuda").manual_seed(M)

@@ -5,7 +5,7 @@ device against itq3s_dequantize (held to the oracle within 1e-6 elsewhere) and a
 import numpy as np
 import pytest
 
-from tests.block_scaled import ROWS, SHARES4, SHARES8, TILED, route, route_and_items
+from tests.block_scaled import ROWS, SHARES4, SHARES8, TILED, route, route_items_columns
 from tests.packed_inputs import random_packed
 
 pytestmark = pytest.mark.gpu
@@ -67,7 +67,8 @@ SIZES = [
 def test_many_rows(gpu, size):
     M, N, K, kernel = size if len(size) == 4 else (*size, ROWS)
     assert kernel is None or route(M, N, K) == kernel
-    assert (M, N, K) != (97, 13000, 512) or route_and_items(M, N, K)[1] > 256  # (an item to a unit)
+    if (M, N, K) == (97, 13000, 512):
+        assert route_items_columns(M, N, K)[1] > 256 and route_items_columns(M, N, K)[2] == 64
     torch, binding = gpu
     codes, scales, What = tensor(torch, binding, N, K, "rows", M)
     gen = torch.Generator(device="cuda").manual_seed(M + N)
