@@ -63,8 +63,9 @@ constexpr int kGemmLds = kScale + 2 * 1024;
 static_assert(kHalfBytes == 9 * 1024 && kMxMetaBytes == 512, "copies of 1 KiB");
 static_assert(2 * kGemmLds <= 160 * 1024 && kGemmLds <= 64 * 1024, "two workgroups per unit, no raised limit");
 
-// Copies global -> LDS, 16 bytes a lane: lane l of copy i to lds + 1024 i + 16 l from its offset + 1024 i.  (No register is
-// written.)
+// Copies global -> LDS, 16 bytes a lane: lane l of copy i to lds + 1024 i + 16 l from its offset + 1024 i.  (No vector
+// register is written; LDS is, which sync() orders for the compiler as well; and m0, which is reserved and so cannot be
+// named as clobbered: nothing else in a kernel with these copies may use it, which a test reads from the assembly.)
 template <int COUNT>
 __device__ __forceinline__ void dma16(u32x4 rsrc, int voffset, int soffset, uint32_t lds) {
     static_assert(COUNT == 1 || COUNT == 4, "");

@@ -205,6 +205,12 @@ def test_kernels_keep_their_registers(source):
     asm = subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
     kernels = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_private_segment_fixed_size (\d+)", asm, flags=re.S)
     assert kernels and [k for k in kernels if k[1] != "0"] == []
+    # the copies written in assembly set m0, which cannot be named as clobbered: where there are any, nothing else uses it
+    written, other = [], []
+    for block in re.split(r"(;;?#ASMSTART.*?;;?#ASMEND)", asm, flags=re.S):
+        (written if block.lstrip(";").startswith("#ASMSTART") else other).append(block)
+    assert not any(re.search(r"\bm0\b", b) for b in written) or not any(re.search(r"^\s+\w.*\bm0\b", b, flags=re.M) for b in other)
+    assert source != "gemm" or any(re.search(r"\bm0\b", b) for b in written)
 
 
 # us a call (weights cycled through memory): M, N, K, the tiled kernel (17 rows: two passes of the kernel for 16
