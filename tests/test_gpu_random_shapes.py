@@ -84,3 +84,32 @@ def test_other_matmul_routes_on_random_shapes(seed):
         want2 = X.double() @ binding.itq3s_dequantize_sub(c2, s2, u2, N, K).double().T
         assert rel(binding.itq3s_matmul_sub(c2, s2, u2, N, K, X, dtype=dtype), want2) <= 2e-3, ("sub", M, N, K)
         done += 1
+
+
+# M <= 4 (three rows in a kernel of four), 5 to 16, the many-row kernel, K over eight and over four wavefronts, tiles
+@pytest.mark.parametrize("M,N,K", [(1, 40, 2048), (3, 40, 2048), (3, 40, 1024), (3, 40, 8192), (5, 40, 1024), (13, 40, 1024), (20, 40, 1024), (33, 40, 2304),
+                                   (500, 1000, 4096), (517, 3000, 4096), (6300, 17, 256), (65, 64900, 512)])
+def test_what_stands_behind_the_operands_plays_no_part(M, N, K):
+    """Row tiles and activation rows beyond those of the call are asked for with empty ranges: behind the call's own, the same
+    buffers hold codes that would set the format flag and activations that are not finite."""
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_27914_amd import binding
+
+    rows = (N + 15) // 16 * 16 + 256
+    W = 0.02 * torch.randn((rows, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda")
+    sub = binding.itq3s_quantize_sub(W)
+    codes, scales = binding.itq3s_quantize(W)
+    for c in (codes, sub[0]):
+        c.view(-1, 384)[(N + 15) // 16 * (K // 256) :, 256:] = -1
+    X = torch.full((M + 64, K), float("nan"), dtype=torch.float16, device="cuda")
+    X[:M] = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M + 1), device="cuda").half()
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    Y = binding.itq3s_matmul(codes, scales, N, K, X[:M], status_flags=flags)
+    assert int(flags.item()) == 0 and bool(torch.isfinite(Y).all())
+    assert torch.equal(Y, binding.itq3s_matmul(*binding.itq3s_quantize(W[:N]), N, K, X[:M].clone()))
+    if M <= 64:
+        Y = binding.itq3s_matmul_sub(*sub, N, K, X[:M], status_flags=flags)
+        assert int(flags.item()) == 0 and bool(torch.isfinite(Y).all())
