@@ -78,8 +78,8 @@ size_t itq3s_scales_bytes(int64_t N, int64_t K);
  * (rounded up to 256 bytes; for M <= 32 those of a pass of 16 rows), 768 bytes and, where there are at most 128 tiles
  * of 128 x 256 outputs, 128 KB for each of them times min(256 / tiles, 8, K / 1024) if that is at least 2
  * would fit.  (The last is more than any route takes today; it stays the line between accepted and refused.)
- * A call with less room takes its rows in several turns, with the same bits, or a route that needs less, with
- * results that differ in the last bits. */
+ * A call with less room takes its rows in several turns, with the same bits and up to one and a half times the time
+ * (the weights are read once a turn), or a route that needs less, with results that differ in the last bits. */
 size_t itq3s_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /* Offline quantization (Alg. 1, Def. 1).  Per block: w' = H w in fp64 (butterfly stages
@@ -104,7 +104,8 @@ int itq3s_dequantize(const uint32_t *codes, const uint32_t *scales, int64_t N, i
 /* Fused matmul (problem statement of Alg. 2; Sec. 5.4 for M = 1):  Y[m][n] = sum_k X[m][k] w_hat[n][k].
  * No dequantized weight is written to memory.  M <= 16 takes the bandwidth-bound streaming path; more
  * rows a second streaming kernel up to the sizes where the block-scaled MFMA path (fp4 digits, activations in
- * three fp6 parts) is the faster one: wide tensors from 18 rows on, everything from 480 rows on.
+ * three fp6 parts) is the faster one: wide tensors from 18 rows on, from 480 rows on (fewer with K beyond 8192) every call of
+ * at least 1.6 million activations; a call with fewer by the same comparison as one with fewer rows.
  * Which path is a function of the three sizes (and of the room, see above).
  * M > 16 accepts K <= 4194304 only (ITQ3S_ERR_SHAPE beyond), M <= 16 K <= 2^28.  fp32 accumulation in
  * all, the zero-point terms included: an output element is rounded once.

@@ -19,7 +19,7 @@
 //
 // What bounds it: power and the instructions' turns.  Two 4096x14336 with 2048 rows: 340 us, 1.42 PFLOP/s, matrix pipes 54 % busy
 // at 1.87 GHz; the same with activations of zero, where the clock stays up, 262 us (a loop of nothing but these products
-// on random registers does 2.16 PFLOP/s at 1.64 GHz).  Vector instructions are 3 per product; without the copies
+// on random registers does 2.16 PFLOP/s at 1.64 GHz).  Vector instructions are 3.3 per product; without the copies
 // 300 us, without two of the three parts 215, without the scaling by d 334.  Measured without gain: three halves in LDS,
 // tiles of 64 x 128 (four or eight wavefronts), a second half of the workgroup on the other blocks of K.  Before
 // (fp16 operands, 128 x 256), whole calls in us: two 4096x14336 M = 2048 403 -> 350, 14336x4096 M = 2048 250 -> 188,

@@ -21,14 +21,15 @@
 // further up, at bits 11:10, a stored 3 would count as 4), so a shift of a low-plane word by a
 // multiple of four gives two half2 operands with one mask each; the factors are applied together with d.  Four-row decode is bound by this arithmetic (two of 4096x11008, M = 4: 5.5 us of
 // vector instructions in a launch of 11): the two positions took a sixth off a tile's share, and the rows
-// are rotated together, two by two, instead of one after another.  us, before / now (K x N): 11008x4096 M = 1 7.0 / 6.6, M = 4 9.5 / 8.6;
-// 28672x8192 M = 1 18.8 / 17.9, M = 4 25.0 / 22.5; 8192x57344 M = 4 39.5 / 36.5; 5120x5120 M = 4 7.4 / 6.8.
+// are rotated together, two by two, instead of one after another.  us, a shift a pair and row after row / now, launches
+// of a graph (K x N): 11008x4096 M = 1 5.9 / 5.8, M = 4 8.5 / 7.9; 28672x8192 M = 1 19.6 / 18.9, M = 4 25.6 / 24.0; two of
+// 8192x28672 M = 4 39.6 / 37.0; 5120x5120 M = 4 6.4 / 6.3; three 4096x4096 M = 1 6.1 / 6.3, M = 4 7.6 / 7.5.
 //
 // Work split: workgroup g (8 wavefronts) owns RT or RT-1 consecutive 16-row tiles of the launch and
 // all of K; wavefront w takes blocks w, w+8, ...  A step of a wavefront is one block against the
 // workgroup's row tiles: the tile loads of the next step are in flight (two register buffers) while
 // the wavefront rotates the 256 activations of its current block on the matrix cores, parks them in
-// its private 512 M bytes of LDS in operand order, and multiplies.  No wavefront waits for another
+// its private 576 M bytes of LDS in operand order, and multiplies.  No wavefront waits for another
 // before the cross-wavefront sum at the end.  Every load goes through a buffer descriptor: a row
 // tile the workgroup does not have gets an empty descriptor (its loads return zeros without touching
 // memory), so the step is branch-free.  The kernel needs 86 to 128 registers, which leaves room for

@@ -65,10 +65,13 @@ inline double rows_time(int64_t M, int64_t N, int64_t K, int units) {
 
 // Which kernel computes a tensor (M >= 17): among the block-scaled ones the fastest by the times above; the many-row kernel,
 // where its own rule takes the call,
-//  - below a line of rows (480, with K beyond 8192 fewer: 70 at 28672) and of 1.6 million activations, unless they save what
-//    a tensor an eighth as wide takes by itself, less its share of a joint launch.  The tensors of a group go each by this
-//    rule, and a thin one left behind costs a rotation and a launch with all of K: 2112 + 2112 + 264 columns, K = 23040,
-//    M = 58 44 us in one launch of the many-row kernel, 69 with the two wide tensors here and the thin one there.
+//  - below a line of rows (480, with K beyond 8192 fewer: 70 at 28672) or of 1.6 million activations, unless they save what
+//    a tensor an eighth as wide takes by itself, less its share of a joint launch: that is k or v beside q with grouped
+//    queries (8192 + 1024 + 1024 columns).  The tensors of a group go each by this rule, and a thin one left behind costs a
+//    rotation and a launch with all of K.  us, one launch of the many-row kernel / q here and k, v there by the faster
+//    kernel alone: K = 8192, 8192 + 1024 + 1024, M = 32 18.8 / 27.8, 48 22.1 / 32.6, 64 24.8 / 32.5, 100 40.6 / 40.0, 149 53.0 / 47.3, 300
+//    80.6 / 66.7; K = 4096, 4096 + 1024 + 1024, M = 100 16.6 / 24.6, 149 22.2 / 28.7, 256 25.1 / 33.4, 300 30.5 / 34.6, 400 44.0 / 35.1.  A tensor
+//    without such a sibling pays for it: 11008x4090, M = 149 30.6 / 27.3, 256 35.6 / 30.1; 8192x8192, M = 100 27.5 / 23.7.
 //  - above it, not at all, whatever the columns: from 1024 on the block-scaled kernels are the faster ones there (0.71 to
 //    1.0 of the time), and thinner tensors lose up to 5 % (512 columns, K = 8192, M = 366 21.1 / 22.2), 64 to 264 up to 10 %.
 // A rule on the sizes of one tensor (counted for 256 units), and how a kernel adds up depends on K alone: a grouped call

@@ -230,8 +230,9 @@ ROUTES = [
 
 
 def test_no_call_goes_to_the_slower_kernel(tmp_path):
-    """The many-row kernel takes a call only where it beats what computed it before, and wherever it
-    clearly does (sizes on both sides of each line of the rule, with the times that were measured)."""
+    """rows_path, which calls the many-row kernel may take: only where it beats what computed them before, and wherever it
+    clearly does (sizes on both sides of each line of the rule, with the times that were measured; the tiled kernel had
+    fp16 operands then.  Between it and the block-scaled kernels many_row_route decides, by times of its own)."""
     from paper_2603_27914_amd import build
 
     main = tmp_path / "rule.cpp"
