@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             unpack(n, next_step);
         }
     };
-    uint64_t any_wide = 0;
+    uint32_t any_wide = 0;
     auto order = [&](auto reads, auto head, auto next_step) {
         constexpr int kReads = decltype(reads)::value, kHead = decltype(head)::value, kUnpack = decltype(next_step)::value == 0 ? 4 : 8;
         __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
@@ -224,7 +224,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     auto begin_block = [&](int b) -> bool {
         const char* const meta = lds + kMeta + (b & 1) * 1024 + wm * kMxMetaBytes;
         scale_a = *reinterpret_cast<const int*>(meta + lane * 4);
-        any_wide |= __builtin_amdgcn_ballot_w64(wide_steps((uint32_t)scale_a) != 0u);
         uint32_t any = 0;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
@@ -303,6 +302,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         copy_half(b + 1, c0);
         ITQ3S_FENCE;
         load_a(a1, t1, 1, 1);
+        any_wide |= wide_steps((uint32_t)scale_a);
         all(a0, t0, c2, c1);
         order(second_reads, c0, c1);
         ITQ3S_FENCE;
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int n = 0; n < NT; ++n)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[n][v] = __builtin_fmaf(d[n], blk[n][v], acc[n][v]);
-    if (any_wide != 0 && wm < x_tiles) {  // (no second tile of 32 rows: its scales are read as 0 too)
+    if (__builtin_amdgcn_ballot_w64(any_wide != 0u) != 0 && wm < x_tiles) {  // (no second tile of 32 rows: its scales are read as 0 too)
         const int64_t tile0 = nt0 + wn * (2 * NT);
         const int rows = tensor_tiles - tile0 < 2 * NT ? (tensor_tiles > tile0 ? (int)(tensor_tiles - tile0) : 0) : 2 * NT;
         const int64_t from = rows > 0 ? tile0 * KB : 0;

@@ -1,6 +1,6 @@
 // What the block-scaled kernels (itq3s_mx.hip, itq3s_gemm.hip) do for groups of activations that are fp16: behind their main
 // loop, which has added nothing for them (scales of 0), a pass over the steps that have some, straight from memory.  So the
-// main loop has neither a branch nor a register for them, and its price is a comparison a block (a branch in front of the
+// main loop has neither a branch nor the registers for them, and its price is three instructions a block (a branch in front of the
 // products, or behind them, with the main loop's registers alive, put its sums into scratch).
 // The pass is bound by its products: four of 32x32x16 where a step has three at four times the rate.
 // us, normal activations / an offset of 4 deviations (one step of a block's four) / offsets of 30 that change every 64 channels (two):
