@@ -1,7 +1,9 @@
 """For the tests of the calls with more than 16 rows: which kernel takes a size (the host rule, compiled from its header), and
 the operand that the block-scaled kernels read, decoded from a workspace."""
+import atexit
 import functools
 import os
+import shutil
 import subprocess
 import tempfile
 
@@ -36,6 +38,7 @@ def _rule():
     from paper_2603_27914_amd import build
 
     folder = tempfile.mkdtemp(prefix="itq3s_rule_")
+    atexit.register(shutil.rmtree, folder, ignore_errors=True)
     source, exe = os.path.join(folder, "rule.cpp"), os.path.join(folder, "rule")
     with open(source, "w") as f:
         f.write(MAIN)
