@@ -2,7 +2,10 @@
 // loop, which has added nothing for them (scales of 0), a pass over the steps that have some, straight from memory.  So the
 // main loop has neither a branch nor the registers for them, and its price is three instructions a block (a branch in front of the
 // products, or behind them, with the main loop's registers alive, put its sums into scratch).
-// The pass is bound by its products: four of 32x32x16 where a step has three at four times the rate.
+// The pass is bound by its loads, 8 KB a step and wavefront through the address units, besides the products, four of 32x32x16 where a
+// step has three at four times the rate.  Neither two products a group instead of four a step (two 4096x14336 M = 2048 with an
+// offset 470 us, with more groups 775) nor half of the vector instructions (codes, and their offset from products with ones:
+// 483 and 626) was clearly faster.
 // us, normal activations / an offset of 4 deviations (one step of a block's four) / offsets of 30 that change every 64 channels (two):
 // 4096x4096 M = 512 24.9 / 30.5 / 35.6, two 4096x11008 M = 512 82 / 116 / 146, two 4096x14336 M = 2048 345 / 483 / 613 (a
 // kernel with fp16 operands throughout: 33, 92, 349).
